@@ -1,7 +1,6 @@
-// k_plain64.hip -- FP64 plain particle path: absolute FP64 positions, one
-// thread per particle, fields read from global memory, current added with
-// FP64 atomics.  This is the reference-precision GPU path the FP32 split path
-// is measured against.
+// k_plain64.hip -- FP64 particles: beam sampling, plasma lattice sheets and
+// compaction.  Absolute FP64 positions in slots; the step works on them tile by
+// tile (k_tiles64.hip).
 #include "pic_internal.h"
 
 namespace pic {
@@ -109,126 +108,6 @@ void launch_inject64(const Params &P, int64_t l0, int64_t nsheets, double t, Par
     int64_t total = nsheets * sheet_particles(P);
     if (total <= 0) return;
     hipLaunchKernelGGL(k_inject64, dim3(nblocks(total, 256)), dim3(256), 0, st, P, l0, total, t, p, slot0);
-}
-
-// ---------------------------------------------------------------- the step
-// Field value of one Yee component at absolute position X, quadratic shape at
-// the component's own staggered sites (sx, sy, sz in {0, 1/2}).
-__device__ inline double gather64(const Params &P, const StepCtx &S, const double *F, const double X[3], int sx,
-                                  int sy, int sz) {
-    double wx[3], wy[3], wz[3];
-    int64_t lo[3];
-    const int st[3] = {sx, sy, sz};
-    double *ws[3] = {wx, wy, wz};
-    for (int d = 0; d < 3; ++d) {
-        double off = st[d] ? 0.5 : 0.0;
-        double n = floor(X[d] - off + 0.5);
-        weights3<double>(X[d] - off - n, ws[d]);
-        lo[d] = (int64_t)n - 1;
-    }
-    double acc = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        int p = ring_plane((int)(lo[2] + c - S.k0), S.k0r, P.nz);
-        for (int b = 0; b < 3; ++b) {
-            double wyz = wy[b] * wz[c];
-            for (int a = 0; a < 3; ++a)
-                acc += wx[a] * wyz * F[cell_index(P, (int)(lo[0] + a), (int)(lo[1] + b), p)];
-        }
-    }
-    return acc;
-}
-
-// Esirkepov (2001) current of the move X0 -> X1 (|dX| < 1 per axis) with
-// quadratic shapes, on the tight four-node window of each axis:
-//   W_c = DS_c (S0_a S0_b + DS_a S0_b / 2 + S0_a DS_b / 2 + DS_a DS_b / 3),
-//   J_c(m + 1/2) = J_c(m - 1/2) - q w W_c(m) / dt (running sum from below),
-// the fourth running sum vanishing identically.  q w = -w: electrons carry
-// w > 0, mobile ions w < 0.
-__device__ inline void deposit64(const Params &P, const StepCtx &S, double *J[3], const double X0[3],
-                                 const double X1[3], double w) {
-    double S0[3][4], DS[3][4];
-    int64_t base[3];
-    for (int d = 0; d < 3; ++d) {
-        int64_t n0 = (int64_t)floor(X0[d] + 0.5), n1 = (int64_t)floor(X1[d] + 0.5);
-        base[d] = (n0 < n1 ? n0 : n1) - 1;
-        for (int m = 0; m < 4; ++m) {
-            double node = (double)(base[d] + m);
-            S0[d][m] = spline2<double>(X0[d] - node);
-            DS[d][m] = spline2<double>(X1[d] - node) - S0[d][m];
-        }
-    }
-    double f = w / P.dt;  // -q w / dt
-    for (int c = 0; c < 3; ++c) {
-        int ca = (c + 1) % 3, cb = (c + 2) % 3;
-        for (int ma = 0; ma < 4; ++ma)
-            for (int mb = 0; mb < 4; ++mb) {
-                double A = S0[ca][ma] * S0[cb][mb] + 0.5 * DS[ca][ma] * S0[cb][mb] + 0.5 * S0[ca][ma] * DS[cb][mb] +
-                           DS[ca][ma] * DS[cb][mb] * (1.0 / 3.0);
-                if (A == 0.0) continue;
-                double run = 0.0;
-                for (int m = 0; m < 3; ++m) {
-                    run += DS[c][m] * A;
-                    if (run == 0.0) continue;
-                    int64_t id[3];
-                    id[c] = base[c] + m;
-                    id[ca] = base[ca] + ma;
-                    id[cb] = base[cb] + mb;
-                    int p = ring_plane((int)(id[2] - S.k0), S.k0r, P.nz);
-                    atomicAdd(&J[c][cell_index(P, (int)id[0], (int)id[1], p)], f * run);
-                }
-            }
-    }
-}
-
-__global__ void __launch_bounds__(256) k_step64(Params P, StepCtx S, Part64 p, int64_t n, FieldsT<double> f,
-                                                double *Jx, double *Jy, double *Jz, int32_t *flags) {
-    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n || !p.alive[q]) return;
-    double X[3] = {p.x[q], p.y[q], p.z[q]};
-    double U[3] = {p.ux[q], p.uy[q], p.uz[q]};
-    double E[3], B[3], Ee[3], Be[3], dEe[3], dBe[3];
-    E[0] = gather64(P, S, f.E[0], X, 1, 0, 0);
-    E[1] = gather64(P, S, f.E[1], X, 0, 1, 0);
-    E[2] = gather64(P, S, f.E[2], X, 0, 0, 1);
-    B[0] = gather64(P, S, f.B[0], X, 0, 1, 1);
-    B[1] = gather64(P, S, f.B[1], X, 1, 0, 1);
-    B[2] = gather64(P, S, f.B[2], X, 1, 1, 0);
-    ext_field64(P, X[2], S.t, Ee, Be, dEe, dBe);
-    for (int d = 0; d < 3; ++d) {
-        E[d] += Ee[d];
-        B[d] += Be[d];
-    }
-    double Un[3];
-    push<double>(P.pusher, p.w[q] < 0.0 ? P.ahi : -0.5 * P.dt, U, E, B, Un);
-    double g = sqrt(1.0 + dot3(Un, Un));
-    double X1[3];
-    for (int d = 0; d < 3; ++d) X1[d] = X[d] + P.dt * Un[d] / g;
-    if (!(isfinite(X1[0]) && isfinite(X1[1]) && isfinite(X1[2]) && isfinite(g))) {
-        // never let a non-finite position reach the index arithmetic: drop the particle
-        atomicOr(flags, DFLAG_NONFINITE);
-        p.alive[q] = 0;
-        return;
-    }
-    double *J[3] = {Jx, Jy, Jz};
-    deposit64(P, S, J, X, X1, p.w[q]);
-    if (X1[0] < 0) X1[0] += P.nx;
-    if (X1[0] >= P.nx) X1[0] -= P.nx;
-    if (X1[1] < 0) X1[1] += P.ny;
-    if (X1[1] >= P.ny) X1[1] -= P.ny;
-    p.x[q] = X1[0];
-    p.y[q] = X1[1];
-    p.z[q] = X1[2];
-    p.ux[q] = Un[0];
-    p.uy[q] = Un[1];
-    p.uz[q] = Un[2];
-    // window after this step's shift: active band [k0n + 3, k0n + nz - 4)
-    if (X1[2] < (double)(S.k0n + 3) || X1[2] >= (double)(S.k0n + P.nz - 4)) p.alive[q] = 0;
-}
-
-void launch_step64(const Params &P, const StepCtx &S, Part64 p, int64_t n, FieldsT<double> f, double *J[3],
-                   int32_t *flags, hipStream_t st) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_step64, dim3(nblocks(n, 256)), dim3(256), 0, st, P, S, p, n, f, J[0], J[1], J[2], flags);
 }
 
 // ---------------------------------------------------------------- compaction

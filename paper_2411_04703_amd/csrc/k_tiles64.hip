@@ -1,0 +1,524 @@
+// k_tiles64.hip -- FP64 particle step on cell tiles: per-call particle lists of
+// every tile, then gather, push, move and deposit with the tile's fields and
+// currents in LDS.  FP64 throughout (absolute positions, FP64 sums).
+#include <algorithm>
+
+#include "tiles64.h"
+
+namespace pic {
+
+constexpr int LT = 256;   // threads of the list kernels
+constexpr int ST64 = 512; // threads of the step kernel
+
+// ---------------------------------------------------------------- lists
+bool tiles64_flat(const Params &P) { return P.ny == 1; }
+
+void tiles64_dims(const Params &P, int &ntx, int &nty, int &ntz) {
+    const bool flat = tiles64_flat(P);
+    const int tx = flat ? Geom2D::TX : Geom3D::TX, ty = flat ? Geom2D::TY : Geom3D::TY,
+              tz = flat ? Geom2D::TZ : Geom3D::TZ;
+    ntx = (P.nx + tx - 1) / tx;
+    nty = (P.ny + ty - 1) / ty;
+    ntz = (P.nz + tz - 1) / tz;
+}
+
+// Particles per item: few flushes of a crowded tile in large runs, half a workgroup in small ones,
+// where the items would leave compute units idle (110 k particles: 43 us a step at 256, 48 at 512).
+constexpr int CHUNK_MIN = ST64 / 2;
+static int chunk_of(int64_t slots) {
+    return slots >= (int64_t)1 << 22 ? 4 * ST64 : (slots >= (int64_t)1 << 18 ? ST64 : CHUNK_MIN);
+}
+
+static uint64_t al(uint64_t v) { return (v + 255) & ~(uint64_t)255; }
+
+static int64_t bins_of(const Params &P) {
+    int a, b, c;
+    tiles64_dims(P, a, b, c);
+    return (int64_t)a * b * c;
+}
+
+uint64_t tiles64_bytes(const Params &P, int64_t slots) {
+    const uint64_t nb = (uint64_t)bins_of(P), n = (uint64_t)std::max<int64_t>(slots, 1);
+    return 2 * al(4 * nb) + 3 * al(4 * n) + al(16 * (nb + n / CHUNK_MIN + 16)) + 256 * 9;
+}
+
+// cell (i, j in the grid, l logical) of an absolute position; false outside the window or not finite
+__device__ inline bool locate64(const Params &P, int64_t k0, double x, double y, double z, int &i, int &j, int &l) {
+    const double zl = floor(z) - (double)k0;
+    if (!(zl >= 0.0 && zl < (double)P.nz) || !isfinite(x) || !isfinite(y)) return false;
+    l = (int)zl;
+    i = (int)floor(x);
+    j = (int)floor(y);
+    if (i < 0 || i >= P.nx) i = wrapi(i, P.nx);
+    if (j < 0 || j >= P.ny) j = wrapi(j, P.ny);
+    return true;
+}
+
+// Bin of every live particle and its place there.  A block counts its particles in an LDS hash
+// table of bins and adds each bin's count to the global one once: a beam's particles come in no
+// order and crowd a few hundred bins, whose counters took 0.60 ms for 4.2 M particles when every
+// wave added to them (0.07 ms with the table).  A particle that finds no slot in 16 probes counts
+// globally.  A live particle that is not finite or outside the window is taken out.
+constexpr int CT = 1024, HB = 13;
+template <int PPT>
+__global__ void __launch_bounds__(CT) k_tile_count(Params P, int64_t k0, Species64 b, Species64 p, int lgx, int lgy,
+                                                   int lgz, TileList T, int32_t *flags) {
+    __shared__ uint32_t hkey[1 << HB], hcnt[1 << HB];
+    for (int e = threadIdx.x; e < 1 << HB; e += CT) {
+        hkey[e] = NO_BIN;
+        hcnt[e] = 0;
+    }
+    __syncthreads();
+    const int64_t q0 = (int64_t)blockIdx.x * (CT * PPT) + threadIdx.x;
+    uint32_t key[PPT], place[PPT];
+    int slot[PPT];
+#pragma unroll
+    for (int v = 0; v < PPT; ++v) {
+        const int64_t q = q0 + v * CT;
+        const bool beam = q < b.n;
+        const int64_t s = beam ? q : q - b.n;
+        const Species64 S = beam ? b : p;
+        key[v] = NO_BIN;
+        if (q < b.n + p.n && S.alive()[s]) {
+            const double x = S.x[s], y = S.x[S.cap + s], z = S.x[2 * S.cap + s];
+            int i, j, l;
+            if (locate64(P, k0, x, y, z, i, j, l)) {
+                key[v] = (uint32_t)((i >> lgx) + T.ntx * ((j >> lgy) + T.nty * (l >> lgz)));
+            } else {
+                S.alive()[s] = 0;
+                if (!(isfinite(x) && isfinite(y) && isfinite(z))) atomicOr(flags, DFLAG_NONFINITE);
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < PPT; ++v) {
+        slot[v] = -1;
+        place[v] = 0;
+        if (key[v] == NO_BIN) continue;
+        uint32_t h = (key[v] * 2654435761u) >> (32 - HB);
+        for (int probe = 0; probe < 16; ++probe, h = (h + 1) & ((1 << HB) - 1)) {
+            uint32_t have = hkey[h];
+            if (have == NO_BIN) have = atomicCAS(&hkey[h], NO_BIN, key[v]);
+            if (have == NO_BIN || have == key[v]) {
+                slot[v] = (int)h;
+                break;
+            }
+        }
+        place[v] = slot[v] >= 0 ? atomicAdd(&hcnt[slot[v]], 1u) : atomicAdd(&T.cnt[key[v]], 1u);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 1 << HB; e += CT) {
+        const uint32_t n = hcnt[e];
+        if (n) hcnt[e] = atomicAdd(&T.cnt[hkey[e]], n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < PPT; ++v) {
+        const int64_t q = q0 + v * CT;
+        if (q >= b.n + p.n) continue;
+        T.key[q] = key[v];
+        T.rank[q] = place[v] + (slot[v] >= 0 ? hcnt[slot[v]] : 0u);
+    }
+}
+
+// First list entry of every bin and the work items; clears the counts.  One block.
+__global__ void __launch_bounds__(1024) k_tile_scan(TileList T, int per_queue) {
+    constexpr int V = 4;
+    __shared__ uint32_t wn[16], wi[16];
+    __shared__ uint32_t run_n, run_i;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t == 0) run_n = run_i = 0;
+    if (t < 8) T.qnext[t * QPAD64] = per_queue;  // the workgroups' first items are taken by number
+    __syncthreads();
+    for (int base = 0; base < T.nbins; base += 1024 * V) {
+        uint32_t n[V], it[V], sn = 0, si = 0;
+        for (int v = 0; v < V; ++v) {
+            const int bin = base + t * V + v;
+            n[v] = bin < T.nbins ? T.cnt[bin] : 0u;
+            it[v] = (n[v] + T.chunk - 1) / T.chunk;
+            sn += n[v];
+            si += it[v];
+        }
+        uint32_t an = sn, ai = si;  // inclusive scans over the wave, then over the waves
+        for (int k = 1; k < 64; k <<= 1) {
+            const uint32_t un = __shfl_up(an, k), ui = __shfl_up(ai, k);
+            if (lane >= k) {
+                an += un;
+                ai += ui;
+            }
+        }
+        if (lane == 63) {
+            wn[wave] = an;
+            wi[wave] = ai;
+        }
+        __syncthreads();
+        uint32_t pn = run_n, pi = run_i;
+        for (int w = 0; w < wave; ++w) {
+            pn += wn[w];
+            pi += wi[w];
+        }
+        pn += an - sn;
+        pi += ai - si;
+        for (int v = 0; v < V; ++v) {
+            const int bin = base + t * V + v;
+            if (bin < T.nbins) {
+                T.off[bin] = pn;
+                T.cnt[bin] = 0;
+                for (uint32_t k = 0; k < it[v]; ++k)
+                    T.items[pi + k] = make_int4(bin, (int)(pn + k * T.chunk),
+                                                (int)(pn + min(n[v], (k + 1) * (uint32_t)T.chunk)), 0);
+            }
+            pn += n[v];
+            pi += it[v];
+        }
+        __syncthreads();
+        if (t == 1023) {
+            run_n = pn;
+            run_i = pi;
+        }
+        __syncthreads();
+    }
+    if (t == 0) *T.nitems = (int)run_i;
+}
+
+__global__ void __launch_bounds__(LT) k_tile_scatter(int64_t n, TileList T) {
+    const int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x;
+    if (q >= n) return;
+    const uint32_t key = T.key[q];
+    if (key != NO_BIN) T.list[T.off[key] + T.rank[q]] = (uint32_t)q;
+}
+
+void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid) {
+    const int64_t n = b.n + p.n;
+    const bool flat = tiles64_flat(c.P);
+    c.tiles.chunk = chunk_of(n);
+    const int lgx = 3, lgy = flat ? 0 : 3, lgz = flat ? 4 : 2;
+    if (n >= (int64_t)1 << 21)  // many particles a thread where there are blocks enough all the same
+        hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(n, 8 * CT)), dim3(CT), 0, c.st, c.P, c.k0, b, p, lgx, lgy,
+                           lgz, c.tiles, c.dflags);
+    else if (n > 0)
+        hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(n, CT)), dim3(CT), 0, c.st, c.P, c.k0, b, p, lgx, lgy, lgz,
+                           c.tiles, c.dflags);
+    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, c.st, c.tiles, grid / 8);
+    if (n > 0) hipLaunchKernelGGL(k_tile_scatter, dim3(nblocks(n, LT)), dim3(LT), 0, c.st, n, c.tiles);
+}
+
+// ---------------------------------------------------------------- the step
+// Weights of the three integer nodes around a coordinate: n the nearest node's distance above the
+// cell's lower node (0 or 1), w the weights of n - 1, n, n + 1.
+__device__ inline int near_int(double x, double fl, double w[3]) {
+    const double n = floor(x + 0.5);
+    weights3<double>(x - n, w);
+    return (int)(n - fl);
+}
+
+template <class G, int K> __device__ inline double gather_lds(const double *F, const double wi[3][3],
+                                                              const double wh[3][3], const int bi[3], const int bh[3]) {
+    constexpr bool hx = G::half(K, 0), hy = G::half(K, 1), hz = G::half(K, 2);
+    const double *wx = hx ? wh[0] : wi[0], *wy = hy ? wh[1] : wi[1], *wz = hz ? wh[2] : wi[2];
+    constexpr int SY = G::FX, SZ = G::FX * G::FY;
+    const double *f = F + K * G::NB + (hx ? bh[0] : bi[0]) + SY * (hy ? bh[1] : bi[1]) + SZ * (hz ? bh[2] : bi[2]);
+    double v = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double py = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const double *r = f + SY * b + SZ * c;
+            py = fma(wy[b], fma(wx[2], r[2], fma(wx[1], r[1], wx[0] * r[0])), py);
+        }
+        v = fma(wz[c], py, v);
+    }
+    // the sum is taken here: left to itself the compiler sinks the arithmetic of all six components
+    // below their 162 reads and spills what they returned
+    asm volatile("" : "+v"(v));
+    __builtin_amdgcn_sched_barrier(0);
+    return v;
+}
+
+// Hides v's value from the optimiser, so that what is computed from it is not hoisted out of the
+// work-item loop and kept live (or spilled) across it.
+__device__ inline void opaque64(int &v) { asm volatile("" : "+v"(v)); }
+
+// The six fields of the tile into LDS (nodes outside the window: 0, never gathered with a nonzero
+// weight).  A thread takes whole nodes: one address for six loads.  load() leaves all of a thread's
+// loads in flight together, store() writes what came.
+template <class G> struct Stage64 {
+    static constexpr int R = (G::NB + ST64 - 1) / ST64;
+    double v[R][6];
+    __device__ void load(const Params &P, int k0r, const Item64 &I, const FieldsT<double> &f) {
+        const double *src[6] = {f.E[0], f.E[1], f.E[2], f.B[0], f.B[1], f.B[2]};
+        int e0 = threadIdx.x;
+        opaque64(e0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = e0 + r * ST64, y = e / G::FX, a = e - y * G::FX, c = y / G::FY, b = y - c * G::FY;
+            const int l = I.t0z - 1 + c;
+            const bool in = e < G::NB && l >= 0 && l < P.nz;
+            const int64_t o = in ? cell_near(P, I.t0x - 1 + a, I.t0y - 1 + b, ring_plane(l, k0r, P.nz)) : 0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[r][k] = in ? src[k][o] : 0.0;
+        }
+    }
+    __device__ void store(double *F) const {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = threadIdx.x + r * ST64;
+            if (e < G::NB)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) F[k * G::NB + e] = v[r][k];
+        }
+    }
+};
+
+// current box of component K to the grid, cleared
+template <class G, int K> __device__ inline void flush_lds(const Params &P, int k0r, const Item64 &I, double *Js,
+                                                           double *J) {
+    constexpr int X = G::jx(K), Y = G::jy(K), N = G::jsize(K);
+    int e = threadIdx.x;
+    opaque64(e);
+    for (; e < N; e += ST64) {
+        const double v = Js[G::jofs(K) + e];
+        if (v == 0.0) continue;
+        Js[G::jofs(K) + e] = 0.0;
+        const int r = e / X, a = e - r * X, c = r / Y, b = r - c * Y;
+        const int l = I.t0z - 2 + c;
+        if (l >= 0 && l < P.nz) atomicAdd(&J[cell_near(P, I.t0x - 2 + a, I.t0y - 2 + b, ring_plane(l, k0r, P.nz))], v);
+    }
+}
+
+// One component of the Esirkepov current (the scheme is described at esk_component in k_split32.hip:
+// the same factorisation J_c(m, a, b) = f P_c[m] A_c[a][b], here in FP64): a window's last node only
+// where some lane of the wave crosses a half cell, a component only where some lane moves along it.
+template <class G, int C> __device__ inline void deposit_lds(double *Js, const int jb[3], const double S0[3][4],
+                                                             const double DS[3][4], const bool cross[3], double f) {
+    constexpr int CA = (C + 1) % 3, CB = (C + 2) % 3;
+    constexpr int ST[3] = {1, G::jx(C), G::jx(C) * G::jy(C)};
+    double P[3];
+    P[0] = DS[C][0] * f;
+    P[1] = (DS[C][0] + DS[C][1]) * f;
+    P[2] = (DS[C][0] + DS[C][1] + DS[C][2]) * f;  // the running sum, rounded as the rigid ions' is
+    if (!__any(P[0] != 0.0 || P[1] != 0.0 || P[2] != 0.0)) return;
+    double *o = Js + G::jofs(C) + jb[0] + ST[1] * jb[1] + ST[2] * jb[2];
+    const bool m2 = __any(cross[C]), a3 = __any(cross[CA]), b3 = __any(cross[CB]);
+    double ub[4], vb[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        ub[b] = fma(0.5, DS[CB][b], S0[CB][b]);
+        vb[b] = fma(1.0 / 3.0, DS[CB][b], 0.5 * S0[CB][b]);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        if (a == 3 && !a3) break;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b == 3 && !b3) break;
+            const double A = fma(S0[CA][a], ub[b], DS[CA][a] * vb[b]);
+            double *e = o + ST[CA] * a + ST[CB] * b;
+            atomicAdd(e, A * P[0]);
+            atomicAdd(e + ST[C], A * P[1]);
+            if (m2) atomicAdd(e + 2 * ST[C], A * P[2]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// a particle as loaded, and its number in the list
+struct Raw64 {
+    double X[3], U[3], w;
+    uint32_t id;
+};
+
+// where a particle's x is (the other arrays follow `cap` doubles apart), and its alive flag
+__device__ inline double *slot64(const Species64 &sb, const Species64 &sp, uint32_t id, int64_t &cap, int32_t *&alive) {
+    const bool beam = id < (uint32_t)sb.n;
+    const uint32_t s = beam ? id : id - (uint32_t)sb.n;
+    double *const x0 = beam ? sb.x : sp.x;
+    cap = beam ? sb.cap : sp.cap;
+    alive = (int32_t *)(x0 + 7 * cap) + s;
+    return x0 + s;
+}
+
+__device__ inline Raw64 load_raw64(const Species64 &sb, const Species64 &sp, uint32_t id) {
+    Raw64 r;
+    int64_t cap;
+    int32_t *alive;
+    const double *at = slot64(sb, sp, id, cap, alive);
+    r.id = id;
+    for (int d = 0; d < 3; ++d) {
+        r.X[d] = at[d * cap];
+        r.U[d] = at[(3 + d) * cap];
+    }
+    r.w = at[6 * cap];
+    return r;
+}
+
+// Per item: stage the tile's E and B (B^n, already advanced), then per particle gather, push, move
+// and deposit into the LDS current boxes, which are added to the grid at the end.  One thread per
+// particle over the grid (fields from global memory, every contribution a global FP64 atomic) took
+// 25.5 ms for the 128x128x512 run's 4.2 M beam and 16.5 M plasma particles; this takes 2.1 ms and
+// its lists 0.37.  Bound: the plasma's 1.2 ms by VALU (1430 instructions a wave, 55 % busy) and LDS
+// (162 reads and 27 to 144 FP64 adds of 8 clocks a wave), the beam's 0.9 ms by its slots, which are
+// in no order (a 64-byte line for every 8 bytes read or written; 0.4 ms were they in tile order).
+// Two 512-thread workgroups share a CU, so that one's rounds run under the other's staging and
+// flush; 512 is the particles of a tile at 2 per cell (384 threads: 2.9 ms, 256: 2.2 ms).  128
+// VGPRs spill 30, nearly all outside the particle loop.  The next item is claimed when the current
+// one starts; loading its fields and particles across the flush as well took 10 to 40 % longer
+// (spills).
+template <class G>
+__global__ void __launch_bounds__(ST64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_step64(Params P, StepCtx S, Species64 sb, Species64 sp, TileList T, FieldsT<double> f, double *Jx, double *Jy,
+         double *Jz, int32_t *flags) {
+    extern __shared__ __align__(16) double sm64[];
+    __shared__ int s_item;
+    double *F = sm64, *Js = sm64 + G::NF;
+    for (int e = threadIdx.x; e < G::NJ; e += ST64) Js[e] = 0.0;
+    const uint32_t tid = threadIdx.x;
+    ItemQueue64 Q;
+    if (tid == 0) s_item = Q.first(T);
+    __syncthreads();
+    int cur = __builtin_amdgcn_readfirstlane(s_item);
+    while (cur >= 0) {
+        const Item64 I = item64(T, cur, G::TX, G::TY, G::TZ);
+        Stage64<G> st;
+        st.load(P, S.k0r, I, f);
+        Raw64 r = load_raw64(sb, sp, T.list[min(I.begin + tid, I.end - 1)]);
+        st.store(F);
+        __syncthreads();  // fields staged, boxes clear, s_item read
+        if (tid == 0) Q.claim(T);
+        for (uint32_t base = I.begin; base < I.end; base += ST64) {
+            if (base > I.begin) r = load_raw64(sb, sp, T.list[min(base + tid, I.end - 1)]);
+            if (base + tid >= I.end) continue;
+            double X1[3], Un[3], wi[3][3], fl[3];
+            int c0[3], bi[3];
+            (void)locate64(P, S.k0, r.X[0], r.X[1], r.X[2], c0[0], c0[1], c0[2]);
+            c0[0] -= I.t0x;
+            c0[1] -= I.t0y;
+            c0[2] -= I.t0z;
+            double wh[3][3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                fl[d] = floor(r.X[d]);
+                bi[d] = c0[d] + near_int(r.X[d], fl[d], wi[d]);
+                weights3<double>(r.X[d] - 0.5 - fl[d], wh[d]);
+            }
+            double E[3], B[3], Ee[3], Be[3], dEe[3], dBe[3];
+            E[0] = gather_lds<G, 0>(F, wi, wh, bi, c0);
+            E[1] = gather_lds<G, 1>(F, wi, wh, bi, c0);
+            E[2] = gather_lds<G, 2>(F, wi, wh, bi, c0);
+            B[0] = gather_lds<G, 3>(F, wi, wh, bi, c0);
+            B[1] = gather_lds<G, 4>(F, wi, wh, bi, c0);
+            B[2] = gather_lds<G, 5>(F, wi, wh, bi, c0);
+            ext_field64(P, r.X[2], S.t, Ee, Be, dEe, dBe);
+            for (int d = 0; d < 3; ++d) {
+                E[d] += Ee[d];
+                B[d] += Be[d];
+            }
+            push<double>(P.pusher, r.w < 0.0 ? P.ahi : -0.5 * P.dt, r.U, E, B, Un);
+            const double g = sqrt(1.0 + dot3(Un, Un));
+            for (int d = 0; d < 3; ++d) X1[d] = r.X[d] + P.dt * Un[d] / g;
+            int64_t cap;
+            int32_t *alive;
+            double *const at = slot64(sb, sp, r.id, cap, alive);
+            if (!(isfinite(X1[0]) && isfinite(X1[1]) && isfinite(X1[2]) && isfinite(g))) {
+                // never let a non-finite position reach the index arithmetic: drop the particle
+                atomicOr(flags, DFLAG_NONFINITE);
+                *alive = 0;
+                continue;
+            }
+            double S0[3][4], DS[3][4];
+            int jb[3];
+            bool cross[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int n0 = bi[d] - c0[d];
+                double w1[3];
+                const int n1 = near_int(X1[d], fl[d], w1), lo = n0 < n1 ? n0 : n1;
+                const bool h0 = n0 > lo, h1 = n1 > lo;
+                cross[d] = n0 != n1;
+                jb[d] = c0[d] + lo + 1;  // box node of offset lo - 1, origin -2
+                S0[d][0] = h0 ? 0.0 : wi[d][0];
+                S0[d][1] = h0 ? wi[d][0] : wi[d][1];
+                S0[d][2] = h0 ? wi[d][1] : wi[d][2];
+                S0[d][3] = h0 ? wi[d][2] : 0.0;
+                DS[d][0] = (h1 ? 0.0 : w1[0]) - S0[d][0];
+                DS[d][1] = (h1 ? w1[0] : w1[1]) - S0[d][1];
+                DS[d][2] = (h1 ? w1[1] : w1[2]) - S0[d][2];
+                DS[d][3] = (h1 ? w1[2] : 0.0) - S0[d][3];
+            }
+            if (X1[0] < 0) X1[0] += P.nx;
+            if (X1[0] >= P.nx) X1[0] -= P.nx;
+            if (X1[1] < 0) X1[1] += P.ny;
+            if (X1[1] >= P.ny) X1[1] -= P.ny;
+            for (int d = 0; d < 3; ++d) {
+                at[d * cap] = X1[d];
+                at[(3 + d) * cap] = Un[d];
+            }
+            // window after this step's shift: active band [k0n + 3, k0n + nz - 4)
+            if (X1[2] < (double)(S.k0n + 3) || X1[2] >= (double)(S.k0n + P.nz - 4)) *alive = 0;
+            const double fq = r.w / P.dt;  // -q w / dt
+            deposit_lds<G, 0>(Js, jb, S0, DS, cross, fq);
+            deposit_lds<G, 1>(Js, jb, S0, DS, cross, fq);
+            deposit_lds<G, 2>(Js, jb, S0, DS, cross, fq);
+        }
+        if (tid == 0) s_item = Q.resolve(T);
+        __syncthreads();  // every deposit is in the boxes
+        cur = __builtin_amdgcn_readfirstlane(s_item);
+        flush_lds<G, 0>(P, S.k0r, I, Js, Jx);
+        flush_lds<G, 1>(P, S.k0r, I, Js, Jy);
+        flush_lds<G, 2>(P, S.k0r, I, Js, Jz);
+    }
+}
+
+template <class G> static constexpr int step_lds() { return 8 * (G::NF + G::NJ); }
+
+pic_status tiles64_carve(Ctx &c, char *base, int64_t slots) {
+    const uint64_t nb = (uint64_t)bins_of(c.P), n = (uint64_t)std::max<int64_t>(slots, 1);
+    TileList &T = c.tiles;
+    tiles64_dims(c.P, T.ntx, T.nty, T.ntz);
+    T.nbins = (int)nb;
+    auto take = [&](uint64_t bytes) {
+        char *r = base;
+        base += al(bytes);
+        return r;
+    };
+    T.cnt = (uint32_t *)take(4 * nb);
+    T.off = (uint32_t *)take(4 * nb);
+    T.key = (uint32_t *)take(4 * n);
+    T.rank = (uint32_t *)take(4 * n);
+    T.list = (uint32_t *)take(4 * n);
+    T.items = (int4 *)take(16 * (nb + n / CHUNK_MIN + 16));
+    T.qnext = (int32_t *)take(256 * 8);
+    T.nitems = (int32_t *)take(256);
+    PIC_HIP(c, hipMemsetAsync(T.cnt, 0, 4 * nb, c.st));
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, c.device) == hipSuccess && prop.multiProcessorCount > 0)
+        c.ncu = (prop.multiProcessorCount + 7) / 8 * 8;
+    const bool flat = tiles64_flat(c.P);
+    PIC_HIP(c, hipFuncSetAttribute(flat ? (const void *)k_step64<Geom2D> : (const void *)k_step64<Geom3D>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   flat ? step_lds<Geom2D>() : step_lds<Geom3D>()));
+    return PIC_OK;
+}
+
+template <class G>
+static void launch_step(Ctx &c, const StepCtx &S, Species64 b, Species64 p, FieldsT<double> f, int grid) {
+    constexpr int lds = step_lds<G>();
+    static_assert(2 * lds + 512 <= 160 * 1024, "two workgroups per CU");
+    hipLaunchKernelGGL(k_step64<G>, dim3(grid), dim3(ST64), lds, c.st, c.P, S, b, p, c.tiles, f, c.J64[0],
+                       c.J64[1], c.J64[2], c.dflags);
+}
+
+void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f) {
+    const Species64 b{c.b64.x, std::max<int64_t>(c.cap_b, 1), c.nb_slots},
+        p{c.p64.x, std::max<int64_t>(c.cap_p, 1), c.np_slots};
+    if (b.n + p.n <= 0) return;
+    const int grid = 2 * c.ncu;
+    tiles64_build(c, b, p, grid);
+    if (tiles64_flat(c.P))
+        launch_step<Geom2D>(c, S, b, p, f, grid);
+    else
+        launch_step<Geom3D>(c, S, b, p, f, grid);
+}
+
+}  // namespace pic

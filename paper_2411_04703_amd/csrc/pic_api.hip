@@ -247,6 +247,7 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         off[11] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1));   // beam
         off[12] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));   // plasma
         off[13] = pl.record ? 0 : take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));  // plasma (compaction)
+        off[27] = take(tiles64_bytes(P, pl.cap_b + pl.cap_p));                          // tile lists
     } else {
         pl.cap_p = P.has_plasma ? fill : 0;
         for (int k = 0; k < 6; ++k) off[k] = take(4 * P.nc);  // E B float
@@ -421,8 +422,7 @@ static pic_status step64(Ctx &c) {
     launch_bhalf<double>(P, S.k0r, f, 0.5 * P.dt, nullptr, c.st);
     timing_end(c, 1, t0);
     hipEvent_t t1 = timing_begin(c);
-    launch_step64(P, S, c.b64, c.nb_slots, f, c.J64, c.dflags, c.st);
-    launch_step64(P, S, c.p64, c.np_slots, f, c.J64, c.dflags, c.st);
+    step64_particles(c, S, f);
     timing_end(c, 0, t1);
     hipEvent_t t2 = timing_begin(c);
     if (P.ions) launch_ion64(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jion64, c.st);
@@ -591,6 +591,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->p64 = carve64(A + off[12], c->cap_p);
         if (!pl.record) c->p64alt = carve64(A + off[13], c->cap_p);
         if (e == hipSuccess) e = hipMemsetAsync(c->b64.alive, 0, 4 * std::max<int64_t>(c->cap_b, 1), c->st);
+        if (e == hipSuccess && tiles64_carve(*c, A + off[27], c->cap_b + c->cap_p) != PIC_OK) e = hipErrorUnknown;
     } else {
         for (int k = 0; k < 3; ++k) {
             c->E32[k] = (float *)(A + off[k]);

@@ -31,6 +31,16 @@ template <typename T> struct FieldsT {
 
 enum { DFLAG_FIXED_OVERFLOW = 1, DFLAG_NONFINITE = 2, DFLAG_BIN_LOST = 4 };
 
+// list entries number the particles through: slot q of the beam is q, of the plasma nb + q
+struct TileList {
+    int ntx, nty, ntz, nbins, chunk;
+    uint32_t *cnt;          // per bin, zero between uses
+    uint32_t *off;          // per bin, first list entry
+    uint32_t *key, *rank;   // per particle (numbered through): its bin (NO_BIN: not listed), place in it
+    uint32_t *list;         // particles bin by bin
+    int4 *items;            // (bin, first entry, end entry, 0): at most `chunk` particles of one bin
+    int32_t *nitems, *qnext;
+};
 struct Ctx {
     Params P;
     int precision = 0, record = 0, device = 0, check_every = 64;
@@ -71,6 +81,8 @@ struct Ctx {
 
     // particles
     Part64 b64{}, p64{}, p64alt{};
+    TileList tiles{};  // FP64 mode: particle lists of the cell tiles, rebuilt at every use
+    int ncu = 256;     // compute units of the device
     Part32 b32[2]{}, p32[2]{};
     int cur32 = 0;  // which of the double buffers is current
     int64_t ovf_cap_b = 0, ovf_cap_p = 0;
@@ -121,9 +133,12 @@ void launch_beam_init64(const Params &P, const double *normals, int64_t n, const
                         double es, Part64 p, double *partials, int nblk, hipStream_t st);
 void launch_inject64(const Params &P, int64_t l0, int64_t nsheets, double t, Part64 p, int64_t slot0,
                      hipStream_t st);
-void launch_step64(const Params &P, const StepCtx &S, Part64 p, int64_t n, FieldsT<double> f, double *J[3],
-                   int32_t *flags, hipStream_t st);
 int64_t compact64(Ctx &c, Part64 src, Part64 dst, int64_t n);  // returns survivors (synchronising)
+
+// FP64 particles on cell tiles (k_tiles64.hip)
+uint64_t tiles64_bytes(const Params &P, int64_t slots);  // arena bytes of the particle lists
+pic_status tiles64_carve(Ctx &c, char *base, int64_t slots);
+void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f);  // gather, push, move, deposit of both species
 
 // FP32 split particles (k_split32.hip)
 void split_setup(Ctx &c);

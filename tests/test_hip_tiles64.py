@@ -1,0 +1,52 @@
+"""Cell tiles of the FP64 particle kernels where they can go wrong: grids smaller than a tile or a
+remainder past one, crowded tiles of several work items, the block sizes of the list kernel, and a
+beam scattered over more tiles than its table of bins holds.  The oracle is the reference, at the
+FP64 path's bar of 1e-12 per step (round-off of sums in another order)."""
+import numpy as np
+import pytest
+
+import picinputs as pin
+from test_hip_fp64 import _compare, _pair
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("oracle_built")]
+
+
+@pytest.mark.parametrize("nx,ny,nz,n_beam,sigma", [
+    (5, 3, 24, 300, (1, 1, 2)),       # smaller than a tile: its boxes wrap around more than once
+    (8, 8, 20, 1, (1, 1, 2)),         # one tile across, one particle
+    (9, 17, 33, 2000, (1, 2, 3)),     # one cell past the tiles along every axis
+    (16, 8, 32, 6000, (.3, .3, .5)),  # a tile of thousands of particles: many items, one flush each
+    (13, 1, 40, 500, (2, 1, 4)),      # two-dimensional tiles, ragged
+], ids=lambda v: str(v).replace(" ", ""))
+def test_tile_edges_match_oracle(nx, ny, nz, n_beam, sigma):
+    w = pin.scaled(pin.workload(1), nx=nx, ny=ny, nz=nz, n_beam=n_beam, sigma=sigma)
+    w["beam"]["charge_C"] = 3e-10
+    ref, gpu = _pair(w)
+    for n in range(1, 5):
+        ref.step(1)
+        gpu.step(1)
+        _compare(ref, gpu, 1e-12 * n, f"step {n}")
+
+
+def test_many_particles_a_thread_match_few():
+    """A run of more than 2^21 particles (eight a thread in the list kernel, more tiles to a block than
+    its table of bins holds) against the same beam in two halves, each below: without a plasma and
+    with fields too weak to move anyone measurably, the currents of the halves add up to the whole's."""
+    from paper_2411_04703_amd.sim import Sim
+    w = pin.scaled(pin.workload(1), nx=192, ny=192, nz=512, n_beam=(1 << 21) + 77, sigma=(60, 60, 90))
+    w["plasma"]["n0_lab_cm3"] = 0.0
+    w["beam"]["charge_C"] = 1e-18
+    w["frame"]["window_beta"] = 0.9
+    n = w["beam"]["n_macro"]
+    nrm = pin.beam_normals(n, 3)
+    cut = n // 2
+
+    def fields(cols):
+        v = pin.scaled(w, n_beam=cols.shape[1])
+        v["beam"]["charge_C"] *= cols.shape[1] / n  # the same charge per particle
+        s = Sim(v, cols, precision=0)
+        s.step(1)
+        return np.stack([s.field(f) for f in ("Ex", "Ey", "Ez")])
+
+    whole, parts = fields(nrm), fields(nrm[:, :cut]) + fields(nrm[:, cut:])
+    assert np.linalg.norm(whole - parts) <= 1e-12 * np.linalg.norm(whole)
