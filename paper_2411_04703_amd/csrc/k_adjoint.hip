@@ -16,11 +16,40 @@
 #include <algorithm>
 #include <vector>
 
-#include "pic_internal.h"
+#include "tiles64.h"
 
 namespace pic {
 
 constexpr int AT = 256;
+constexpr int PT = 512;  // threads of the particle kernel
+
+// A sum with its rounding error carried along (Knuth's two-sum).  The gradients are small
+// differences of large sums -- the plasma electrons' current against the ions', a bunching wave's
+// adjoint over a uniform lattice -- whose plain FP64 sums left 1e-6 of the density gradient to the
+// order of their terms on the 64x64x256 workload.
+struct Sum2 {
+    double hi, lo;
+    __host__ __device__ void add(double v, double e = 0.0) {
+        const double s = hi + v, b = s - hi;
+        lo += ((hi - (s - b)) + (v - b)) + e;
+        hi = s;
+    }
+    __host__ __device__ double value() const { return hi + lo; }
+};
+
+// the workgroup's sum, in thread 0; red: one entry per wave
+template <int NT> __device__ inline Sum2 block_sum2(Sum2 v, Sum2 *red) {
+    for (int k = 32; k > 0; k >>= 1) {
+        const double h = __shfl_down(v.hi, k), l = __shfl_down(v.lo, k);
+        v.add(h, l);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < NT / 64; ++w) v.add(red[w].hi, red[w].lo);
+    __syncthreads();
+    return v;
+}
 
 struct Lam {  // views into the caller's adjoint vector
     double *x[3], *u[3];
@@ -126,109 +155,107 @@ __global__ void k_zero_plane(int64_t plane, int p, double *a0, double *a1, doubl
 }
 
 // <lam_Jz, J_ion>: sum over cells of lam_Jz times the ion profile of the cell's plane
-__global__ void __launch_bounds__(AT) k_ion_dot(Params P, int k0r, const double *lJz, const double *jion, double *out) {
-    __shared__ double s[AT];
-    double v = 0.0;
+__global__ void __launch_bounds__(AT) k_ion_dot(Params P, int k0r, const double *lJz, const double *jion, Sum2 *out) {
+    __shared__ Sum2 red[AT / 64];
+    Sum2 v{0.0, 0.0};
     for (int64_t o = (int64_t)blockIdx.x * AT + threadIdx.x; o < P.nc; o += (int64_t)gridDim.x * AT) {
         int p = (int)(o / P.plane);
         int l = p - k0r;
         if (l < 0) l += P.nz;
-        if (l != P.nz - 1) v += lJz[o] * jion[l];
+        if (l != P.nz - 1) v.add(lJz[o] * jion[l]);
     }
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int h = AT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) s[threadIdx.x] += s[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[blockIdx.x] = s[0];
+    v = block_sum2<AT>(v, red);
+    if (threadIdx.x == 0) out[blockIdx.x] = v;
 }
 
 // ---------------------------------------------------------------- particle reverse
-__device__ inline void weights_d(double x, double off, double w[3], double dw[3], int64_t &lo) {
-    double n = floor(x - off + 0.5);
-    lo = (int64_t)n - 1;
-    for (int a = 0; a < 3; ++a) {
-        double d = x - off - (double)(lo + a);
-        w[a] = spline2<double>(d);
-        dw[a] = dspline2<double>(d);
-    }
-}
-
-// value of one component and the scatter of lam * shape into the adjoint field; returns d(lam*value)/dX
-__device__ inline void gather_adj(const Params &P, const StepCtx &S, const double *F, double *lF, const double X[3],
-                                  int sx, int sy, int sz, double lam, double gX[3]) {
-    double w[3][3], dw[3][3];
-    int64_t lo[3];
-    weights_d(X[0], sx ? 0.5 : 0.0, w[0], dw[0], lo[0]);
-    weights_d(X[1], sy ? 0.5 : 0.0, w[1], dw[1], lo[1]);
-    weights_d(X[2], sz ? 0.5 : 0.0, w[2], dw[2], lo[2]);
+// The transpose of one component's gather: lam times its weights into the adjoint field's box L, and
+// lam times its derivatives along x, y, z from the field's box F added to gX.
+template <class G, int K>
+__device__ inline void gather_adj(const double *F, double *L, const double wi[3][3], const double wh[3][3],
+                                  const double di[3][3], const double dh[3][3], const int bi[3], const int bh[3],
+                                  double lam, double gX[3]) {
+    if (!__any(lam != 0.0)) return;
+    constexpr bool hx = G::half(K, 0), hy = G::half(K, 1), hz = G::half(K, 2);
+    constexpr int SY = G::FX, SZ = G::FX * G::FY;
+    const int o = K * G::NB + (hx ? bh[0] : bi[0]) + SY * (hy ? bh[1] : bi[1]) + SZ * (hz ? bh[2] : bi[2]);
+    const double *f = F + o;
+    double *l = L + o;
+    const double *wx = hx ? wh[0] : wi[0], *wy = hy ? wh[1] : wi[1], *wz = hz ? wh[2] : wi[2];
+    const double *dx = hx ? dh[0] : di[0], *dy = hy ? dh[1] : di[1], *dz = hz ? dh[2] : di[2];
+    double gx = 0.0, gy = 0.0, gz = 0.0;
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
-        int p = ring_plane((int)(lo[2] + c - S.k0), S.k0r, P.nz);
-        for (int b = 0; b < 3; ++b)
-            for (int a = 0; a < 3; ++a) {
-                int64_t o = cell_index(P, (int)(lo[0] + a), (int)(lo[1] + b), p);
-                if (lam != 0.0) atomicAdd(&lF[o], lam * w[0][a] * w[1][b] * w[2][c]);
-                double f = F[o] * lam;
-                gX[0] += f * dw[0][a] * w[1][b] * w[2][c];
-                gX[1] += f * w[0][a] * dw[1][b] * w[2][c];
-                gX[2] += f * w[0][a] * w[1][b] * dw[2][c];
-            }
+        const double lc = lam * wz[c];
+        double p = 0.0, px = 0.0, py = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const int r = SY * b + SZ * c;
+            const double r0 = f[r], r1 = f[r + 1], r2 = f[r + 2], lb = lc * wy[b];
+            atomicAdd(&l[r], lb * wx[0]);
+            atomicAdd(&l[r + 1], lb * wx[1]);
+            atomicAdd(&l[r + 2], lb * wx[2]);
+            const double q = fma(wx[2], r2, fma(wx[1], r1, wx[0] * r0));
+            p = fma(wy[b], q, p);
+            py = fma(dy[b], q, py);
+            px = fma(wy[b], fma(dx[2], r2, fma(dx[1], r1, dx[0] * r0)), px);
+        }
+        gz = fma(dz[c], p, gz);
+        gy = fma(wz[c], py, gy);
+        gx = fma(wz[c], px, gx);
     }
+    gX[0] = fma(lam, gx, gX[0]);
+    gX[1] = fma(lam, gy, gX[1]);
+    gX[2] = fma(lam, gz, gX[2]);
+    asm volatile("" : "+v"(gX[0]), "+v"(gX[1]), "+v"(gX[2]));  // summed here, not after the other components' reads
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// adjoint of the tight-window Esirkepov deposit: returns <lamJ, J_p>
-__device__ inline double deposit_adj(const Params &P, const StepCtx &S, double *const lJ[3], const double X0[3],
-                                     const double X1[3], double w, double gX0[3], double gX1[3]) {
-    double S0[3][4], DS[3][4], d0[3][4], d1[3][4];
-    int64_t base[3];
-    for (int d = 0; d < 3; ++d) {
-        int64_t n0 = (int64_t)floor(X0[d] + 0.5), n1 = (int64_t)floor(X1[d] + 0.5);
-        base[d] = (n0 < n1 ? n0 : n1) - 1;
-        for (int m = 0; m < 4; ++m) {
-            double node = (double)(base[d] + m);
-            S0[d][m] = spline2<double>(X0[d] - node);
-            DS[d][m] = spline2<double>(X1[d] - node) - S0[d][m];
-            d0[d][m] = dspline2<double>(X0[d] - node);
-            d1[d][m] = dspline2<double>(X1[d] - node);
-        }
-    }
-    double f = w / P.dt;
-    double gS0[3][4] = {{0}}, gDS[3][4] = {{0}};
+// Adjoint of one component of the Esirkepov current, J_c(m, a, b) = f P_c[m] A_c[a][b]: returns
+// <lam_J, J> of the particle and adds the derivatives with respect to S0 and DS.  Nodes that no
+// lane of the wave reaches (the windows' last, without a crossing) are left out: their weights and
+// the weights' derivatives vanish, and what the last node along the axis adds to every P_c[m]'s
+// factor alike drops out, the DS and their derivatives summing to zero.
+template <class G, int C>
+__device__ inline double deposit_grad(const double *Ls, const int jb[3], const double S0[3][4], const double DS[3][4],
+                                      const bool cross[3], double f, double gS0[3][4], double gDS[3][4]) {
+    constexpr int CA = (C + 1) % 3, CB = (C + 2) % 3;
+    constexpr int ST[3] = {1, G::jx(C), G::jx(C) * G::jy(C)};
+    const double *o = Ls + G::jofs(C) + jb[0] + ST[1] * jb[1] + ST[2] * jb[2];
+    const bool m2 = __any(cross[C]), a3 = __any(cross[CA]), b3 = __any(cross[CB]);
     double val = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        int ca = (c + 1) % 3, cb = (c + 2) % 3;
-        for (int ma = 0; ma < 4; ++ma)
-            for (int mb = 0; mb < 4; ++mb) {
-                double lam[3], suf = 0.0;
-                for (int m = 2; m >= 0; --m) {
-                    int64_t id[3];
-                    id[c] = base[c] + m;
-                    id[ca] = base[ca] + ma;
-                    id[cb] = base[cb] + mb;
-                    int p = ring_plane((int)(id[2] - S.k0), S.k0r, P.nz);
-                    suf += lJ[c][cell_index(P, (int)id[0], (int)id[1], p)];
-                    lam[m] = f * suf;
-                }
-                double A = S0[ca][ma] * S0[cb][mb] + 0.5 * DS[ca][ma] * S0[cb][mb] + 0.5 * S0[ca][ma] * DS[cb][mb] +
-                           DS[ca][ma] * DS[cb][mb] * (1.0 / 3.0);
-                double gA = 0.0;
-                for (int m = 0; m < 3; ++m) {
-                    val += DS[c][m] * A * lam[m];
-                    gDS[c][m] += A * lam[m];
-                    gA += DS[c][m] * lam[m];
-                }
-                gS0[ca][ma] += gA * (S0[cb][mb] + 0.5 * DS[cb][mb]);
-                gDS[ca][ma] += gA * (0.5 * S0[cb][mb] + DS[cb][mb] * (1.0 / 3.0));
-                gS0[cb][mb] += gA * (S0[ca][ma] + 0.5 * DS[ca][ma]);
-                gDS[cb][mb] += gA * (0.5 * S0[ca][ma] + DS[ca][ma] * (1.0 / 3.0));
-            }
-    }
-    for (int d = 0; d < 3; ++d)
-        for (int m = 0; m < 4; ++m) {
-            gX0[d] += (gS0[d][m] - gDS[d][m]) * d0[d][m];
-            gX1[d] += gDS[d][m] * d1[d][m];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        if (a == 3 && !a3) break;
+        const double sa = S0[CA][a], da = DS[CA][a];
+        double ga = 0.0, gda = 0.0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b == 3 && !b3) break;
+            const double *e = o + ST[CA] * a + ST[CB] * b;
+            const double l2 = m2 ? f * e[2 * ST[C]] : 0.0;
+            const double l1 = fma(f, e[ST[C]], l2), l0 = fma(f, e[0], l1);
+            const double sb = S0[CB][b], db = DS[CB][b];
+            const double ub = fma(0.5, db, sb), vb = fma(1.0 / 3.0, db, 0.5 * sb);
+            const double A = fma(sa, ub, da * vb);
+            const double gA = fma(DS[C][2], l2, fma(DS[C][1], l1, DS[C][0] * l0));
+            val = fma(A, gA, val);
+            gDS[C][0] = fma(A, l0, gDS[C][0]);
+            gDS[C][1] = fma(A, l1, gDS[C][1]);
+            gDS[C][2] = fma(A, l2, gDS[C][2]);
+            ga = fma(gA, ub, ga);
+            gda = fma(gA, vb, gda);
+            gS0[CB][b] = fma(gA, fma(0.5, da, sa), gS0[CB][b]);
+            gDS[CB][b] = fma(gA, fma(1.0 / 3.0, da, 0.5 * sa), gDS[CB][b]);
         }
+        gS0[CA][a] += ga;
+        gDS[CA][a] += gda;
+        // each row is finished before the next one's reads
+        asm volatile("" : "+v"(val), "+v"(gDS[C][0]), "+v"(gDS[C][1]), "+v"(gDS[C][2]), "+v"(gS0[CB][0]),
+                     "+v"(gS0[CB][1]), "+v"(gS0[CB][2]), "+v"(gDS[CB][0]), "+v"(gDS[CB][1]), "+v"(gDS[CB][2]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     return val;
 }
 
@@ -315,113 +342,228 @@ __device__ inline void push_vay_adj(double dt, const double u[3], const double E
     for (int d = 0; d < 3; ++d) lu[d] += lv0[d] / g0 - u[d] * uv / (g0 * g0 * g0);
 }
 
-__global__ void __launch_bounds__(AT) k_adj_particles(Params P, StepCtx S, Part64 p, int64_t n, Lam L,
-                                                      FieldsT<double> fE, const double *Bnx, const double *Bny,
-                                                      const double *Bnz, double *nEx, double *nEy, double *nEz,
-                                                      double *lBx, double *lBy, double *lBz, double *lJx,
-                                                      double *lJy, double *lJz, int plasma, double *part) {
-    __shared__ double sh[2][AT];
-    double gK = 0.0, gn = 0.0;
-    int64_t q = (int64_t)blockIdx.x * AT + threadIdx.x;
-    if (q < n) {
-        if (!p.alive[q]) {
-            for (int d = 0; d < 3; ++d) {
-                L.x[d][q] = 0.0;
-                L.u[d][q] = 0.0;
-            }
-        } else {
-            double X[3] = {p.x[q], p.y[q], p.z[q]}, U[3] = {p.ux[q], p.uy[q], p.uz[q]};
-            const double *Bn[3] = {Bnx, Bny, Bnz};
-            double E[3], B[3], Ee[3], Be[3], dEe[3], dBe[3];
-            // forward recompute: gather (values only), push, move
-            const int stE[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}}, stB[3][3] = {{0, 1, 1}, {1, 0, 1}, {1, 1, 0}};
-            for (int c = 0; c < 3; ++c) {
-                E[c] = 0.0;
-                B[c] = 0.0;
-                double wv[3][3], dv[3][3];
-                int64_t lo[3];
-                for (int d = 0; d < 3; ++d) weights_d(X[d], stE[c][d] ? 0.5 : 0.0, wv[d], dv[d], lo[d]);
-                for (int cc = 0; cc < 3; ++cc) {
-                    int pl = ring_plane((int)(lo[2] + cc - S.k0), S.k0r, P.nz);
-                    for (int b = 0; b < 3; ++b)
-                        for (int a = 0; a < 3; ++a)
-                            E[c] += wv[0][a] * wv[1][b] * wv[2][cc] *
-                                    fE.E[c][cell_index(P, (int)(lo[0] + a), (int)(lo[1] + b), pl)];
+// adjoint of the particles that no list holds (dead slots): zero
+__global__ void __launch_bounds__(AT) k_adj_dead(int64_t n, const uint32_t *key, int64_t nb, double *lb, int64_t capb,
+                                                 double *lp, int64_t capp) {
+    const int64_t q = (int64_t)blockIdx.x * AT + threadIdx.x;
+    if (q >= n || key[q] != NO_BIN) return;
+    double *l = q < nb ? lb + q : lp + (q - nb);
+    const int64_t cap = q < nb ? capb : capp;
+    for (int d = 0; d < 6; ++d) l[d * cap] = 0.0;
+}
+
+// the nodes of an adjoint field's box to the grid, cleared
+template <class G> __device__ inline void flush_nodes(const Params &P, int k0r, const Item64 &I, double *L,
+                                                      double *const dst[6]) {
+    int e = threadIdx.x;
+    opaque64(e);
+    for (; e < G::NB; e += PT) {
+        const int y = e / G::FX, a = e - y * G::FX, c = y / G::FY, b = y - c * G::FY;
+        const int l = I.t0z - 1 + c;
+        const bool in = l >= 0 && l < P.nz;
+        const int64_t o = in ? cell_near(P, I.t0x - 1 + a, I.t0y - 1 + b, ring_plane(l, k0r, P.nz)) : 0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const double v = L[k * G::NB + e];
+            L[k * G::NB + e] = 0.0;
+            if (in && v != 0.0) atomicAdd(&dst[k][o], v);
+        }
+    }
+}
+
+// lam_J of the tile into LDS
+template <class G, int K> __device__ inline void stage_lj(const Params &P, int k0r, const Item64 &I, const double *src,
+                                                          double *L) {
+    constexpr int X = G::jx(K), Y = G::jy(K), N = G::jsize(K), R = (N + PT - 1) / PT;
+    double v[R];
+    int e0 = threadIdx.x;
+    opaque64(e0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = e0 + r * PT, y = e / X, a = e - y * X, c = y / Y, b = y - c * Y, l = I.t0z - 2 + c;
+        const bool in = e < N && l >= 0 && l < P.nz;
+        v[r] = in ? src[cell_near(P, I.t0x - 2 + a, I.t0y - 2 + b, ring_plane(l, k0r, P.nz))] : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (e0 + r * PT < N) L[G::jofs(K) + e0 + r * PT] = v[r];
+}
+
+// The particles' part of the reverse step, tile by tile through the lists of k_tiles64.hip: E^n, B^n
+// and lam_J staged in LDS (74 KB), the adjoint fields' contributions summed in LDS boxes (41 KB) and
+// added to the grid once per item.  One thread per particle over the grid, with 162 global FP64
+// atomics each, took 15.0 ms on the 64x64x256 workload (1 M beam, 2 M plasma particles); this takes
+// 0.90 ms.  Bound: VALU (about 3500 instructions a wave) on one workgroup a CU, which is what the
+// LDS boxes leave: 512 threads, two waves a SIMD.  The fields are gathered twice, before the push and
+// with the scatter: keeping the first pass's 18 derivatives costs more in spills than 162 LDS reads.
+template <class G>
+__global__ void __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_adj_particles(Params P, StepCtx S, Bounds64 W, Species64 sb, Species64 sp, TileList T, double *lamb, double *lamp,
+                FieldsT<double> f, double *nEx, double *nEy, double *nEz, double *lBx, double *lBy, double *lBz,
+                const double *lJx, const double *lJy, const double *lJz, Sum2 *part) {
+    extern __shared__ __align__(16) double sma[];
+    __shared__ int s_item;
+    __shared__ Sum2 red[PT / 64];
+    double *F = sma, *L = F + G::NF, *Ls = L + G::NF;  // fields, adjoint fields, lam_J
+    const uint32_t tid = threadIdx.x;
+    for (int e = tid; e < G::NF; e += PT) L[e] = 0.0;
+    Sum2 gK{0.0, 0.0}, gn{0.0, 0.0};
+    ItemQueue64 Q;
+    if (tid == 0) s_item = Q.first(T);
+    __syncthreads();
+    int cur = __builtin_amdgcn_readfirstlane(s_item);
+    while (cur >= 0) {
+        const Item64 I = item64(T, cur, G::TX, G::TY, G::TZ);
+        {
+            Stage64<G, PT> st;
+            st.load(P, S.k0r, I, f);
+            stage_lj<G, 0>(P, S.k0r, I, lJx, Ls);
+            stage_lj<G, 1>(P, S.k0r, I, lJy, Ls);
+            stage_lj<G, 2>(P, S.k0r, I, lJz, Ls);
+            st.store(F);
+        }
+        __syncthreads();
+        if (tid == 0) Q.claim(T);
+        for (uint32_t e = I.begin + tid; e < I.end; e += PT) {
+            const Raw64 r = load_raw64(sb, sp, T.list[e]);
+            int c0[3], bi[3];
+            double wi[3][3], fl[3], E[3], B[3];
+            for (int d = 0; d < 3; ++d) fl[d] = floor(r.X[d]);
+            cell_in_tile64(P, W, I, fl, c0);
+            {
+                double wh[3][3];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    bi[d] = c0[d] + near_int(r.X[d], fl[d], wi[d]);
+                    weights3<double>(r.X[d] - 0.5 - fl[d], wh[d]);
                 }
-                for (int d = 0; d < 3; ++d) weights_d(X[d], stB[c][d] ? 0.5 : 0.0, wv[d], dv[d], lo[d]);
-                for (int cc = 0; cc < 3; ++cc) {
-                    int pl = ring_plane((int)(lo[2] + cc - S.k0), S.k0r, P.nz);
-                    for (int b = 0; b < 3; ++b)
-                        for (int a = 0; a < 3; ++a)
-                            B[c] += wv[0][a] * wv[1][b] * wv[2][cc] *
-                                    Bn[c][cell_index(P, (int)(lo[0] + a), (int)(lo[1] + b), pl)];
-                }
+                E[0] = gather_lds<G, 0>(F, wi, wh, bi, c0);
+                E[1] = gather_lds<G, 1>(F, wi, wh, bi, c0);
+                E[2] = gather_lds<G, 2>(F, wi, wh, bi, c0);
+                B[0] = gather_lds<G, 3>(F, wi, wh, bi, c0);
+                B[1] = gather_lds<G, 4>(F, wi, wh, bi, c0);
+                B[2] = gather_lds<G, 5>(F, wi, wh, bi, c0);
             }
-            ext_field64(P, X[2], S.t, Ee, Be, dEe, dBe);
+            double Ee[3], Be[3], dEe[3], dBe[3];
+            ext_field64(P, r.X[2], S.t, Ee, Be, dEe, dBe);
             for (int d = 0; d < 3; ++d) {
                 E[d] += Ee[d];
                 B[d] += Be[d];
             }
-            double Un[3];
-            push<double>(P.pusher, -0.5 * P.dt, U, E, B, Un);
-            double g = sqrt(1.0 + dot3(Un, Un));
-            double X1[3];
-            for (int d = 0; d < 3; ++d) X1[d] = X[d] + P.dt * Un[d] / g;
+            double Un[3], X1[3];
+            push<double>(P.pusher, -0.5 * P.dt, r.U, E, B, Un);
+            const double g = sqrt(1.0 + dot3(Un, Un));
+            for (int d = 0; d < 3; ++d) X1[d] = r.X[d] + P.dt * Un[d] / g;
+            const bool beam = r.id < (uint32_t)sb.n;
+            const int64_t cap = beam ? sb.cap : sp.cap;
+            double *const lq = beam ? lamb + r.id : lamp + (r.id - (uint32_t)sb.n);
             if (!(isfinite(X1[0]) && isfinite(X1[1]) && isfinite(X1[2]))) {
                 // the forward step dropped this particle without a deposit
+                for (int d = 0; d < 6; ++d) lq[d * cap] = 0.0;
+                continue;
+            }
+            const bool alive1 = !(X1[2] < W.lo || X1[2] >= W.hi);
+            double gX[3] = {0.0, 0.0, 0.0}, gX1[3], lun[3];
+            for (int d = 0; d < 3; ++d) {
+                const double lx = lq[d * cap], lu1 = lq[(3 + d) * cap];  // loaded by all, then selected
+                gX1[d] = alive1 ? lx : 0.0;
+                lun[d] = alive1 ? lu1 : 0.0;
+            }
+            {
+                double S0[3][4], DS[3][4], gS0[3][4], gDS[3][4];
+                int jb[3];
+                bool cross[3], h0[3], h1[3];
+                double d1[3];
+#pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    L.x[d][q] = 0.0;
-                    L.u[d][q] = 0.0;
+                    const int n0 = bi[d] - c0[d];
+                    double w1[3];
+                    const int n1 = near_int(X1[d], fl[d], w1), lo = n0 < n1 ? n0 : n1;
+                    d1[d] = X1[d] - fl[d] - (double)n1;
+                    h0[d] = n0 > lo;
+                    h1[d] = n1 > lo;
+                    cross[d] = n0 != n1;
+                    jb[d] = c0[d] + lo + 1;  // box node of offset lo - 1, origin -2
+                    window4(wi[d], h0[d], S0[d]);
+                    window4(w1, h1[d], DS[d]);
+                    for (int m = 0; m < 4; ++m) {
+                        DS[d][m] -= S0[d][m];
+                        gS0[d][m] = 0.0;
+                        gDS[d][m] = 0.0;
+                    }
                 }
-            } else {
-                int alive1 = !(X1[2] < (double)(S.k0n + 3) || X1[2] >= (double)(S.k0n + P.nz - 4));
-                double gX1[3], lun[3];
+                const double fq = r.w / P.dt;
+                double val = deposit_grad<G, 0>(Ls, jb, S0, DS, cross, fq, gS0, gDS);
+                val += deposit_grad<G, 1>(Ls, jb, S0, DS, cross, fq, gS0, gDS);
+                val += deposit_grad<G, 2>(Ls, jb, S0, DS, cross, fq, gS0, gDS);
+                gn.add(beam ? 0.0 : val);
+#pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    gX1[d] = alive1 ? L.x[d][q] : 0.0;
-                    lun[d] = alive1 ? L.u[d][q] : 0.0;
-                }
-                double gX[3] = {0, 0, 0};
-                double *lJ[3] = {lJx, lJy, lJz};
-                double val = deposit_adj(P, S, lJ, X, X1, p.w[q], gX, gX1);
-                if (plasma) gn += val;
-                double ug = dot3(Un, gX1);
-                for (int d = 0; d < 3; ++d) {
-                    gX[d] += gX1[d];
-                    lun[d] += P.dt * (gX1[d] / g - Un[d] * ug / (g * g * g));
-                }
-                double lu[3], lEp[3], lBp[3];
-                if (P.pusher == 1)
-                    push_vay_adj(P.dt, U, E, B, lun, lu, lEp, lBp);
-                else
-                    push_boris_adj(P.dt, U, E, B, lun, lu, lEp, lBp);
-                gK += dot3(lEp, Ee) + dot3(lBp, Be);
-                gX[2] += dot3(lEp, dEe) + dot3(lBp, dBe);
-                double *nE[3] = {nEx, nEy, nEz}, *lB[3] = {lBx, lBy, lBz};
-                for (int c = 0; c < 3; ++c) {
-                    gather_adj(P, S, fE.E[c], nE[c], X, stE[c][0], stE[c][1], stE[c][2], lEp[c], gX);
-                    gather_adj(P, S, Bn[c], lB[c], X, stB[c][0], stB[c][1], stB[c][2], lBp[c], gX);
-                }
-                for (int d = 0; d < 3; ++d) {
-                    L.x[d][q] = gX[d];
-                    L.u[d][q] = lu[d];
+                    double dw[3], w4[4];
+                    dweights3(r.X[d] - fl[d] - (double)(bi[d] - c0[d]), dw);
+                    window4(dw, h0[d], w4);
+                    for (int m = 0; m < 4; ++m) gX[d] += (gS0[d][m] - gDS[d][m]) * w4[m];
+                    dweights3(d1[d], dw);
+                    window4(dw, h1[d], w4);
+                    for (int m = 0; m < 4; ++m) gX1[d] += gDS[d][m] * w4[m];
                 }
             }
+            const double ug = dot3(Un, gX1);
+            for (int d = 0; d < 3; ++d) {
+                gX[d] += gX1[d];
+                lun[d] += P.dt * (gX1[d] / g - Un[d] * ug / (g * g * g));
+            }
+            double lu[3], lEp[3], lBp[3];
+            if (P.pusher == 1)
+                push_vay_adj(P.dt, r.U, E, B, lun, lu, lEp, lBp);
+            else
+                push_boris_adj(P.dt, r.U, E, B, lun, lu, lEp, lBp);
+            gK.add(dot3(lEp, Ee) + dot3(lBp, Be));
+            gX[2] += dot3(lEp, dEe) + dot3(lBp, dBe);
+            double wh[3][3], di[3][3], dh[3][3];  // the weights again: kept from the gather they would be spilled
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                double x = r.X[d];
+                asm volatile("" : "+v"(x));
+                const double oi = x - fl[d] - (double)(bi[d] - c0[d]), oh = x - 0.5 - fl[d];
+                weights3<double>(oi, wi[d]);
+                dweights3(oi, di[d]);
+                weights3<double>(oh, wh[d]);
+                dweights3(oh, dh[d]);
+            }
+            gather_adj<G, 0>(F, L, wi, wh, di, dh, bi, c0, lEp[0], gX);
+            gather_adj<G, 1>(F, L, wi, wh, di, dh, bi, c0, lEp[1], gX);
+            gather_adj<G, 2>(F, L, wi, wh, di, dh, bi, c0, lEp[2], gX);
+            gather_adj<G, 3>(F, L, wi, wh, di, dh, bi, c0, lBp[0], gX);
+            gather_adj<G, 4>(F, L, wi, wh, di, dh, bi, c0, lBp[1], gX);
+            gather_adj<G, 5>(F, L, wi, wh, di, dh, bi, c0, lBp[2], gX);
+            for (int d = 0; d < 3; ++d) {
+                lq[d * cap] = gX[d];
+                lq[(3 + d) * cap] = lu[d];
+            }
         }
-    }
-    sh[0][threadIdx.x] = gK;
-    sh[1][threadIdx.x] = gn;
-    __syncthreads();
-    for (int h = AT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            sh[0][threadIdx.x] += sh[0][threadIdx.x + h];
-            sh[1][threadIdx.x] += sh[1][threadIdx.x + h];
-        }
+        if (tid == 0) s_item = Q.resolve(T);
         __syncthreads();
+        cur = __builtin_amdgcn_readfirstlane(s_item);
+        double *const dst[6] = {nEx, nEy, nEz, lBx, lBy, lBz};
+        flush_nodes<G>(P, S.k0r, I, L, dst);
     }
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = sh[0][0];
-        part[2 * blockIdx.x + 1] = sh[1][0];
+    gK = block_sum2<PT>(gK, red);
+    gn = block_sum2<PT>(gn, red);
+    if (tid == 0) {
+        part[2 * blockIdx.x] = gK;
+        part[2 * blockIdx.x + 1] = gn;
     }
+}
+
+template <class G> static constexpr int adj_lds() { return 8 * (2 * G::NF + G::NJ); }
+
+pic_status adjoint_setup(Ctx &c) {
+    const bool flat = tiles64_flat(c.P);
+    PIC_HIP(c, hipFuncSetAttribute(flat ? (const void *)k_adj_particles<Geom2D> : (const void *)k_adj_particles<Geom3D>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   flat ? adj_lds<Geom2D>() : adj_lds<Geom3D>()));
+    return PIC_OK;
 }
 
 __global__ void k_zero_slots(Lam L, int64_t a, int64_t b) {
@@ -545,30 +687,41 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
     hipLaunchKernelGGL(k_adj_bhalf, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2], nE[0],
                        nE[1], nE[2]);
     // ion current: n0 dL/dn0 += <lam_Jz, J_ion>
-    double gn = 0.0, gK = 0.0;
+    Sum2 gn{0.0, 0.0}, gK{0.0, 0.0};
+    Sum2 *const part = (Sum2 *)c.red;
     if (P.ions && c.sh_hi > c.sh_lo) {
         launch_ion64(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jion64, c.st);
-        hipLaunchKernelGGL(k_ion_dot, dim3(256), dim3(AT), 0, c.st, P, S.k0r, c.J64[2], c.jion64, c.red);
-        std::vector<double> h(256);
-        PIC_HIP(c, hipMemcpyAsync(h.data(), c.red, 8 * 256, hipMemcpyDeviceToHost, c.st));
+        hipLaunchKernelGGL(k_ion_dot, dim3(256), dim3(AT), 0, c.st, P, S.k0r, c.J64[2], c.jion64, part);
+        std::vector<Sum2> h(256);
+        PIC_HIP(c, hipMemcpyAsync(h.data(), part, sizeof(Sum2) * 256, hipMemcpyDeviceToHost, c.st));
         PIC_HIP(c, hipMemsetAsync(c.jion64, 0, 8 * P.nz, c.st));
         PIC_HIP(c, hipStreamSynchronize(c.st));
-        for (int b = 0; b < 256; ++b) gn += h[b];
+        for (const Sum2 &v : h) gn.add(v.hi, v.lo);
     }
     // particles
-    for (int sp = 0; sp < 2; ++sp) {
-        int64_t n = sp ? c.np_slots : c.nb_slots;
-        if (n <= 0) continue;
-        int nblk = nblocks(n, AT);
-        hipLaunchKernelGGL(k_adj_particles, dim3(nblk), dim3(AT), 0, c.st, P, S, sp ? c.p64 : c.b64, n, sp ? Lp : Lb,
-                           fn, Bn[0], Bn[1], Bn[2], nE[0], nE[1], nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1],
-                           c.J64[2], sp, c.red);
-        std::vector<double> h(2 * (size_t)nblk);
-        PIC_HIP(c, hipMemcpyAsync(h.data(), c.red, 16 * (uint64_t)nblk, hipMemcpyDeviceToHost, c.st));
+    const Species64 b{c.b64.x, (int64_t)cb, c.nb_slots}, p{c.p64.x, (int64_t)cp, c.np_slots};
+    const int64_t n = b.n + p.n;
+    if (n > 0) {
+        const int grid = c.ncu;
+        const bool flat = tiles64_flat(P);
+        tiles64_build(c, b, p, grid);
+        hipLaunchKernelGGL(k_adj_dead, dim3(nblocks(n, AT)), dim3(AT), 0, c.st, n, c.tiles.key, b.n, Lb.x[0], b.cap,
+                           Lp.x[0], p.cap);
+        const Bounds64 W(P, S.k0, S.k0n);
+        auto launch = [&](auto kernel, int lds) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(PT), lds, c.st, P, S, W, b, p, c.tiles, Lb.x[0], Lp.x[0], fn,
+                               nE[0], nE[1], nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1], c.J64[2], part);
+        };
+        if (flat)
+            launch(k_adj_particles<Geom2D>, adj_lds<Geom2D>());
+        else
+            launch(k_adj_particles<Geom3D>, adj_lds<Geom3D>());
+        std::vector<Sum2> h(2 * (size_t)grid);
+        PIC_HIP(c, hipMemcpyAsync(h.data(), part, sizeof(Sum2) * h.size(), hipMemcpyDeviceToHost, c.st));
         PIC_HIP(c, hipStreamSynchronize(c.st));
-        for (int b = 0; b < nblk; ++b) {
-            gK += h[2 * b];
-            gn += h[2 * b + 1];
+        for (int k = 0; k < grid; ++k) {
+            gK.add(h[2 * k].hi, h[2 * k].lo);
+            gn.add(h[2 * k + 1].hi, h[2 * k + 1].lo);
         }
     }
     // first half step, then the new lam_E
@@ -579,8 +732,8 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
         PIC_HIP(c, hipMemsetAsync(c.J64[k], 0, 8 * P.nc, c.st));
     }
     PIC_HIP(c, hipStreamSynchronize(c.st));
-    grad[0] += gK;
-    grad[1] += gn;
+    grad[0] += gK.value();
+    grad[1] += gn.value();
     return PIC_OK;
 }
 

@@ -42,18 +42,6 @@ uint64_t tiles64_bytes(const Params &P, int64_t slots) {
     return 2 * al(4 * nb) + 3 * al(4 * n) + al(16 * (nb + n / CHUNK_MIN + 16)) + 256 * 9;
 }
 
-// cell (i, j in the grid, l logical) of an absolute position; false outside the window or not finite
-__device__ inline bool locate64(const Params &P, int64_t k0, double x, double y, double z, int &i, int &j, int &l) {
-    const double zl = floor(z) - (double)k0;
-    if (!(zl >= 0.0 && zl < (double)P.nz) || !isfinite(x) || !isfinite(y)) return false;
-    l = (int)zl;
-    i = (int)floor(x);
-    j = (int)floor(y);
-    if (i < 0 || i >= P.nx) i = wrapi(i, P.nx);
-    if (j < 0 || j >= P.ny) j = wrapi(j, P.ny);
-    return true;
-}
-
 // Bin of every live particle and its place there.  A block counts its particles in an LDS hash
 // table of bins and adds each bin's count to the global one once: a beam's particles come in no
 // order and crowd a few hundred bins, whose counters took 0.60 ms for 4.2 M particles when every
@@ -61,7 +49,7 @@ __device__ inline bool locate64(const Params &P, int64_t k0, double x, double y,
 // globally.  A live particle that is not finite or outside the window is taken out.
 constexpr int CT = 1024, HB = 13;
 template <int PPT>
-__global__ void __launch_bounds__(CT) k_tile_count(Params P, int64_t k0, Species64 b, Species64 p, int lgx, int lgy,
+__global__ void __launch_bounds__(CT) k_tile_count(Params P, Bounds64 W, Species64 b, Species64 p, int lgx, int lgy,
                                                    int lgz, TileList T, int32_t *flags) {
     __shared__ uint32_t hkey[1 << HB], hcnt[1 << HB];
     for (int e = threadIdx.x; e < 1 << HB; e += CT) {
@@ -82,7 +70,7 @@ __global__ void __launch_bounds__(CT) k_tile_count(Params P, int64_t k0, Species
         if (q < b.n + p.n && S.alive()[s]) {
             const double x = S.x[s], y = S.x[S.cap + s], z = S.x[2 * S.cap + s];
             int i, j, l;
-            if (locate64(P, k0, x, y, z, i, j, l)) {
+            if (locate64(P, W, x, y, z, i, j, l)) {
                 key[v] = (uint32_t)((i >> lgx) + T.ntx * ((j >> lgy) + T.nty * (l >> lgz)));
             } else {
                 S.alive()[s] = 0;
@@ -192,85 +180,19 @@ void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid) {
     const int64_t n = b.n + p.n;
     const bool flat = tiles64_flat(c.P);
     c.tiles.chunk = chunk_of(n);
+    const Bounds64 W(c.P, c.k0, c.k0);
     const int lgx = 3, lgy = flat ? 0 : 3, lgz = flat ? 4 : 2;
     if (n >= (int64_t)1 << 21)  // many particles a thread where there are blocks enough all the same
-        hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(n, 8 * CT)), dim3(CT), 0, c.st, c.P, c.k0, b, p, lgx, lgy,
+        hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(n, 8 * CT)), dim3(CT), 0, c.st, c.P, W, b, p, lgx, lgy,
                            lgz, c.tiles, c.dflags);
     else if (n > 0)
-        hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(n, CT)), dim3(CT), 0, c.st, c.P, c.k0, b, p, lgx, lgy, lgz,
+        hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(n, CT)), dim3(CT), 0, c.st, c.P, W, b, p, lgx, lgy, lgz,
                            c.tiles, c.dflags);
     hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, c.st, c.tiles, grid / 8);
     if (n > 0) hipLaunchKernelGGL(k_tile_scatter, dim3(nblocks(n, LT)), dim3(LT), 0, c.st, n, c.tiles);
 }
 
 // ---------------------------------------------------------------- the step
-// Weights of the three integer nodes around a coordinate: n the nearest node's distance above the
-// cell's lower node (0 or 1), w the weights of n - 1, n, n + 1.
-__device__ inline int near_int(double x, double fl, double w[3]) {
-    const double n = floor(x + 0.5);
-    weights3<double>(x - n, w);
-    return (int)(n - fl);
-}
-
-template <class G, int K> __device__ inline double gather_lds(const double *F, const double wi[3][3],
-                                                              const double wh[3][3], const int bi[3], const int bh[3]) {
-    constexpr bool hx = G::half(K, 0), hy = G::half(K, 1), hz = G::half(K, 2);
-    const double *wx = hx ? wh[0] : wi[0], *wy = hy ? wh[1] : wi[1], *wz = hz ? wh[2] : wi[2];
-    constexpr int SY = G::FX, SZ = G::FX * G::FY;
-    const double *f = F + K * G::NB + (hx ? bh[0] : bi[0]) + SY * (hy ? bh[1] : bi[1]) + SZ * (hz ? bh[2] : bi[2]);
-    double v = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double py = 0.0;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double *r = f + SY * b + SZ * c;
-            py = fma(wy[b], fma(wx[2], r[2], fma(wx[1], r[1], wx[0] * r[0])), py);
-        }
-        v = fma(wz[c], py, v);
-    }
-    // the sum is taken here: left to itself the compiler sinks the arithmetic of all six components
-    // below their 162 reads and spills what they returned
-    asm volatile("" : "+v"(v));
-    __builtin_amdgcn_sched_barrier(0);
-    return v;
-}
-
-// Hides v's value from the optimiser, so that what is computed from it is not hoisted out of the
-// work-item loop and kept live (or spilled) across it.
-__device__ inline void opaque64(int &v) { asm volatile("" : "+v"(v)); }
-
-// The six fields of the tile into LDS (nodes outside the window: 0, never gathered with a nonzero
-// weight).  A thread takes whole nodes: one address for six loads.  load() leaves all of a thread's
-// loads in flight together, store() writes what came.
-template <class G> struct Stage64 {
-    static constexpr int R = (G::NB + ST64 - 1) / ST64;
-    double v[R][6];
-    __device__ void load(const Params &P, int k0r, const Item64 &I, const FieldsT<double> &f) {
-        const double *src[6] = {f.E[0], f.E[1], f.E[2], f.B[0], f.B[1], f.B[2]};
-        int e0 = threadIdx.x;
-        opaque64(e0);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int e = e0 + r * ST64, y = e / G::FX, a = e - y * G::FX, c = y / G::FY, b = y - c * G::FY;
-            const int l = I.t0z - 1 + c;
-            const bool in = e < G::NB && l >= 0 && l < P.nz;
-            const int64_t o = in ? cell_near(P, I.t0x - 1 + a, I.t0y - 1 + b, ring_plane(l, k0r, P.nz)) : 0;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) v[r][k] = in ? src[k][o] : 0.0;
-        }
-    }
-    __device__ void store(double *F) const {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int e = threadIdx.x + r * ST64;
-            if (e < G::NB)
-#pragma unroll
-                for (int k = 0; k < 6; ++k) F[k * G::NB + e] = v[r][k];
-        }
-    }
-};
-
 // current box of component K to the grid, cleared
 template <class G, int K> __device__ inline void flush_lds(const Params &P, int k0r, const Item64 &I, double *Js,
                                                            double *J) {
@@ -323,36 +245,6 @@ template <class G, int C> __device__ inline void deposit_lds(double *Js, const i
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// a particle as loaded, and its number in the list
-struct Raw64 {
-    double X[3], U[3], w;
-    uint32_t id;
-};
-
-// where a particle's x is (the other arrays follow `cap` doubles apart), and its alive flag
-__device__ inline double *slot64(const Species64 &sb, const Species64 &sp, uint32_t id, int64_t &cap, int32_t *&alive) {
-    const bool beam = id < (uint32_t)sb.n;
-    const uint32_t s = beam ? id : id - (uint32_t)sb.n;
-    double *const x0 = beam ? sb.x : sp.x;
-    cap = beam ? sb.cap : sp.cap;
-    alive = (int32_t *)(x0 + 7 * cap) + s;
-    return x0 + s;
-}
-
-__device__ inline Raw64 load_raw64(const Species64 &sb, const Species64 &sp, uint32_t id) {
-    Raw64 r;
-    int64_t cap;
-    int32_t *alive;
-    const double *at = slot64(sb, sp, id, cap, alive);
-    r.id = id;
-    for (int d = 0; d < 3; ++d) {
-        r.X[d] = at[d * cap];
-        r.U[d] = at[(3 + d) * cap];
-    }
-    r.w = at[6 * cap];
-    return r;
-}
-
 // Per item: stage the tile's E and B (B^n, already advanced), then per particle gather, push, move
 // and deposit into the LDS current boxes, which are added to the grid at the end.  One thread per
 // particle over the grid (fields from global memory, every contribution a global FP64 atomic) took
@@ -367,7 +259,7 @@ __device__ inline Raw64 load_raw64(const Species64 &sb, const Species64 &sp, uin
 // (spills).
 template <class G>
 __global__ void __launch_bounds__(ST64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_step64(Params P, StepCtx S, Species64 sb, Species64 sp, TileList T, FieldsT<double> f, double *Jx, double *Jy,
+k_step64(Params P, StepCtx S, Bounds64 W, Species64 sb, Species64 sp, TileList T, FieldsT<double> f, double *Jx, double *Jy,
          double *Jz, int32_t *flags) {
     extern __shared__ __align__(16) double sm64[];
     __shared__ int s_item;
@@ -380,7 +272,7 @@ k_step64(Params P, StepCtx S, Species64 sb, Species64 sp, TileList T, FieldsT<do
     int cur = __builtin_amdgcn_readfirstlane(s_item);
     while (cur >= 0) {
         const Item64 I = item64(T, cur, G::TX, G::TY, G::TZ);
-        Stage64<G> st;
+        Stage64<G, ST64> st;
         st.load(P, S.k0r, I, f);
         Raw64 r = load_raw64(sb, sp, T.list[min(I.begin + tid, I.end - 1)]);
         st.store(F);
@@ -391,14 +283,11 @@ k_step64(Params P, StepCtx S, Species64 sb, Species64 sp, TileList T, FieldsT<do
             if (base + tid >= I.end) continue;
             double X1[3], Un[3], wi[3][3], fl[3];
             int c0[3], bi[3];
-            (void)locate64(P, S.k0, r.X[0], r.X[1], r.X[2], c0[0], c0[1], c0[2]);
-            c0[0] -= I.t0x;
-            c0[1] -= I.t0y;
-            c0[2] -= I.t0z;
+            for (int d = 0; d < 3; ++d) fl[d] = floor(r.X[d]);
+            cell_in_tile64(P, W, I, fl, c0);
             double wh[3][3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                fl[d] = floor(r.X[d]);
                 bi[d] = c0[d] + near_int(r.X[d], fl[d], wi[d]);
                 weights3<double>(r.X[d] - 0.5 - fl[d], wh[d]);
             }
@@ -437,25 +326,20 @@ k_step64(Params P, StepCtx S, Species64 sb, Species64 sp, TileList T, FieldsT<do
                 const bool h0 = n0 > lo, h1 = n1 > lo;
                 cross[d] = n0 != n1;
                 jb[d] = c0[d] + lo + 1;  // box node of offset lo - 1, origin -2
-                S0[d][0] = h0 ? 0.0 : wi[d][0];
-                S0[d][1] = h0 ? wi[d][0] : wi[d][1];
-                S0[d][2] = h0 ? wi[d][1] : wi[d][2];
-                S0[d][3] = h0 ? wi[d][2] : 0.0;
-                DS[d][0] = (h1 ? 0.0 : w1[0]) - S0[d][0];
-                DS[d][1] = (h1 ? w1[0] : w1[1]) - S0[d][1];
-                DS[d][2] = (h1 ? w1[1] : w1[2]) - S0[d][2];
-                DS[d][3] = (h1 ? w1[2] : 0.0) - S0[d][3];
+                window4(wi[d], h0, S0[d]);
+                window4(w1, h1, DS[d]);
+                for (int m = 0; m < 4; ++m) DS[d][m] -= S0[d][m];
             }
-            if (X1[0] < 0) X1[0] += P.nx;
-            if (X1[0] >= P.nx) X1[0] -= P.nx;
-            if (X1[1] < 0) X1[1] += P.ny;
-            if (X1[1] >= P.ny) X1[1] -= P.ny;
+            if (X1[0] < 0) X1[0] += W.nx;
+            if (X1[0] >= W.nx) X1[0] -= W.nx;
+            if (X1[1] < 0) X1[1] += W.ny;
+            if (X1[1] >= W.ny) X1[1] -= W.ny;
             for (int d = 0; d < 3; ++d) {
                 at[d * cap] = X1[d];
                 at[(3 + d) * cap] = Un[d];
             }
             // window after this step's shift: active band [k0n + 3, k0n + nz - 4)
-            if (X1[2] < (double)(S.k0n + 3) || X1[2] >= (double)(S.k0n + P.nz - 4)) *alive = 0;
+            if (X1[2] < W.lo || X1[2] >= W.hi) *alive = 0;
             const double fq = r.w / P.dt;  // -q w / dt
             deposit_lds<G, 0>(Js, jb, S0, DS, cross, fq);
             deposit_lds<G, 1>(Js, jb, S0, DS, cross, fq);
@@ -505,7 +389,7 @@ template <class G>
 static void launch_step(Ctx &c, const StepCtx &S, Species64 b, Species64 p, FieldsT<double> f, int grid) {
     constexpr int lds = step_lds<G>();
     static_assert(2 * lds + 512 <= 160 * 1024, "two workgroups per CU");
-    hipLaunchKernelGGL(k_step64<G>, dim3(grid), dim3(ST64), lds, c.st, c.P, S, b, p, c.tiles, f, c.J64[0],
+    hipLaunchKernelGGL(k_step64<G>, dim3(grid), dim3(ST64), lds, c.st, c.P, S, Bounds64(c.P, S.k0, S.k0n), b, p, c.tiles, f, c.J64[0],
                        c.J64[1], c.J64[2], c.dflags);
 }
 

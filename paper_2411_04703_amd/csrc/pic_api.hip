@@ -592,6 +592,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         if (!pl.record) c->p64alt = carve64(A + off[13], c->cap_p);
         if (e == hipSuccess) e = hipMemsetAsync(c->b64.alive, 0, 4 * std::max<int64_t>(c->cap_b, 1), c->st);
         if (e == hipSuccess && tiles64_carve(*c, A + off[27], c->cap_b + c->cap_p) != PIC_OK) e = hipErrorUnknown;
+        if (e == hipSuccess && pl.record && adjoint_setup(*c) != PIC_OK) e = hipErrorUnknown;
     } else {
         for (int k = 0; k < 3; ++k) {
             c->E32[k] = (float *)(A + off[k]);

@@ -177,6 +177,7 @@ void launch_neutraliser_current(Ctx &c, const StepCtx &S);  // adds its current 
 void launch_neutraliser_rho(Ctx &c, double *rho);           // adds its charge now into rho (ring order)
 
 // adjoint (k_adjoint.hip)
+pic_status adjoint_setup(Ctx &c);  // once per context in record mode
 pic_status adjoint_seed(Ctx &c, double kb, double *lam, double *loss);
 pic_status adjoint_step(Ctx &c, double *lam, double grad[2]);
 

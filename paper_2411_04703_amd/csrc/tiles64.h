@@ -110,6 +110,156 @@ __device__ inline int64_t cell_near(const Params &P, int i, int j, int p) {
     return (int64_t)i + (int64_t)P.nx * ((int64_t)j + (int64_t)P.ny * p);
 }
 
+// Window and grid bounds as doubles.  Kernel arguments, so that they stay in scalar registers:
+// converted in the kernel they are vector registers, kept (or spilled) across its loops.
+struct Bounds64 {
+    double k0, nx, ny, nz;  // window origin and extents
+    double lo, hi;          // active band after the step's shift: [k0n + 3, k0n + nz - 4)
+    __host__ Bounds64(const Params &P, int64_t k0_, int64_t k0n)
+        : k0((double)k0_), nx(P.nx), ny(P.ny), nz(P.nz), lo((double)(k0n + 3)), hi((double)(k0n + P.nz - 4)) {}
+};
+
+// cell (i, j in the grid, l logical) of an absolute position; false outside the window or not finite
+__device__ inline bool locate64(const Params &P, const Bounds64 &W, double x, double y, double z, int &i, int &j,
+                                int &l) {
+    const double zl = floor(z) - W.k0;
+    if (!(zl >= 0.0 && zl < W.nz) || !isfinite(x) || !isfinite(y)) return false;
+    l = (int)zl;
+    i = (int)floor(x);
+    j = (int)floor(y);
+    if (i < 0 || i >= P.nx) i = wrapi(i, P.nx);
+    if (j < 0 || j >= P.ny) j = wrapi(j, P.ny);
+    return true;
+}
+
+// The same for a listed particle, whose place the list kernel has checked: relative to its tile, and
+// without a branch (the coordinate wraps on the way out of a step, so it lies in the grid but for
+// positions a caller wrote).
+__device__ inline void cell_in_tile64(const Params &P, const Bounds64 &W, const Item64 &I, const double fl[3],
+                                      int c0[3]) {
+    int i = (int)fl[0], j = (int)fl[1];
+    if (__any((unsigned)i >= (unsigned)P.nx || (unsigned)j >= (unsigned)P.ny)) {
+        i = wrapi(i, P.nx);
+        j = wrapi(j, P.ny);
+    }
+    c0[0] = i - I.t0x;
+    c0[1] = j - I.t0y;
+    c0[2] = (int)(fl[2] - W.k0) - I.t0z;
+}
+
+// Weights of the three integer nodes around a coordinate: n the nearest node's distance above the
+// cell's lower node (0 or 1), w the weights of n - 1, n, n + 1.
+__device__ inline int near_int(double x, double fl, double w[3]) {
+    const double n = floor(x + 0.5);
+    weights3<double>(x - n, w);
+    return (int)(n - fl);
+}
+
+// derivatives of weights3 with respect to the offset d
+__device__ inline void dweights3(double d, double w[3]) {
+    w[0] = d - 0.5;
+    w[1] = -2.0 * d;
+    w[2] = d + 0.5;
+}
+
+// three weights in a four-node window, one node up where `up`
+__device__ inline void window4(const double w[3], bool up, double o[4]) {
+    o[0] = up ? 0.0 : w[0];
+    o[1] = up ? w[0] : w[1];
+    o[2] = up ? w[1] : w[2];
+    o[3] = up ? w[2] : 0.0;
+}
+
+// one component at a particle from its tile's box
+template <class G, int K> __device__ inline double gather_lds(const double *F, const double wi[3][3],
+                                                              const double wh[3][3], const int bi[3], const int bh[3]) {
+    constexpr bool hx = G::half(K, 0), hy = G::half(K, 1), hz = G::half(K, 2);
+    const double *wx = hx ? wh[0] : wi[0], *wy = hy ? wh[1] : wi[1], *wz = hz ? wh[2] : wi[2];
+    constexpr int SY = G::FX, SZ = G::FX * G::FY;
+    const double *f = F + K * G::NB + (hx ? bh[0] : bi[0]) + SY * (hy ? bh[1] : bi[1]) + SZ * (hz ? bh[2] : bi[2]);
+    double v = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double py = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const double *r = f + SY * b + SZ * c;
+            py = fma(wy[b], fma(wx[2], r[2], fma(wx[1], r[1], wx[0] * r[0])), py);
+        }
+        v = fma(wz[c], py, v);
+    }
+    // the sum is taken here: left to itself the compiler sinks the arithmetic of all six components
+    // below their 162 reads and spills what they returned
+    asm volatile("" : "+v"(v));
+    __builtin_amdgcn_sched_barrier(0);
+    return v;
+}
+
+// Hides v's value from the optimiser, so that what is computed from it is not hoisted out of the
+// work-item loop and kept live (or spilled) across it.
+__device__ inline void opaque64(int &v) { asm volatile("" : "+v"(v)); }
+
+// The six fields of the tile into LDS (nodes outside the window: 0, never gathered with a nonzero
+// weight).  A thread takes whole nodes: one address for six loads.  load() leaves all of a thread's
+// loads in flight together, store() writes what came.
+template <class G, int NT> struct Stage64 {
+    static constexpr int R = (G::NB + NT - 1) / NT;
+    double v[R][6];
+    __device__ void load(const Params &P, int k0r, const Item64 &I, const FieldsT<double> &f) {
+        const double *src[6] = {f.E[0], f.E[1], f.E[2], f.B[0], f.B[1], f.B[2]};
+        int e0 = threadIdx.x;
+        opaque64(e0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = e0 + r * NT, y = e / G::FX, a = e - y * G::FX, c = y / G::FY, b = y - c * G::FY;
+            const int l = I.t0z - 1 + c;
+            const bool in = e < G::NB && l >= 0 && l < P.nz;
+            const int64_t o = in ? cell_near(P, I.t0x - 1 + a, I.t0y - 1 + b, ring_plane(l, k0r, P.nz)) : 0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[r][k] = in ? src[k][o] : 0.0;
+        }
+    }
+    __device__ void store(double *F) const {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = threadIdx.x + r * NT;
+            if (e < G::NB)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) F[k * G::NB + e] = v[r][k];
+        }
+    }
+};
+
+// a particle as loaded, and its number in the list
+struct Raw64 {
+    double X[3], U[3], w;
+    uint32_t id;
+};
+
+// where a particle's x is (the other arrays follow `cap` doubles apart), and its alive flag
+__device__ inline double *slot64(const Species64 &sb, const Species64 &sp, uint32_t id, int64_t &cap, int32_t *&alive) {
+    const bool beam = id < (uint32_t)sb.n;
+    const uint32_t s = beam ? id : id - (uint32_t)sb.n;
+    double *const x0 = beam ? sb.x : sp.x;
+    cap = beam ? sb.cap : sp.cap;
+    alive = (int32_t *)(x0 + 7 * cap) + s;
+    return x0 + s;
+}
+
+__device__ inline Raw64 load_raw64(const Species64 &sb, const Species64 &sp, uint32_t id) {
+    Raw64 r;
+    int64_t cap;
+    int32_t *alive;
+    const double *at = slot64(sb, sp, id, cap, alive);
+    r.id = id;
+    for (int d = 0; d < 3; ++d) {
+        r.X[d] = at[d * cap];
+        r.U[d] = at[(3 + d) * cap];
+    }
+    r.w = at[6 * cap];
+    return r;
+}
+
 // host side (k_tiles64.hip)
 bool tiles64_flat(const Params &P);  // two-dimensional tiles?
 // lists of the live particles of beam and plasma (either may be empty) for the window of c.k0
