@@ -104,30 +104,6 @@ __device__ inline void lab_table_clear(double *tab, int ng) {
         tab[k] = v == 3 ? INFINITY : (v == 4 ? -INFINITY : 0.0);
     }
 }
-__device__ inline void lab_group_add(double *tab, const LabGroupSpec &G, const Params &P, double t, double x, double y,
-                                     double z, double ux, double uy, double uz, double w) {
-    const int g = lab_group_of(G, z, uz);
-    if (g < 0) return;
-    double L[8];
-    lab_of(P, t, x, y, z, ux, uy, uz, L);
-    double *e = tab + LAB_GROUP_VALUES * g;
-    atomicAdd(&e[0], 1.0);
-    atomicAdd(&e[1], w);
-    atomicAdd(&e[2], w * L[3]);
-    atomicMin(&e[3], L[3]);
-    atomicMax(&e[4], L[3]);
-    atomicAdd(&e[5], w * L[2]);
-    atomicAdd(&e[6], w * L[2] * L[2]);
-    atomicAdd(&e[7], w * L[0]);
-    atomicAdd(&e[8], w * L[0] * L[0]);
-    atomicAdd(&e[9], w * L[1]);
-    atomicAdd(&e[10], w * L[1] * L[1]);
-    atomicAdd(&e[11], w * L[4]);
-    atomicAdd(&e[12], w * L[4] * L[4]);
-    atomicAdd(&e[13], w * L[5]);
-    atomicAdd(&e[14], w * L[5] * L[5]);
-    atomicAdd(&e[15], w * L[7]);
-}
 // the block's nonempty groups into the global table
 __device__ inline void lab_table_flush(const double *tab, int ng, double *out) {
     for (int k = threadIdx.x; k < LAB_GROUP_VALUES * ng; k += blockDim.x) {

@@ -15,122 +15,47 @@
 #include <mutex>
 #include <vector>
 
-#include "pic_internal.h"
+#include "diag_dev.h"
 
 namespace pic {
 
-void split_rho(Ctx &c, double *rho, int mask);                 // k_split32.hip
-int split_plasma_kinetic_partials(Ctx &c, double *red);        // k_split32.hip
-int64_t split_beam_to64(Ctx &c, double *dst6);                 // k_split32.hip
-
-constexpr int DT = 256;
-
-template <int NV> __device__ inline void block_sum(double (*s)[DT], double v[NV], double *out) {
-    for (int k = 0; k < NV; ++k) s[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int h = DT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < NV; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int k = 0; k < NV; ++k) out[(int64_t)blockIdx.x * NV + k] = s[k][0];
-}
-
-// pass 1: count, w, w x, w y, w z, w ux, w uy, w uz, w cos kz, w sin kz, w cos 2kz, w sin 2kz, w (gamma - 1)
-__global__ void __launch_bounds__(DT) k_mom1(Part64 p, int64_t n, double wconst, double kb, double *out) {
-    __shared__ double s[13][DT];
+// FP64 particles: pass 1 and pass 2 of the beam, plasma count and kinetic energy
+__global__ void __launch_bounds__(DT) k_mom1(Part64 p, int64_t n, double kb, double *out) {
     double v[13] = {0};
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q < n && (!p.alive || p.alive[q])) {
-        double w = p.w ? p.w[q] : wconst;
-        double z = p.z[q], ux = p.ux[q], uy = p.uy[q], uz = p.uz[q];
-        double s1, c1, s2, c2;
-        sincos(kb * z, &s1, &c1);
-        sincos(2.0 * kb * z, &s2, &c2);
-        v[0] = 1.0;
-        v[1] = w;
-        v[2] = w * p.x[q];
-        v[3] = w * p.y[q];
-        v[4] = w * z;
-        v[5] = w * ux;
-        v[6] = w * uy;
-        v[7] = w * uz;
-        v[8] = w * c1;
-        v[9] = w * s1;
-        v[10] = w * c2;
-        v[11] = w * s2;
-        v[12] = w * (sqrt(1.0 + ux * ux + uy * uy + uz * uz) - 1.0);
-    }
-    block_sum<13>(s, v, out);
+    int64_t a, b;
+    row_range(n, a, b);
+    for (int64_t q = a + threadIdx.x; q < b; q += DT)
+        if (p.alive[q]) moment1_add(v, p.w[q], p.x[q], p.y[q], p.z[q], p.ux[q], p.uy[q], p.uz[q], kb);
+    block_sums<13>(v, out + 13 * (int64_t)blockIdx.x);
 }
 
-// pass 2: central second moments about the pass-1 means
-__global__ void __launch_bounds__(DT) k_mom2(Part64 p, int64_t n, double wconst, double mx, double my, double mz,
-                                             double mux, double muy, double muz, double *out) {
-    __shared__ double s[8][DT];
+__global__ void __launch_bounds__(DT) k_mom2(Part64 p, int64_t n, const double *m1, double *out) {
     double v[8] = {0};
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q < n && (!p.alive || p.alive[q])) {
-        double w = p.w ? p.w[q] : wconst;
-        double dx = p.x[q] - mx, dy = p.y[q] - my, dz = p.z[q] - mz;
-        double a = p.ux[q] - mux, b = p.uy[q] - muy, cz = p.uz[q] - muz;
-        v[0] = w * dx * dx;
-        v[1] = w * dy * dy;
-        v[2] = w * dz * dz;
-        v[3] = w * a * a;
-        v[4] = w * b * b;
-        v[5] = w * cz * cz;
-        v[6] = w * dx * a;
-        v[7] = w * dy * b;
-    }
-    block_sum<8>(s, v, out);
+    const Means M(m1);
+    int64_t a, b;
+    row_range(n, a, b);
+    for (int64_t q = a + threadIdx.x; q < b; q += DT)
+        if (p.alive[q]) moment2_add(v, M, p.w[q], p.x[q], p.y[q], p.z[q], p.ux[q], p.uy[q], p.uz[q]);
+    block_sums<8>(v, out + 8 * (int64_t)blockIdx.x);
 }
 
-// count and kinetic energy m w (gamma - 1) of the plasma slots (mobile ions: w < 0, mass mi)
 __global__ void __launch_bounds__(DT) k_kin(Part64 p, int64_t n, double mi, double *out) {
-    __shared__ double s[2][DT];
-    double v[2] = {0, 0};
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q < n && p.alive[q]) {
-        double ux = p.ux[q], uy = p.uy[q], uz = p.uz[q];
-        v[0] = 1.0;
-        const double w = p.w[q];
-        v[1] = (w < 0.0 ? -mi * w : w) * (sqrt(1.0 + ux * ux + uy * uy + uz * uz) - 1.0);
-    }
-    block_sum<2>(s, v, out);
+    double v[2] = {0};
+    int64_t a, b;
+    row_range(n, a, b);
+    for (int64_t q = a + threadIdx.x; q < b; q += DT)
+        if (p.alive[q]) kinetic_add(v, p.w[q], p.ux[q], p.uy[q], p.uz[q], mi);
+    block_sums<2>(v, out + 2 * (int64_t)blockIdx.x);
 }
 
 template <typename T> __global__ void __launch_bounds__(DT) k_fenergy(FieldsT<T> f, int64_t nc, double *out) {
-    __shared__ double s[1][DT];
     double v[1] = {0};
     for (int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x; q < nc; q += (int64_t)gridDim.x * DT)
         for (int c = 0; c < 3; ++c) {
             double e = f.E[c][q], b = f.B[c][q];
             v[0] += e * e + b * b;
         }
-    block_sum<1>(s, v, out);
-}
-
-// charge -w of FP64 particles on the nodes (mobile ions carry w < 0), FP64 atomics into rho (ring order)
-__global__ void __launch_bounds__(DT) k_rho64(Params P, int64_t k0, int k0r, Part64 p, int64_t n, double *rho) {
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q >= n || !p.alive[q]) return;
-    double X[3] = {p.x[q], p.y[q], p.z[q]};
-    double w[3][3];
-    int64_t lo[3];
-    for (int d = 0; d < 3; ++d) {
-        double nn = floor(X[d] + 0.5);
-        weights3<double>(X[d] - nn, w[d]);
-        lo[d] = (int64_t)nn - 1;
-    }
-    double qw = -p.w[q];
-    for (int c = 0; c < 3; ++c) {
-        int pl = ring_plane((int)(lo[2] + c - k0), k0r, P.nz);
-        for (int b = 0; b < 3; ++b)
-            for (int a = 0; a < 3; ++a)
-                atomicAdd(&rho[cell_index(P, (int)(lo[0] + a), (int)(lo[1] + b), pl)], qw * w[0][a] * w[1][b] * w[2][c]);
-    }
+    block_sums<1>(v, out + blockIdx.x);
 }
 
 // ion charge profile (logical planes): sum over sheets of w ppx ppy S(k - z_l)
@@ -152,109 +77,84 @@ __global__ void k_rho_ion(Params P, int64_t sh_lo, int64_t ns, double t, int64_t
     }
 }
 
-// r = div E - rho on nodes of the band [band, nz - band); max |r|, max |rho|,
-// max |r - r_prev| where the previous residual covers the same absolute plane.
+// r = div E - rho on nodes of the band [band, nz - band); max |r|, max |rho|, max |r - r_prev| where the
+// previous call's residual covers the same absolute plane.  The residual is kept in ring order: a plane
+// keeps its place while it is in the window, so that one pass reads the old value, stores the new one
+// and clears the charge (the scratch is a current array, zero between steps).  In-plane indices in 32
+// bits; a block takes its cells of every gridDim.y-th ring plane.  HBM: 64 us
+// at 128x128x512 (44 bytes a cell) against 65 + 46 + 20 for residual, store and clearing apart.
 template <typename T>
-__global__ void __launch_bounds__(DT) k_gauss(Params P, int k0r, FieldsT<T> f, const double *rho, const double *ion,
+__global__ void __launch_bounds__(DT) k_gauss(Params P, int k0r, FieldsT<T> f, double *rho, const double *ion,
                                               double *rprev, int64_t dk, int have, int band, double *out) {
-    __shared__ double s[3][DT];
+    __shared__ double s[3][DT / 64];
     double v[3] = {0, 0, 0};
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q < P.nc) {
-        int i = (int)(q % P.nx);
-        int64_t r = q / P.nx;
-        int j = (int)(r % P.ny);
-        int l = (int)(r / P.ny);
-        double rv = 0.0;
-        if (l >= band && l < P.nz - band) {
-            int p = ring_plane(l, k0r, P.nz), pm = ring_plane(l - 1, k0r, P.nz);
-            int64_t o = cell_index(P, i, j, p);
-            double dv = ((double)f.E[0][o] - (double)f.E[0][cell_index(P, i - 1, j, p)]) +
-                        ((double)f.E[1][o] - (double)f.E[1][cell_index(P, i, j - 1, p)]) +
-                        ((double)f.E[2][o] - (double)f.E[2][cell_index(P, i, j, pm)]);
-            double rh = rho[o] + ion[l];
-            rv = dv - rh;
-            v[0] = fabs(rv);
-            v[1] = fabs(rh);
-            int64_t lp = (int64_t)l + dk;  // same absolute plane in the previous call
-            if (have && lp >= band && lp < P.nz - band)
-                v[2] = fabs(rv - rprev[(int64_t)i + (int64_t)P.nx * (j + (int64_t)P.ny * lp)]);
+    const int c = (int)blockIdx.x * DT + (int)threadIdx.x;
+    if (c < P.plane) {
+        const int j = c / P.nx, i = c - j * P.nx;
+        const int64_t di = i == 0 ? P.nx - 1 : -1, dj = j == 0 ? (int64_t)P.nx * (P.ny - 1) : -(int64_t)P.nx;
+        for (int p = (int)blockIdx.y; p < P.nz; p += (int)gridDim.y) {
+            const int l = p < k0r ? p - k0r + P.nz : p - k0r, pm = p == 0 ? P.nz - 1 : p - 1;
+            const int64_t o = (int64_t)p * P.plane + c;
+            double rv = 0.0;
+            if (l >= band && l < P.nz - band) {
+                const double dv = ((double)f.E[0][o] - (double)f.E[0][o + di]) +
+                                  ((double)f.E[1][o] - (double)f.E[1][o + dj]) +
+                                  ((double)f.E[2][o] - (double)f.E[2][(int64_t)pm * P.plane + c]);
+                const double rh = rho[o] + ion[l];
+                rv = dv - rh;
+                v[0] = v[0] < fabs(rv) ? fabs(rv) : v[0];
+                v[1] = v[1] < fabs(rh) ? fabs(rh) : v[1];
+                const int64_t lp = (int64_t)l + dk;  // same absolute plane in the previous call
+                if (have && lp >= band && lp < P.nz - band) {
+                    const double dr = fabs(rv - rprev[o]);
+                    v[2] = v[2] < dr ? dr : v[2];
+                }
+            }
+            rprev[o] = rv;
+            rho[o] = 0.0;
         }
     }
-    for (int k = 0; k < 3; ++k) s[k][threadIdx.x] = v[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        double t = v[k];
+        for (int h = 32; h > 0; h >>= 1) {
+            const double q = __shfl_down(t, h);
+            t = t < q ? q : t;
+        }
+        if ((threadIdx.x & 63) == 0) s[k][threadIdx.x >> 6] = t;
+    }
     __syncthreads();
-    for (int h = DT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < 3; ++k) s[k][threadIdx.x] = fmax(s[k][threadIdx.x], s[k][threadIdx.x + h]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int k = 0; k < 3; ++k) out[3 * (int64_t)blockIdx.x + k] = s[k][0];
-}
-
-template <typename T>
-__global__ void __launch_bounds__(DT) k_store_r(Params P, int k0r, FieldsT<T> f, const double *rho, const double *ion,
-                                                double *rnew, int band) {
-    int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x;
-    if (q >= P.nc) return;
-    int i = (int)(q % P.nx);
-    int64_t r = q / P.nx;
-    int j = (int)(r % P.ny);
-    int l = (int)(r / P.ny);
-    double rv = 0.0;
-    if (l >= band && l < P.nz - band) {
-        int p = ring_plane(l, k0r, P.nz), pm = ring_plane(l - 1, k0r, P.nz);
-        int64_t o = cell_index(P, i, j, p);
-        double dv = ((double)f.E[0][o] - (double)f.E[0][cell_index(P, i - 1, j, p)]) +
-                    ((double)f.E[1][o] - (double)f.E[1][cell_index(P, i, j - 1, p)]) +
-                    ((double)f.E[2][o] - (double)f.E[2][cell_index(P, i, j, pm)]);
-        rv = dv - (rho[o] + ion[l]);
-    }
-    rnew[q] = rv;
-}
-
-// The nv values of nblk per-block partials (red[b nv + k]) reduced in a fixed
-// order by one block: thread t takes the blocks [t m, (t + 1) m) in order, then
-// a fixed tree; the results overwrite red[0 .. nv).  OP 0 sums, OP 1 takes the
-// maximum with 0.
-constexpr int RED_MAX_NV = 16;
-template <int OP> __global__ void __launch_bounds__(DT) k_reduce_partials(double *red, int64_t nblk, int nv) {
-    __shared__ double s[DT];
-    const int64_t m = (nblk + DT - 1) / DT, b0 = (int64_t)threadIdx.x * m, b1 = min(b0 + m, nblk);
-    double acc[RED_MAX_NV];
-#pragma unroll
-    for (int k = 0; k < RED_MAX_NV; ++k) acc[k] = 0.0;
-    for (int64_t b = b0; b < b1; ++b)
-#pragma unroll
-        for (int k = 0; k < RED_MAX_NV; ++k)
-            if (k < nv) {
-                const double v = red[b * nv + k];
-                acc[k] = OP == 0 ? acc[k] + v : (acc[k] < v ? v : acc[k]);
-            }
-    __syncthreads();  // every partial read before red[0 .. nv) is overwritten
-    for (int k = 0; k < nv; ++k) {
-        s[threadIdx.x] = acc[k < RED_MAX_NV ? k : 0];
-        __syncthreads();
-        for (int h = DT / 2; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) {
-                const double v = s[threadIdx.x + h];
-                s[threadIdx.x] = OP == 0 ? s[threadIdx.x] + v : (s[threadIdx.x] < v ? v : s[threadIdx.x]);
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) red[k] = s[0];
-        __syncthreads();
+    if (threadIdx.x < 3) {
+        double t = s[threadIdx.x][0];
+        for (int w = 1; w < DT / 64; ++w) t = t < s[threadIdx.x][w] ? s[threadIdx.x][w] : t;
+        out[3 * ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) + threadIdx.x] = t;
     }
 }
 
-// reduce nblk partials of nv values in red and copy the nv results to acc (host)
-static void reduce_partials(Ctx &c, double *red, int64_t nblk, int nv, int op, double *acc) {
+// The nv <= 16 values of `rows` partials (part[row nv + k]) reduced to res[0 .. nv) in a fixed order by
+// one workgroup: wave k takes value k, its lanes the rows lane, lane + 64, ..., then a fixed tree.  OP 0
+// sums, OP 1 takes the maximum with 0.
+template <int OP> __global__ void __launch_bounds__(1024) k_reduce_rows(const double *part, int64_t rows, int nv,
+                                                                        double *res) {
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (k >= nv) return;
+    double t = 0.0;
+    for (int64_t r = lane; r < rows; r += 64) {
+        const double v = part[r * nv + k];
+        t = OP == 0 ? t + v : (t < v ? v : t);
+    }
+    for (int h = 32; h > 0; h >>= 1) {
+        const double v = __shfl_down(t, h);
+        t = OP == 0 ? t + v : (t < v ? v : t);
+    }
+    if (lane == 0) res[k] = t;
+}
+
+static void reduce_rows(Ctx &c, const double *part, int64_t rows, int nv, int op, double *res) {
     if (op == 0)
-        hipLaunchKernelGGL(k_reduce_partials<0>, dim3(1), dim3(DT), 0, c.st, red, nblk, nv);
+        hipLaunchKernelGGL(k_reduce_rows<0>, dim3(1), dim3(64 * nv), 0, c.st, part, rows, nv, res);
     else
-        hipLaunchKernelGGL(k_reduce_partials<1>, dim3(1), dim3(DT), 0, c.st, red, nblk, nv);
-    hipMemcpyAsync(acc, red, 8 * (uint64_t)nv, hipMemcpyDeviceToHost, c.st);
-    hipStreamSynchronize(c.st);
+        hipLaunchKernelGGL(k_reduce_rows<1>, dim3(1), dim3(64 * nv), 0, c.st, part, rows, nv, res);
 }
 
 // lab-frame probe over the live FP64 beam slots: each block's five sums added to acc
@@ -306,8 +206,11 @@ __global__ void __launch_bounds__(DT) k_lab_groups64(Params P, LabGroupSpec G, P
     const int ng = G.nz * G.nu;
     lab_table_clear(tab, ng);
     __syncthreads();
-    for (int64_t q = (int64_t)blockIdx.x * DT + threadIdx.x; q < n; q += (int64_t)gridDim.x * DT)
-        if (p.alive[q]) lab_group_add(tab, G, P, t, p.x[q], p.y[q], p.z[q], p.ux[q], p.uy[q], p.uz[q], p.w[q]);
+    for (int64_t base = (int64_t)blockIdx.x * DT; base < n; base += (int64_t)gridDim.x * DT) {
+        const int64_t q = std::min<int64_t>(base + threadIdx.x, n - 1);
+        const bool in = base + threadIdx.x < n && p.alive[q];
+        lab_group_add_wave(tab, G, P, t, in, p.x[q], p.y[q], p.z[q], p.ux[q], p.uy[q], p.uz[q], p.w[q]);
+    }
     __syncthreads();
     lab_table_flush(tab, ng, out);
 }
@@ -361,17 +264,14 @@ void probe_step(Ctx &c) {
 
 // beam charge on the nodes (ring order), added into rho
 void beam_rho(Ctx &c, double *rho) {
-    const Params &P = c.P;
-    if (c.precision == PIC_FP64_PLAIN) {
-        if (c.nb_slots)
-            hipLaunchKernelGGL(k_rho64, dim3(nblocks(c.nb_slots, DT)), dim3(DT), 0, c.st, P, c.k0,
-                               (int)(c.k0 % P.nz), c.b64, c.nb_slots, rho);
-    } else {
+    if (c.precision == PIC_FP64_PLAIN)
+        rho64(c, rho, 1);
+    else
         split_rho(c, rho, 1);
-    }
 }
 
-// partial sums run_diag needs in red (doubles)
+// what the caller's reduction buffer has to hold (doubles), by the documented rule of one row of partials
+// per 256 particles, FP32 bins or cells; run_diag's sums need far fewer rows
 int64_t diag_partials(const Ctx &c, uint32_t mask) {
     const Params &P = c.P;
     const int64_t nb = c.precision == PIC_FP64_PLAIN ? c.nb_slots : c.beam.n_macro;
@@ -398,42 +298,95 @@ pic_status run_diag(Ctx &c, uint32_t mask, double kb, pic_diag_out *o, double *r
     o->window_beta = c.bw;
     o->window_x = c.win_x0 + c.bw * ((double)c.step * P.dt - c.win_t0);
     o->frac_bits = P.frac_bits;
-    int k0r = (int)(c.k0 % P.nz);
-    // beam as FP64 arrays
-    Part64 bp;
-    int64_t nb;
-    double wconst = P.wbeam;
-    if (c.precision == PIC_FP64_PLAIN) {
-        bp = c.b64;
-        nb = c.nb_slots;
-    } else {
-        nb = split_beam_to64(c, c.stage);
-        uint64_t cap = (uint64_t)std::max<int64_t>(c.beam.n_macro, 1);
-        bp.x = c.stage;
-        bp.y = c.stage + cap;
-        bp.z = c.stage + 2 * cap;
-        bp.ux = c.stage + 3 * cap;
-        bp.uy = c.stage + 4 * cap;
-        bp.uz = c.stage + 5 * cap;
-        bp.w = nullptr;
-        bp.alive = nullptr;
+    const int k0r = (int)(c.k0 % P.nz);
+    const bool plain = c.precision == PIC_FP64_PLAIN;
+    // every sum's results stay on the device (res) until all are there: one copy, one synchronisation
+    enum { R_M1 = 0, R_M2 = 16, R_FIELD = 24, R_PLASMA = 26, R_GAUSS = 28, R_END = 31 };
+    static_assert(R_END <= SUM_RESULTS, "results fit");
+    double *const res = red, *const part = red + SUM_RESULTS;
+    PIC_HIP(c, hipMemsetAsync(res, 0, 8 * SUM_RESULTS, c.st));
+    const bool beam = plain ? c.nb_slots > 0 : c.beam.n_macro > 0;
+    if (beam) {
+        int rows = plain ? sum_rows(c.nb_slots) : 0;
+        if (plain)
+            hipLaunchKernelGGL(k_mom1, dim3(rows), dim3(DT), 0, c.st, c.b64, c.nb_slots, kb, part);
+        else
+            rows = split_moments1(c, kb, part);
+        reduce_rows(c, part, rows, 13, 0, res + R_M1);
+        if (mask & PIC_DIAG_MOMENTS) {
+            if (plain)
+                hipLaunchKernelGGL(k_mom2, dim3(rows), dim3(DT), 0, c.st, c.b64, c.nb_slots, res + R_M1, part);
+            else
+                rows = split_moments2(c, res + R_M1, part);
+            reduce_rows(c, part, rows, 8, 0, res + R_M2);
+        }
     }
-    double m1[13] = {0};
-    if (nb > 0) {
-        int nblk = nblocks(nb, DT);
-        hipLaunchKernelGGL(k_mom1, dim3(nblk), dim3(DT), 0, c.st, bp, nb, wconst, kb, red);
-        reduce_partials(c, red, nblk, 13, 0, m1);
+    FieldsT<double> f64;
+    FieldsT<float> f32;
+    for (int k = 0; k < 3; ++k) {
+        f64.E[k] = c.E64[k];
+        f64.B[k] = c.B64[k];
+        f32.E[k] = c.E32[k];
+        f32.B[k] = c.B32[k];
     }
+    if (mask & PIC_DIAG_ENERGY) {
+        const int rows = sum_rows(P.nc);
+        if (plain)
+            hipLaunchKernelGGL(k_fenergy<double>, dim3(rows), dim3(DT), 0, c.st, f64, P.nc, part);
+        else
+            hipLaunchKernelGGL(k_fenergy<float>, dim3(rows), dim3(DT), 0, c.st, f32, P.nc, part);
+        reduce_rows(c, part, rows, 1, 0, res + R_FIELD);
+    }
+    if (P.has_plasma && (!plain || c.np_slots > 0)) {  // plasma counts and kinetic energy
+        int rows = plain ? sum_rows(c.np_slots) : 0;
+        if (plain)
+            hipLaunchKernelGGL(k_kin, dim3(rows), dim3(DT), 0, c.st, c.p64, c.np_slots, P.mi, part);
+        else
+            rows = split_plasma_kinetic(c, part);
+        reduce_rows(c, part, rows, 2, 0, res + R_PLASMA);
+    }
+    if (mask & PIC_DIAG_GAUSS) {
+        const int band = 8;
+        // scratch: rho in J_x (zero between steps), ion profile in the ion-current buffer
+        double *rho = plain ? c.J64[0] : (double *)c.Ji[0];
+        double *ion = plain ? c.jion64 : (double *)c.jioni;
+        if (plain)
+            rho64(c, rho, 3);
+        else
+            split_rho(c, rho, 3);
+        if (P.ions && c.sh_hi > c.sh_lo)
+            hipLaunchKernelGGL(k_rho_ion, dim3(nblocks(c.sh_hi - c.sh_lo, 128)), dim3(128), 0, c.st, P, c.sh_lo,
+                               c.sh_hi - c.sh_lo, o->t, c.k0, ion, !plain);
+        launch_neutraliser_rho(c, rho);
+        // about 2048 workgroups, never more rows than the buffer of diag_partials() holds
+        const int nbx = nblocks(P.plane, DT);
+        const int64_t most = std::min<int64_t>(2048, 8 * (int64_t)nblocks(P.nc, DT));
+        const dim3 grid(nbx, (unsigned)std::min<int64_t>(P.nz, std::max<int64_t>(1, most / nbx)));
+        const int64_t dk = c.k0 - c.rprev_k0;
+        if (plain)
+            hipLaunchKernelGGL(k_gauss<double>, grid, dim3(DT), 0, c.st, P, k0r, f64, rho, ion, c.rprev, dk,
+                               c.have_rprev, band, part);
+        else
+            hipLaunchKernelGGL(k_gauss<float>, grid, dim3(DT), 0, c.st, P, k0r, f32, rho, ion, c.rprev, dk,
+                               c.have_rprev, band, part);
+        PIC_HIP(c, hipMemsetAsync(ion, 0, 8 * P.nz, c.st));
+        reduce_rows(c, part, (int64_t)grid.x * grid.y, 3, 1, res + R_GAUSS);
+    }
+    double h[R_END];
+    int32_t fl = 0;
+    PIC_HIP(c, hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, c.st));
+    PIC_HIP(c, hipMemcpyAsync(&fl, c.dflags, 4, hipMemcpyDeviceToHost, c.st));
+    hipError_t e = hipStreamSynchronize(c.st);
+    if (e != hipSuccess) return hip_check(c, e, "diag");
+    o->error_flags = fl;
+    const double *m1 = h + R_M1, *m2 = h + R_M2, W = m1[1];
     o->n_beam = m1[0];
     o->beam_lost = (double)c.beam.n_macro - m1[0];
-    o->wsum = m1[1];
-    double W = m1[1];
+    o->wsum = W;
     if (W > 0) {
-        double mean[6];
-        for (int k = 0; k < 6; ++k) mean[k] = m1[2 + k] / W;
         for (int k = 0; k < 3; ++k) {
-            o->mean[k] = mean[k];
-            o->umean[k] = mean[3 + k];
+            o->mean[k] = m1[2 + k] / W;
+            o->umean[k] = m1[5 + k] / W;
         }
         o->b1_re = m1[8] / W;
         o->b1_im = m1[9] / W;
@@ -443,11 +396,6 @@ pic_status run_diag(Ctx &c, uint32_t mask, double kb, pic_diag_out *o, double *r
         o->b2_abs = sqrt(m1[10] * m1[10] + m1[11] * m1[11]) / W;
         o->kin_beam = m1[12];
         if (mask & PIC_DIAG_MOMENTS) {
-            int nblk = nblocks(nb, DT);
-            hipLaunchKernelGGL(k_mom2, dim3(nblk), dim3(DT), 0, c.st, bp, nb, wconst, mean[0], mean[1], mean[2],
-                               mean[3], mean[4], mean[5], red);
-            double m2[8];
-            reduce_partials(c, red, nblk, 8, 0, m2);
             for (int k = 0; k < 3; ++k) {
                 o->sigma[k] = sqrt(m2[k] / W);
                 o->usigma[k] = sqrt(m2[3 + k] / W);
@@ -458,97 +406,16 @@ pic_status run_diag(Ctx &c, uint32_t mask, double kb, pic_diag_out *o, double *r
             }
         }
     }
-    if (mask & PIC_DIAG_ENERGY) {
-        int nblk = 1024;
-        double fe[1];
-        if (c.precision == PIC_FP64_PLAIN) {
-            FieldsT<double> f;
-            for (int k = 0; k < 3; ++k) {
-                f.E[k] = c.E64[k];
-                f.B[k] = c.B64[k];
-            }
-            hipLaunchKernelGGL(k_fenergy<double>, dim3(nblk), dim3(DT), 0, c.st, f, P.nc, red);
-        } else {
-            FieldsT<float> f;
-            for (int k = 0; k < 3; ++k) {
-                f.E[k] = c.E32[k];
-                f.B[k] = c.B32[k];
-            }
-            hipLaunchKernelGGL(k_fenergy<float>, dim3(nblk), dim3(DT), 0, c.st, f, P.nc, red);
-        }
-        reduce_partials(c, red, nblk, 1, 0, fe);
-        o->field_energy = 0.5 * fe[0];
-    }
-    // plasma counts and kinetic energy
-    if (P.has_plasma) {
-        if (c.precision == PIC_FP64_PLAIN) {
-            if (c.np_slots > 0) {
-                int nblk = nblocks(c.np_slots, DT);
-                hipLaunchKernelGGL(k_kin, dim3(nblk), dim3(DT), 0, c.st, c.p64, c.np_slots, c.P.mi, red);
-                double kp[2];
-                reduce_partials(c, red, nblk, 2, 0, kp);
-                o->n_plasma = kp[0];
-                o->kin_plasma = kp[1];
-            }
-        } else {
-            double kp[2];
-            const int nblk = split_plasma_kinetic_partials(c, red);
-            reduce_partials(c, red, nblk, 2, 0, kp);
-            o->n_plasma = kp[0];
-            o->kin_plasma = kp[1];
-        }
-    }
+    if (mask & PIC_DIAG_ENERGY) o->field_energy = 0.5 * h[R_FIELD];
+    o->n_plasma = h[R_PLASMA];
+    o->kin_plasma = h[R_PLASMA + 1];
     if (mask & PIC_DIAG_GAUSS) {
-        const int band = 8;
-        // scratch: rho in J_x (zero between steps), ion profile in the ion-current buffer
-        double *rho = c.precision == PIC_FP64_PLAIN ? c.J64[0] : (double *)c.Ji[0];
-        double *ion = c.precision == PIC_FP64_PLAIN ? c.jion64 : (double *)c.jioni;
-        if (c.precision == PIC_FP64_PLAIN) {
-            if (c.nb_slots) hipLaunchKernelGGL(k_rho64, dim3(nblocks(c.nb_slots, DT)), dim3(DT), 0, c.st, P, c.k0, k0r, c.b64, c.nb_slots, rho);
-            if (c.np_slots) hipLaunchKernelGGL(k_rho64, dim3(nblocks(c.np_slots, DT)), dim3(DT), 0, c.st, P, c.k0, k0r, c.p64, c.np_slots, rho);
-        } else {
-            split_rho(c, rho, 3);
-        }
-        if (P.ions && c.sh_hi > c.sh_lo)
-            hipLaunchKernelGGL(k_rho_ion, dim3(nblocks(c.sh_hi - c.sh_lo, 128)), dim3(128), 0, c.st, P, c.sh_lo,
-                               c.sh_hi - c.sh_lo, o->t, c.k0, ion, c.precision != PIC_FP64_PLAIN);
-        launch_neutraliser_rho(c, rho);
-        int nblk = nblocks(P.nc, DT);
-        int64_t dk = c.k0 - c.rprev_k0;
-        if (c.precision == PIC_FP64_PLAIN) {
-            FieldsT<double> f;
-            for (int k = 0; k < 3; ++k) {
-                f.E[k] = c.E64[k];
-                f.B[k] = c.B64[k];
-            }
-            hipLaunchKernelGGL(k_gauss<double>, dim3(nblk), dim3(DT), 0, c.st, P, k0r, f, rho, ion, c.rprev, dk,
-                               c.have_rprev, band, red);
-            hipLaunchKernelGGL(k_store_r<double>, dim3(nblk), dim3(DT), 0, c.st, P, k0r, f, rho, ion, c.rprev, band);
-        } else {
-            FieldsT<float> f;
-            for (int k = 0; k < 3; ++k) {
-                f.E[k] = c.E32[k];
-                f.B[k] = c.B32[k];
-            }
-            hipLaunchKernelGGL(k_gauss<float>, dim3(nblk), dim3(DT), 0, c.st, P, k0r, f, rho, ion, c.rprev, dk,
-                               c.have_rprev, band, red);
-            hipLaunchKernelGGL(k_store_r<float>, dim3(nblk), dim3(DT), 0, c.st, P, k0r, f, rho, ion, c.rprev, band);
-        }
-        hipMemsetAsync(rho, 0, 8 * P.nc, c.st);
-        hipMemsetAsync(ion, 0, 8 * P.nz, c.st);
-        double g[3];
-        reduce_partials(c, red, nblk, 3, 1, g);
-        o->gauss_max = g[0];
-        o->rho_max = g[1];
-        o->gauss_drift = c.have_rprev ? g[2] : -1.0;
+        o->gauss_max = h[R_GAUSS];
+        o->rho_max = h[R_GAUSS + 1];
+        o->gauss_drift = c.have_rprev ? h[R_GAUSS + 2] : -1.0;
         c.have_rprev = 1;
         c.rprev_k0 = c.k0;
     }
-    int32_t fl = 0;
-    hipMemcpyAsync(&fl, c.dflags, 4, hipMemcpyDeviceToHost, c.st);
-    hipError_t e = hipStreamSynchronize(c.st);
-    if (e != hipSuccess) return hip_check(c, e, "diag");
-    o->error_flags = fl;
     return PIC_OK;
 }
 

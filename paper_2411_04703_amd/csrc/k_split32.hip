@@ -27,7 +27,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "pic_internal.h"
+#include "diag_dev.h"
 
 namespace pic {
 
@@ -59,7 +59,7 @@ struct SplitState {
     int64_t items_cap;
     int64_t *scan_part;
     int32_t *tmpcnt;       // 2 x nbins
-    int64_t *tmpoff;       // 2 x (nbins + 2)
+    int64_t *tmpoff;       // nbins + 2: a store's BinRanks
     int grid;              // persistent grid of the step kernel
     void (*kern)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, struct IOPair, FieldsT<float>,
                  long long *, long long *, long long *, int32_t *, const double *, const float *,
@@ -71,9 +71,6 @@ struct SplitState {
     float *tabC, *tabS;
     int nslab;             // work queues: slabs of whole bin layers (one per XCD when they divide evenly)
     int32_t *qnext, *qstart;  // per-slab item counters (stride QPAD); slab q's items are [qstart[q], qstart[q + 1])
-    // host copies of a store's bin counts, offsets and prefix (sized once: later reads allocate nothing)
-    std::vector<int32_t> hcnt;
-    std::vector<int64_t> hoff, hpref;
 };
 
 static SplitState &SS(Ctx &c) { return *static_cast<SplitState *>(c.split); }
@@ -1281,9 +1278,6 @@ static Part32 carve32(char *base, int64_t slots) {
 void split_setup(Ctx &c) {
     SplitState *X = new SplitState();
     c.split = X;
-    X->hcnt.resize(c.P.nbins);
-    X->hoff.resize(c.P.nbins + 1);
-    X->hpref.resize(c.P.nbins + 2);
     const Params &P = c.P;
     char *A = c.arena;
     int64_t nb = P.nbins;
@@ -1840,167 +1834,251 @@ pic_status split_check(Ctx &c) {
 }
 
 // ---------------------------------------------------------------- read-back
-// one block per bin (plus one for the overflow tail): FP64 absolute coordinates
-__global__ void k_split_out(Params P, int64_t k0, Part32 in, const int64_t *off, const int32_t *cnt, int64_t ovf_start,
-                            int32_t ovf_n, const int64_t *pref, int nbins, double *dst, int64_t stride, int nout,
-                            int32_t *alive) {
-    int b = blockIdx.x;
-    int64_t s0, n;
-    if (b < nbins) {
-        s0 = off[b];
-        int64_t cap = off[b + 1] - off[b];
-        n = cnt[b] < cap ? cnt[b] : cap;
-    } else {
-        s0 = ovf_start;
-        n = ovf_n;
-    }
-    int64_t d0 = pref[b];
-    for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
-        int64_t s = s0 + k, d = d0 + k;
-        if (alive) {
-            alive[d] = 1;
-            continue;
+// The valid particles of a store numbered through in bin order (the overflow tail last): pref[b] of them
+// come before bin b, pref[nbins] before the tail, pref[nbins + 1] in all.
+struct BinRanks {
+    const int64_t *pref, *off;
+    int64_t ovf_start;
+    int nbins;
+    // bin of particle d (nbins: the tail): the last one that starts at or before it
+    __device__ int bin(int64_t d) const {
+        int lo = 0, hi = nbins;
+        while (lo < hi) {
+            const int m = (lo + hi + 1) >> 1;
+            if (pref[m] <= d) lo = m;
+            else hi = m - 1;
         }
-        int i, j, l;
-        unpack_cell(P, in.cell[s], i, j, l);
-        double v[7] = {(i + 0.5) + (double)in.ox[s], (j + 0.5) + (double)in.oy[s],
-                       ((double)(k0 + l) + 0.5) + (double)in.oz[s],
-                       (double)in.ux[s], (double)in.uy[s], (double)in.uz[s], (double)in.w[s]};
-        for (int q = 0; q < nout; ++q) dst[q * stride + d] = v[q];
+        return lo;
     }
-}
+    // slot of particle d; b: the bin of a particle before it, moved on to d's
+    __device__ int64_t slot(int64_t d, int &b) const {
+        if (d >= pref[b + 1]) {
+            ++b;
+            if (d >= pref[b + 1]) b = bin(d);
+        }
+        return (b < nbins ? off[b] : ovf_start) + (d - pref[b]);
+    }
+};
 
-// charge -w of split particles on the nodes (mobile ions carry w < 0), FP64 atomics into rho (ring order)
-__global__ void k_split_rho(Params P, int64_t k0, int k0r, Part32 in, const int64_t *off, const int32_t *cnt,
-                            int64_t ovf_start, int32_t ovf_n, int nbins, double *rho) {
-    int b = blockIdx.x;
-    int64_t s0, n;
-    if (b < nbins) {
-        s0 = off[b];
-        int64_t cap = off[b + 1] - off[b];
-        n = cnt[b] < cap ? cnt[b] : cap;
-    } else {
-        s0 = ovf_start;
-        n = ovf_n;
-    }
-    for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
-        int64_t s = s0 + k;
-        int i, j, l;
-        unpack_cell(P, in.cell[s], i, j, l);
-        float o[3] = {in.ox[s], in.oy[s], in.oz[s]};
-        double w[3][3];
-        int lo[3];
-        const int base[3] = {i, j, l};
-        for (int d = 0; d < 3; ++d) {
-            int nn = o[d] >= 0.0f ? 1 : 0;
-            weights3<double>((double)o[d] + 0.5 - nn, w[d]);
-            lo[d] = base[d] + nn - 1;
-        }
-        double qw = -(double)in.w[s];
-        for (int c = 0; c < 3; ++c) {
-            int p = ring_plane(lo[2] + c, k0r, P.nz);
-            for (int bb = 0; bb < 3; ++bb)
-                for (int a = 0; a < 3; ++a)
-                    atomicAdd(&rho[cell_index(P, lo[0] + a, lo[1] + bb, p)], qw * w[0][a] * w[1][bb] * w[2][c]);
-        }
-    }
-}
-
-__global__ void k_split_kin(Params P, Part32 in, const int64_t *off, const int32_t *cnt, int64_t ovf_start,
-                            int32_t ovf_n, int nbins, double *part) {
-    __shared__ double s[2][256];
-    int b = blockIdx.x;
-    int64_t s0, n;
-    if (b < nbins) {
-        s0 = off[b];
-        int64_t cap = off[b + 1] - off[b];
-        n = cnt[b] < cap ? cnt[b] : cap;
-    } else {
-        s0 = ovf_start;
-        n = ovf_n;
-    }
-    double v0 = 0, v1 = 0;
-    for (int64_t k = threadIdx.x; k < n; k += 256) {
-        int64_t q = s0 + k;
-        double ux = in.ux[q], uy = in.uy[q], uz = in.uz[q];
-        v0 += 1.0;
-        const double w = (double)in.w[q];
-        v1 += (w < 0.0 ? -P.mi * w : w) * (sqrt(1.0 + ux * ux + uy * uy + uz * uz) - 1.0);
-    }
-    s[0][threadIdx.x] = v0;
-    s[1][threadIdx.x] = v1;
+// pref of a store, by one workgroup
+__global__ void __launch_bounds__(1024) k_split_prefix(const int64_t *off, const int32_t *cnt, const int32_t *ovf,
+                                                       int64_t ovf_cap, int nbins, int64_t *pref) {
+    constexpr int V = 4;
+    __shared__ int64_t ws[16], run;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t == 0) run = 0;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            s[0][threadIdx.x] += s[0][threadIdx.x + h];
-            s[1][threadIdx.x] += s[1][threadIdx.x + h];
+    for (int base = 0; base < nbins; base += 1024 * V) {
+        int64_t n[V], sum = 0;
+        for (int v = 0; v < V; ++v) {
+            const int b = base + t * V + v;
+            n[v] = b < nbins ? bin_count(off, cnt, b) : 0;
+            sum += n[v];
+        }
+        int64_t acc = sum;
+        for (int k = 1; k < 64; k <<= 1) {
+            const int64_t u = __shfl_up(acc, k);
+            if (lane >= k) acc += u;
+        }
+        if (lane == 63) ws[wave] = acc;
+        __syncthreads();
+        int64_t p = run + acc - sum;
+        for (int w = 0; w < wave; ++w) p += ws[w];
+        for (int v = 0; v < V; ++v) {
+            const int b = base + t * V + v;
+            if (b < nbins) pref[b] = p;
+            p += n[v];
         }
         __syncthreads();
+        if (t == 1023) run = p;
+        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        part[2 * b] = s[0][0];
-        part[2 * b + 1] = s[1][0];
+    if (t == 0) {
+        pref[nbins] = run;
+        pref[nbins + 1] = run + min((int64_t)*ovf, ovf_cap);
     }
 }
 
-// prefix offsets (host) of the valid particles of each bin (+ overflow) of species sp
-static int64_t split_prefix(Ctx &c, int sp, int32_t &ovf_n) {
+// the store's particles in canonical order: FP64 absolute coordinates, or the alive flags
+__global__ void __launch_bounds__(256) k_split_out(Params P, int64_t k0, Part32 in, BinRanks R, double *dst,
+                                                   int64_t n, int32_t *alive) {
+    const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (d >= n) return;
+    if (alive) {
+        alive[d] = 1;
+        return;
+    }
+    int b = R.bin(d);
+    const int64_t s = R.slot(d, b);
+    int i, j, l;
+    unpack_cell(P, in.cell[s], i, j, l);
+    dst[d] = (i + 0.5) + (double)in.ox[s];
+    dst[n + d] = (j + 0.5) + (double)in.oy[s];
+    dst[2 * n + d] = ((double)(k0 + l) + 0.5) + (double)in.oz[s];
+    dst[3 * n + d] = (double)in.ux[s];
+    dst[4 * n + d] = (double)in.uy[s];
+    dst[5 * n + d] = (double)in.uz[s];
+    dst[6 * n + d] = (double)in.w[s];
+}
+
+static BinRanks bin_ranks(Ctx &c, int sp) {
     SplitState &X = SS(c);
-    int64_t nb = c.P.nbins;
     Store &s = X.s[sp];
-    int cur = c.cur32;
-    std::vector<int32_t> &h = X.hcnt;
-    std::vector<int64_t> &off = X.hoff, &pref = X.hpref;
-    (void)hipMemcpyAsync(h.data(), s.cnt[cur], 4 * nb, hipMemcpyDeviceToHost, c.st);
-    (void)hipMemcpyAsync(off.data(), s.off[cur], 8 * (nb + 1), hipMemcpyDeviceToHost, c.st);
-    (void)hipMemcpyAsync(&ovf_n, s.ovf[cur], 4, hipMemcpyDeviceToHost, c.st);
-    (void)hipStreamSynchronize(c.st);
-    ovf_n = (int32_t)std::min<int64_t>(ovf_n, s.ovf_cap);
-    pref[0] = 0;
-    for (int64_t b = 0; b < nb; ++b) pref[b + 1] = pref[b] + std::min<int64_t>(h[b], off[b + 1] - off[b]);
-    pref[nb + 1] = pref[nb] + ovf_n;
-    (void)hipMemcpyAsync(X.tmpoff, pref.data(), 8 * (nb + 2), hipMemcpyHostToDevice, c.st);
-    return pref[nb + 1];
+    const int cur = c.cur32;
+    hipLaunchKernelGGL(k_split_prefix, dim3(1), dim3(1024), 0, c.st, s.off[cur], s.cnt[cur], s.ovf[cur], s.ovf_cap,
+                       c.P.nbins, X.tmpoff);
+    return BinRanks{X.tmpoff, s.off[cur], s.bin_slots, c.P.nbins};
 }
 
 void split_read(Ctx &c, int sp, double *dst7, int32_t *alive, int64_t *n) {
     SplitState &X = SS(c);
-    int32_t ovf_n = 0;
-    int64_t tot = split_prefix(c, sp, ovf_n);
+    const BinRanks R = bin_ranks(c, sp);
+    int64_t tot = 0;
+    (void)hipMemcpyAsync(&tot, X.tmpoff + c.P.nbins + 1, 8, hipMemcpyDeviceToHost, c.st);
+    (void)hipStreamSynchronize(c.st);
     *n = tot;
     if ((!dst7 && !alive) || tot == 0) return;
-    Store &s = X.s[sp];
-    int cur = c.cur32;
-    hipLaunchKernelGGL(k_split_out, dim3(c.P.nbins + 1), dim3(256), 0, c.st, c.P, c.k0, s.buf[cur], s.off[cur],
-                       s.cnt[cur], s.bin_slots, ovf_n, X.tmpoff, c.P.nbins, dst7, tot, 7, alive);
+    hipLaunchKernelGGL(k_split_out, dim3(nblocks(tot, 256)), dim3(256), 0, c.st, c.P, c.k0, X.s[sp].buf[c.cur32], R,
+                       dst7, tot, alive);
 }
 
-int64_t split_beam_to64(Ctx &c, double *dst6) {
-    SplitState &X = SS(c);
-    int32_t ovf_n = 0;
-    int64_t tot = split_prefix(c, 0, ovf_n);
-    if (tot == 0) return 0;
-    Store &s = X.s[0];
-    int cur = c.cur32;
-    int64_t stride = std::max<int64_t>(c.beam.n_macro, 1);
-    if (tot > stride) tot = stride;  // cannot happen: beam particles are never created
-    hipLaunchKernelGGL(k_split_out, dim3(c.P.nbins + 1), dim3(256), 0, c.st, c.P, c.k0, s.buf[cur], s.off[cur],
-                       s.cnt[cur], s.bin_slots, ovf_n, X.tmpoff, c.P.nbins, dst6, stride, 6, (int32_t *)nullptr);
-    return tot;
+// ---------------------------------------------------------------- diagnostics
+// A workgroup's particles: a contiguous range of the store's numbering, so that crowded bins are shared
+// out (one workgroup per bin left the rest waiting for a beam's core: 0.53 ms to write the 4.2 M beam
+// particles out as FP64, which the moments were then taken from; they are now read where they are).
+template <int PASS>
+__global__ void __launch_bounds__(DT) k_split_moments(Params P, int64_t k0, Part32 in, BinRanks R, double w, double kb,
+                                                      const double *m1, double *out) {
+    constexpr int NV = PASS == 1 ? 13 : 8;
+    double v[13] = {0};
+    const Means M = PASS == 1 ? Means() : Means(m1);
+    int64_t d, end;
+    row_range(R.pref[R.nbins + 1], d, end);
+    d += threadIdx.x;
+    int b = d < end ? R.bin(d) : 0;
+    for (; d < end; d += DT) {
+        const int64_t s = R.slot(d, b);
+        int i, j, l;
+        unpack_cell(P, in.cell[s], i, j, l);
+        const double x = (i + 0.5) + (double)in.ox[s], y = (j + 0.5) + (double)in.oy[s],
+                     z = ((double)(k0 + l) + 0.5) + (double)in.oz[s];
+        if (PASS == 1)
+            moment1_add(v, w, x, y, z, in.ux[s], in.uy[s], in.uz[s], kb);
+        else
+            moment2_add(v, M, w, x, y, z, in.ux[s], in.uy[s], in.uz[s]);
+    }
+    block_sums<NV>(v, out + NV * (int64_t)blockIdx.x);
+}
+
+int split_moments1(Ctx &c, double kb, double *part) {
+    const int rows = sum_rows(c.beam.n_macro);
+    const BinRanks R = bin_ranks(c, 0);
+    hipLaunchKernelGGL(k_split_moments<1>, dim3(rows), dim3(DT), 0, c.st, c.P, c.k0, SS(c).s[0].buf[c.cur32], R,
+                       c.P.wbeam, kb, (const double *)nullptr, part);
+    return rows;
+}
+
+int split_moments2(Ctx &c, const double *m1, double *part) {
+    const int rows = sum_rows(c.beam.n_macro);
+    const Store &s = SS(c).s[0];
+    const BinRanks R{SS(c).tmpoff, s.off[c.cur32], s.bin_slots, c.P.nbins};
+    hipLaunchKernelGGL(k_split_moments<2>, dim3(rows), dim3(DT), 0, c.st, c.P, c.k0, s.buf[c.cur32], R, c.P.wbeam, 0.0,
+                       m1, part);
+    return rows;
+}
+
+// plasma count and kinetic energy: workgroups stride over the bins (the overflow tail is "bin" nbins)
+__global__ void __launch_bounds__(DT) k_split_kin(Params P, Part32 in, const int64_t *off, const int32_t *cnt,
+                                                  int64_t ovf_start, const int32_t *ovf, int64_t ovf_cap, double *out) {
+    double v[2] = {0};
+    for (int b = blockIdx.x; b <= P.nbins; b += gridDim.x) {
+        const int64_t s0 = b < P.nbins ? off[b] : ovf_start,
+                      n = b < P.nbins ? bin_count(off, cnt, b) : min((int64_t)*ovf, ovf_cap);
+        for (int64_t k = threadIdx.x; k < n; k += DT)
+            kinetic_add(v, in.w[s0 + k], in.ux[s0 + k], in.uy[s0 + k], in.uz[s0 + k], P.mi);
+    }
+    block_sums<2>(v, out + 2 * (int64_t)blockIdx.x);
+}
+
+int split_plasma_kinetic(Ctx &c, double *part) {
+    const Store &s = SS(c).s[1];
+    const int cur = c.cur32, rows = std::min(c.P.nbins + 1, SUM_ROWS);
+    hipLaunchKernelGGL(k_split_kin, dim3(rows), dim3(DT), 0, c.st, c.P, s.buf[cur], s.off[cur], s.cnt[cur],
+                       s.bin_slots, s.ovf[cur], s.ovf_cap, part);
+    return rows;
+}
+
+// Charge -w of split particles on the nodes (mobile ions carry w < 0): summed in an LDS box of the bin's
+// nodes -1 .. T + 1 and added into rho (ring order).  Blocks (bin, part): a crowded bin's particles go to
+// gridDim.y blocks.  27 global FP64 atomics a particle took 20.5 ms for the 128x128x512 run's beam and
+// plasma, this takes 0.37 (LDS adds of 8 clocks a wave); the last "bin" is the overflow tail, which still takes them.
+__global__ void __launch_bounds__(256) k_split_rho(Params P, int64_t k0, int k0r, Part32 in, const int64_t *off,
+                                                   const int32_t *cnt, int64_t ovf_start, const int32_t *ovf,
+                                                   int64_t ovf_cap, int per, double *rho) {
+    extern __shared__ __align__(16) double rbox[];
+    const int b = blockIdx.x;
+    const bool tail = b == P.nbins;
+    const int64_t s0 = tail ? ovf_start : off[b], n = tail ? min((int64_t)*ovf, ovf_cap) : bin_count(off, cnt, b);
+    if ((int64_t)blockIdx.y * per >= n) return;
+    const int X = P.tx + 3, Y = P.ty + 3, N = X * Y * (P.tz + 3);
+    const int t0x = (b % P.ntx) * P.tx, t0y = ((b / P.ntx) % P.nty) * P.ty, t0z = (b / (P.ntx * P.nty)) * P.tz;
+    if (!tail) {
+        for (int e = threadIdx.x; e < N; e += 256) rbox[e] = 0.0;
+        __syncthreads();
+    }
+    for (int64_t q0 = (int64_t)blockIdx.y * per; q0 < n; q0 += (int64_t)gridDim.y * per)
+        for (int64_t q = q0 + threadIdx.x; q < min(n, q0 + per); q += 256) {
+            const int64_t s = s0 + q;
+            int i, j, l;
+            unpack_cell(P, in.cell[s], i, j, l);
+            const float o[3] = {in.ox[s], in.oy[s], in.oz[s]};
+            double w[3][3];
+            int nn[3];
+            for (int d = 0; d < 3; ++d) {
+                nn[d] = o[d] >= 0.0f ? 1 : 0;
+                weights3<double>((double)o[d] + 0.5 - nn[d], w[d]);
+            }
+            const double qw = -(double)in.w[s];
+            if (tail) {
+                for (int c = 0; c < 3; ++c) {
+                    const int p = ring_plane(l + nn[2] - 1 + c, k0r, P.nz);
+                    for (int bb = 0; bb < 3; ++bb)
+                        for (int a = 0; a < 3; ++a)
+                            atomicAdd(&rho[cell_index(P, i + nn[0] - 1 + a, j + nn[1] - 1 + bb, p)],
+                                      qw * w[0][a] * w[1][bb] * w[2][c]);
+                }
+                continue;
+            }
+            double *f = rbox + (i - t0x + nn[0]) + X * ((j - t0y + nn[1]) + Y * (l - t0z + nn[2]));
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int bb = 0; bb < 3; ++bb)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        atomicAdd(f + a + X * (bb + Y * c), qw * w[0][a] * w[1][bb] * w[2][c]);
+        }
+    if (tail) return;
+    __syncthreads();
+    for (int e = threadIdx.x; e < N; e += 256) {
+        const double v = rbox[e];
+        if (v == 0.0) continue;
+        const int y = e / X, a = e - y * X, c = y / Y, bb = y - c * Y, l = t0z - 1 + c;
+        if (l >= 0 && l < P.nz) atomicAdd(&rho[cell_index(P, t0x - 1 + a, t0y - 1 + bb, ring_plane(l, k0r, P.nz))], v);
+    }
 }
 
 void split_rho(Ctx &c, double *rho, int mask) {
     SplitState &X = SS(c);
-    int cur = c.cur32;
+    const Params &P = c.P;
+    const int cur = c.cur32, lds = 8 * (P.tx + 3) * (P.ty + 3) * (P.tz + 3), per = 4096;
     for (int sp = 0; sp < 2; ++sp) {
         if (!(mask & (1 << sp))) continue;
-        Store &s = X.s[sp];
-        int32_t ovf_n = 0;
-        (void)hipMemcpyAsync(&ovf_n, s.ovf[cur], 4, hipMemcpyDeviceToHost, c.st);
-        (void)hipStreamSynchronize(c.st);
-        ovf_n = (int32_t)std::min<int64_t>(ovf_n, s.ovf_cap);
-        hipLaunchKernelGGL(k_split_rho, dim3(c.P.nbins + 1), dim3(256), 0, c.st, c.P, c.k0, (int)(c.k0 % c.P.nz),
-                           s.buf[cur], s.off[cur], s.cnt[cur], s.bin_slots, ovf_n, c.P.nbins, rho);
+        const Store &s = X.s[sp];
+        // the beam crowds a few bins, the plasma fills them evenly
+        const int parts = sp == 0 ? 16 : 2;
+        hipLaunchKernelGGL(k_split_rho, dim3(P.nbins + 1, parts), dim3(256), lds, c.st, P, c.k0, (int)(c.k0 % P.nz),
+                           s.buf[cur], s.off[cur], s.cnt[cur], s.bin_slots, s.ovf[cur], s.ovf_cap, per, rho);
     }
 }
 
@@ -2037,41 +2115,33 @@ __global__ void k_split_probe(Params P, int64_t k0, Part32 in, const int64_t *of
         for (int j = 0; j < 5; ++j) atomicAdd(&acc[j], s[j][0]);
 }
 
-// lab-frame groups of the binned beam: blocks stride over the bins (and the overflow tail, "bin" nbins)
-__global__ void __launch_bounds__(256) k_split_lab_groups(Params P, LabGroupSpec G, int64_t k0, Part32 in,
-                                                          const int64_t *off, const int32_t *cnt, int64_t ovf_start,
-                                                          const int32_t *ovf, int64_t ovf_cap, double t, double *out) {
+// lab-frame groups of the binned beam: each workgroup a contiguous range of the particles
+__global__ void __launch_bounds__(DT) k_split_lab_groups(Params P, LabGroupSpec G, int64_t k0, Part32 in, BinRanks R,
+                                                         double t, double *out) {
     __shared__ double tab[LAB_GROUP_VALUES * LAB_GROUPS_MAX];
     const int ng = G.nz * G.nu;
     lab_table_clear(tab, ng);
     __syncthreads();
-    for (int b = blockIdx.x; b <= P.nbins; b += gridDim.x) {
-        int64_t s0, n;
-        if (b < P.nbins) {
-            s0 = off[b];
-            n = min((int64_t)cnt[b], off[b + 1] - off[b]);
-        } else {
-            s0 = ovf_start;
-            n = min((int64_t)*ovf, ovf_cap);
-        }
-        for (int64_t j = threadIdx.x; j < n; j += 256) {
-            const int64_t q = s0 + j;
-            int i, jj, l;
-            unpack_cell(P, in.cell[q], i, jj, l);
-            lab_group_add(tab, G, P, t, (i + 0.5) + (double)in.ox[q], (jj + 0.5) + (double)in.oy[q],
-                          ((double)(k0 + l) + 0.5) + (double)in.oz[q], in.ux[q], in.uy[q], in.uz[q], in.w[q]);
-        }
+    int64_t a, end;
+    row_range(R.pref[R.nbins + 1], a, end);
+    int b = a < end ? R.bin(min(a + (int64_t)threadIdx.x, end - 1)) : 0;
+    for (int64_t base = a; base < end; base += DT) {
+        const int64_t s = R.slot(min(base + (int64_t)threadIdx.x, end - 1), b);
+        int i, j, l;
+        unpack_cell(P, in.cell[s], i, j, l);
+        lab_group_add_wave(tab, G, P, t, base + threadIdx.x < end, (i + 0.5) + (double)in.ox[s],
+                           (j + 0.5) + (double)in.oy[s], ((double)(k0 + l) + 0.5) + (double)in.oz[s], in.ux[s],
+                           in.uy[s], in.uz[s], in.w[s]);
     }
     __syncthreads();
     lab_table_flush(tab, ng, out);
 }
 
 void split_lab_groups(Ctx &c, const LabGroupSpec &G, double t, double *out) {
-    SplitState &X = SS(c);
-    const Store &S = X.s[0];
-    const int cur = c.cur32;
-    hipLaunchKernelGGL(k_split_lab_groups, dim3(std::min(c.P.nbins + 1, 1024)), dim3(256), 0, c.st, c.P, G, c.k0,
-                       S.buf[cur], S.off[cur], S.cnt[cur], S.bin_slots, S.ovf[cur], S.ovf_cap, t, out);
+    const Store &S = SS(c).s[0];
+    const BinRanks R = bin_ranks(c, 0);
+    hipLaunchKernelGGL(k_split_lab_groups, dim3(sum_rows(c.beam.n_macro)), dim3(DT), 0, c.st, c.P, G, c.k0,
+                       S.buf[c.cur32], R, t, out);
 }
 
 void split_probe(Ctx &c, double *acc) {
@@ -2081,21 +2151,6 @@ void split_probe(Ctx &c, double *acc) {
     hipLaunchKernelGGL(k_split_probe, dim3(c.P.nbins + 1), dim3(256), 0, c.st, c.P, c.k0, S.buf[cur], S.off[cur],
                        S.cnt[cur], S.bin_slots, S.ovf[cur], S.ovf_cap, (double)c.step * c.P.dt, c.probe_t, c.probe_k,
                        acc);
-}
-
-// plasma count and kinetic energy: one pair of partials per bin (and the overflow tail) into red
-int split_plasma_kinetic_partials(Ctx &c, double *red) {
-    SplitState &X = SS(c);
-    int cur = c.cur32;
-    Store &s = X.s[1];
-    int32_t ovf_n = 0;
-    (void)hipMemcpyAsync(&ovf_n, s.ovf[cur], 4, hipMemcpyDeviceToHost, c.st);
-    (void)hipStreamSynchronize(c.st);
-    ovf_n = (int32_t)std::min<int64_t>(ovf_n, s.ovf_cap);
-    int nblk = c.P.nbins + 1;
-    hipLaunchKernelGGL(k_split_kin, dim3(nblk), dim3(256), 0, c.st, c.P, s.buf[cur], s.off[cur], s.cnt[cur],
-                       s.bin_slots, ovf_n, c.P.nbins, red);
-    return nblk;
 }
 
 }  // namespace pic

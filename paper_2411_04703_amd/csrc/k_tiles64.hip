@@ -405,4 +405,72 @@ void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f) {
         launch_step<Geom3D>(c, S, b, p, f, grid);
 }
 
+// ---------------------------------------------------------------- charge
+// Charge -w of the listed particles on the nodes (mobile ions carry w < 0), summed in an LDS box of the
+// tile's nodes -1 .. T + 1 and added into rho (ring order).  With one thread per particle and 27 global
+// FP64 atomics each, the 1 M particles of the 64x64x256 workload's beam took 3.2 ms.
+template <class G>
+__global__ void __launch_bounds__(ST64) k_rho64(Params P, int k0r, Bounds64 W, Species64 sb, Species64 sp, TileList T,
+                                                double *rho) {
+    __shared__ double box[G::NB];
+    __shared__ int s_item;
+    const uint32_t tid = threadIdx.x;
+    for (int e = tid; e < G::NB; e += ST64) box[e] = 0.0;
+    ItemQueue64 Q;
+    if (tid == 0) s_item = Q.first(T);
+    __syncthreads();
+    int cur = __builtin_amdgcn_readfirstlane(s_item);
+    while (cur >= 0) {
+        const Item64 I = item64(T, cur, G::TX, G::TY, G::TZ);
+        __syncthreads();  // s_item read, box clear
+        if (tid == 0) Q.claim(T);
+        for (uint32_t e = I.begin + tid; e < I.end; e += ST64) {
+            int64_t cap;
+            int32_t *alive;
+            const double *at = slot64(sb, sp, T.list[e], cap, alive);
+            const double X[3] = {at[0], at[cap], at[2 * cap]};
+            double fl[3], w[3][3];
+            int c0[3];
+            for (int d = 0; d < 3; ++d) fl[d] = floor(X[d]);
+            cell_in_tile64(P, W, I, fl, c0);
+            for (int d = 0; d < 3; ++d) c0[d] += near_int(X[d], fl[d], w[d]);
+            const double qw = -at[6 * cap];
+            double *o = box + c0[0] + G::FX * (c0[1] + G::FY * c0[2]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int b = 0; b < 3; ++b)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        atomicAdd(o + a + G::FX * (b + G::FY * c), qw * w[0][a] * w[1][b] * w[2][c]);
+        }
+        if (tid == 0) s_item = Q.resolve(T);
+        __syncthreads();
+        cur = __builtin_amdgcn_readfirstlane(s_item);
+        for (int e = tid; e < G::NB; e += ST64) {
+            const double v = box[e];
+            if (v == 0.0) continue;
+            box[e] = 0.0;
+            const int y = e / G::FX, a = e - y * G::FX, c = y / G::FY, b = y - c * G::FY, l = I.t0z - 1 + c;
+            if (l >= 0 && l < P.nz)
+                atomicAdd(&rho[cell_near(P, I.t0x - 1 + a, I.t0y - 1 + b, ring_plane(l, k0r, P.nz))], v);
+        }
+    }
+}
+
+void rho64(Ctx &c, double *rho, int mask) {
+    const Params &P = c.P;
+    const Species64 b{c.b64.x, std::max<int64_t>(c.cap_b, 1), mask & 1 ? c.nb_slots : 0},
+        p{c.p64.x, std::max<int64_t>(c.cap_p, 1), mask & 2 ? c.np_slots : 0};
+    if (b.n + p.n <= 0) return;
+    const int grid = 4 * c.ncu;  // four workgroups of 512 fill a compute unit
+    tiles64_build(c, b, p, grid);
+    const Bounds64 W(P, c.k0, c.k0);
+    const int k0r = (int)(c.k0 % P.nz);
+    if (tiles64_flat(P))
+        hipLaunchKernelGGL(k_rho64<Geom2D>, dim3(grid), dim3(ST64), 0, c.st, P, k0r, W, b, p, c.tiles, rho);
+    else
+        hipLaunchKernelGGL(k_rho64<Geom3D>, dim3(grid), dim3(ST64), 0, c.st, P, k0r, W, b, p, c.tiles, rho);
+}
+
 }  // namespace pic

@@ -94,7 +94,7 @@ struct Ctx {
     // scratch
     double *red = nullptr;       // reduction partials
     int64_t red_cap = 0;
-    double *rprev = nullptr;     // previous Gauss residual (logical order)
+    double *rprev = nullptr;     // previous Gauss residual (ring order)
     int64_t rprev_k0 = 0;
     int have_rprev = 0;
     double *adj = nullptr;       // adjoint scratch: lEn[3], Bn[3]
@@ -139,6 +139,8 @@ int64_t compact64(Ctx &c, Part64 src, Part64 dst, int64_t n);  // returns surviv
 uint64_t tiles64_bytes(const Params &P, int64_t slots);  // arena bytes of the particle lists
 pic_status tiles64_carve(Ctx &c, char *base, int64_t slots);
 void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f);  // gather, push, move, deposit of both species
+
+void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma (bit 1) added into rho (ring order)
 
 // FP32 split particles (k_split32.hip)
 void split_setup(Ctx &c);
