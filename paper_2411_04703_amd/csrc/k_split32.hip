@@ -32,8 +32,7 @@
 namespace pic {
 
 constexpr int ST = 512;    // threads per workgroup of the auxiliary kernels
-constexpr int SST = 768;   // threads per workgroup of the step kernel (3 waves per SIMD)
-constexpr int CH = 12 * SST;  // particles per work item (bins larger than this are split; measured best of 3-24 x SST)
+constexpr int CH = 9216;   // particles per work item (bins larger than this are split; measured best of 2304 to 18432)
 constexpr int WT = 512;    // threads of the work-list kernels
 constexpr int QPAD = 64;   // int32 stride of the slab queue counters: one 256-byte block each, apart from
                            // everything else (a counter sharing a cache line with the read-only queue
@@ -64,7 +63,7 @@ struct SplitState {
     void (*kern)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, struct IOPair, FieldsT<float>,
                  long long *, long long *, long long *, int32_t *, const double *, const float *,
                  const float *);  // its instantiation (tile, deposit variant)
-    int lds_bytes;
+    int lds_bytes, threads;  // of its workgroup
     SpeciesIO *ios;        // device descriptors: [cur 0][2], [cur 1][2], [flat init][2]
     struct IdIO *iids;     // their record-mode id arrays, same order
     double *tabA;          // undulator phase table of the step, entry l + 1 for logical plane l (nz + 2)
@@ -74,16 +73,6 @@ struct SplitState {
 };
 
 static SplitState &SS(Ctx &c) { return *static_cast<SplitState *>(c.split); }
-
-// LDS of one step-kernel workgroup: E box (T+4)^3 and B box (T+3)^3 in FP32,
-// the three int64 current boxes, the undulator phase table
-int split_lds_bytes(int tx, int ty, int tz) {
-    int nF = (tx + 4) * (ty + 4) * (tz + 4), nE = (tx + 3) * (ty + 3) * (tz + 3);
-    int nJ = (tx + 4) * (ty + 5) * (tz + 5) + (tx + 5) * (ty + 4) * (tz + 5) + (tx + 5) * (ty + 5) * (tz + 4);
-    return ((3 * nF * 4 + 3 * nE * 4 + 15) & ~15) + 8 * nJ + 16 * (tz + 3);
-}
-
-static int lds_bytes_of(const Params &P) { return split_lds_bytes(P.tx, P.ty, P.tz); }
 
 // ---------------------------------------------------------------- helpers
 // The particle and bin arrays are device (global) memory: accessed through
@@ -449,8 +438,11 @@ __device__ inline void esk_setup(const float X0[3], const float X1[3], Esk &e) {
 // 48 of a component that moves along its axis; DEP 2 leaves out the window's
 // last node along an axis (m = 2, a = 3 or b = 3) when no lane of the wave
 // crosses there (wave-uniform branches).  The values visited differ only by
-// zeros, so the integer current sums are the same.
-template <int C, int DEP, bool BIASED, typename F>
+// zeros, so the integer current sums are the same.  ROW (with DEP 2), for a grid
+// of one row along y: the contributions of the window's y nodes all go to that
+// row, so their integers are summed in registers and added once, fn's y offset 0
+// (2048 x 1 x 4096: the step kernel 1.24 -> 1.19 ms).
+template <int C, int DEP, bool BIASED, bool ROW, typename F>
 __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&fn) {
     constexpr int CA = C == 2 ? 0 : C + 1, CB = C == 0 ? 2 : C - 1;
     float Pm[3];
@@ -477,6 +469,27 @@ __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&
     };
     if (DEP == 2) {
         const bool m2 = __any(e.cross & (1 << C)), a3 = __any(e.cross & (1 << CA)), b3 = __any(e.cross & (1 << CB));
+        if constexpr (ROW && C != 1) {  // y is the cross axis a of J_x and b of J_z, o the other one
+            const bool y3 = C == 0 ? a3 : b3, o3 = C == 0 ? b3 : a3;
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                if (o == 3 && !o3) break;
+                long long s[3] = {0, 0, 0};
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    if (y == 3 && !y3) break;
+                    const double A = (double)(C == 0 ? Aab(y, o) : Aab(o, y));
+                    s[0] += to_fixed_as<BIASED>(A, Pd[0]);
+                    s[1] += to_fixed_as<BIASED>(A, Pd[1]);
+                    if (m2) s[2] += to_fixed_as<BIASED>(A, Pd[2]);
+                }
+                const int a = C == 0 ? 0 : o, b = C == 0 ? o : 0;
+                fn(C, 0, a, b, s[0]);
+                fn(C, 1, a, b, s[1]);
+                if (m2) fn(C, 2, a, b, s[2]);
+            }
+            return;
+        }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             if (a == 3 && !a3) break;
@@ -484,6 +497,12 @@ __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&
             for (int b = 0; b < 4; ++b) {
                 if (b == 3 && !b3) break;
                 const double A = (double)Aab(a, b);
+                if constexpr (ROW) {  // J_y: the nodes along the axis
+                    long long s = to_fixed_as<BIASED>(A, Pd[0]) + to_fixed_as<BIASED>(A, Pd[1]);
+                    if (m2) s += to_fixed_as<BIASED>(A, Pd[2]);
+                    fn(C, 0, a, b, s);
+                    continue;
+                }
                 fn(C, 0, a, b, to_fixed_as<BIASED>(A, Pd[0]));
                 fn(C, 1, a, b, to_fixed_as<BIASED>(A, Pd[1]));
                 if (m2) fn(C, 2, a, b, to_fixed_as<BIASED>(A, Pd[2]));
@@ -504,13 +523,13 @@ __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&
         }
 }
 
-template <int DEP, bool BIASED = false, typename F>
+template <int DEP, bool BIASED = false, bool ROW = false, typename F>
 __device__ inline void esk_visit(const Esk &e, double f, double fscale, F &&fn) {
-    esk_component<0, DEP, BIASED>(e, f, fscale, fn);
+    esk_component<0, DEP, BIASED, ROW && DEP == 2>(e, f, fscale, fn);
     __builtin_amdgcn_sched_barrier(0);
-    esk_component<1, DEP, BIASED>(e, f, fscale, fn);
+    esk_component<1, DEP, BIASED, ROW && DEP == 2>(e, f, fscale, fn);
     __builtin_amdgcn_sched_barrier(0);
-    esk_component<2, DEP, BIASED>(e, f, fscale, fn);
+    esk_component<2, DEP, BIASED, ROW && DEP == 2>(e, f, fscale, fn);
 }
 
 // carry new offsets into the cell, apply the window shift; false if the particle left the band.
@@ -689,19 +708,34 @@ __device__ inline bool particle_global(const Params &P, const StepCtx &S, const 
 // ---------------------------------------------------------------- the step kernel
 // Tile TX x TY x TZ cells (compile time, so that every LDS access of the gather
 // and the deposit is one per-particle base address plus an immediate offset),
-// ST threads, 2 waves per SIMD.  DEP selects the deposit variant (esk_component).
+// NT threads.  DEP selects the deposit variant (esk_component).
+//
+// On a two-dimensional x-z grid (tile edge 1 in y) every row along y is the grid's
+// one row: the boxes hold it once, with a y stride of zero, so that the same reads
+// and adds go to it.  16 x 1 x 16 then takes 20 KB of LDS instead of 104, stages a
+// quarter of the field rows and flushes a sixth of the current rows, and two
+// workgroups share a CU, 512 threads each (4 waves per SIMD within 128 VGPRs; the
+// 1024 particles of a tile at four per cell are two rounds): 2.32 -> 1.19 ms a
+// step on 2048 x 1 x 4096 cells with 4.2 M beam and 33.5 M plasma particles.
+// A three-dimensional tile fills a CU with one workgroup: 768 threads, 3 waves
+// per SIMD.
 template <int TX, int TY, int TZ> struct TileGeom {
-    static constexpr int EX = TX + 3, EY = TY + 3, EZ = TZ + 3, NE = EX * EY * EZ;  // B box (t0 - 1 ...)
-    static constexpr int FX = TX + 4, FY = TY + 4, FZ = TZ + 4, NF = FX * FY * FZ;  // E box (t0 - 1 ...), one more
-                                                                                    // node for the curl at B sites
+    static constexpr bool FLAT = TY == 1;
+    static constexpr int EX = TX + 3, EY = FLAT ? 1 : TY + 3, EZ = TZ + 3, NE = EX * EY * EZ;  // B box (t0 - 1 ...)
+    static constexpr int FX = TX + 4, FY = FLAT ? 1 : TY + 4, FZ = TZ + 4, NF = FX * FY * FZ;  // E box (t0 - 1 ...), one
+                                                                                               // more node for the
+                                                                                               // curl at B sites
     // current boxes (origin t0 - 2): along their own axis TX + 4, across TX + 5
-    static constexpr int XX = TX + 4, XY = TY + 5, XZ = TZ + 5;
-    static constexpr int YX = TX + 5, YY = TY + 4, YZ = TZ + 5;
-    static constexpr int ZX = TX + 5, ZY = TY + 5, ZZ = TZ + 4;
+    static constexpr int XX = TX + 4, XY = FLAT ? 1 : TY + 5, XZ = TZ + 5;
+    static constexpr int YX = TX + 5, YY = FLAT ? 1 : TY + 4, YZ = TZ + 5;
+    static constexpr int ZX = TX + 5, ZY = FLAT ? 1 : TY + 5, ZZ = TZ + 4;
     static constexpr int NJX = XX * XY * XZ, NJY = YX * YY * YZ, NJZ = ZX * ZY * ZZ, NJ = NJX + NJY + NJZ;
+    // y strides of the boxes
+    static constexpr int ES = FLAT ? 0 : EX, FS = FLAT ? 0 : FX, XS = FLAT ? 0 : XX, YS = FLAT ? 0 : YX, ZS = FLAT ? 0 : ZX;
     static constexpr int NTAB = TZ + 3;
     static constexpr int EBYTES = (3 * NF * 4 + 3 * NE * 4 + 15) & ~15;
     static constexpr int LDS = EBYTES + 8 * NJ + 16 * NTAB;
+    static constexpr int NT = FLAT ? 512 : 768, WAVES_PER_SIMD = FLAT ? 4 : 3;
 };
 
 template <class G> struct LdsBoxT {
@@ -727,9 +761,10 @@ template <class G> struct LdsBoxT {
     };
     __device__ Node node(int comp, int x, int y, int z) const {
         const LdsPtr L = (LdsPtr)F;
-        return comp < 3 ? Node{L, comp * G::NF + (x + 1) + G::FX * ((y + 1) + G::FY * (z + 1)), G::FX, G::FX * G::FY}
-                        : Node{L, 3 * G::NF + (comp - 3) * G::NE + (x + 1) + G::EX * ((y + 1) + G::EY * (z + 1)),
-                               G::EX, G::EX * G::EY};
+        return comp < 3 ? Node{L, comp * G::NF + (x + 1) + G::FS * (y + 1) + G::FX * G::FY * (z + 1), G::FS,
+                               G::FX * G::FY}
+                        : Node{L, 3 * G::NF + (comp - 3) * G::NE + (x + 1) + G::ES * (y + 1) + G::EX * G::EY * (z + 1),
+                               G::ES, G::EX * G::EY};
     }
 };
 
@@ -778,11 +813,12 @@ struct ItemT {
 };
 
 template <int TX, int TY, int TZ, int DEP, bool REC>
-__global__ void __launch_bounds__(SST, 3) k_split_step(Params P, StepCtx S, const int4 *items, const int32_t *qstart,
+__global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, TZ>::WAVES_PER_SIMD)) k_split_step(Params P, StepCtx S, const int4 *items, const int32_t *qstart,
                                                       int32_t *qnext, int nslab, IOPair iop, FieldsT<float> f,
                                                       long long *Jx, long long *Jy, long long *Jz, int32_t *flags,
                                                       const double *gtabA, const float *gtabC, const float *gtabS) {
     using G = TileGeom<TX, TY, TZ>;
+    constexpr int SST = G::NT;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_item, s_qstart[9];
     const int tid = threadIdx.x;
@@ -845,28 +881,45 @@ __global__ void __launch_bounds__(SST, 3) k_split_step(Params P, StepCtx S, cons
             l = l < 0 ? 0 : (l >= P.nz ? P.nz - 1 : l);  // outside the window: never gathered
             return pl * (uint32_t)ring_plane(l, S.k0r, P.nz);
         };
-        if (tid < NCE) {
-            const int b = tid / G::FX, a = tid - b * G::FX;
-            const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
-#pragma unroll
-            for (int c = 0; c < G::FZ; ++c) {
-                const uint32_t o = col + plane_of(c);
-#pragma unroll
-                for (int qq = 0; qq < 3; ++qq) lds_load(F6[qq] + o, Fs + qq * G::NF + c * NCE + w64);
+        if constexpr (G::FLAT) {
+            // one row: a thread per node of the box (a column's planes would leave the loads to two waves)
+            static_assert(G::NF <= SST && G::NE <= SST, "one node per thread");
+            auto node = [&](int X) -> uint32_t {
+                const int c = tid / X, a = tid - c * X;
+                return near_cell32<true>(P, I.t0x - 1 + a, 0, 0) + plane_of(c);
+            };
+            if (tid < G::NF) {
+                const uint32_t o = node(G::FX);
+                for (int qq = 0; qq < 3; ++qq) lds_load(F6[qq] + o, Fs + qq * G::NF + w64);
             }
+            if (tid < G::NE) {
+                const uint32_t o = node(G::EX);
+                for (int qq = 0; qq < 3; ++qq) lds_load(F6[3 + qq] + o, Bs + qq * G::NE + w64);
+            }
+        } else {
+            if (tid < NCE) {
+                const int b = tid / G::FX, a = tid - b * G::FX;
+                const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
+#pragma unroll
+                for (int c = 0; c < G::FZ; ++c) {
+                    const uint32_t o = col + plane_of(c);
+#pragma unroll
+                    for (int qq = 0; qq < 3; ++qq) lds_load(F6[qq] + o, Fs + qq * G::NF + c * NCE + w64);
+                }
+            }
+            auto stage_b = [&](int u, int c0) {  // B column u; the wave's first lane has column c0
+                const int b = u / G::EX, a = u - b * G::EX;
+                const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
+#pragma unroll
+                for (int c = 0; c < G::EZ; ++c) {
+                    const uint32_t o = col + plane_of(c);
+#pragma unroll
+                    for (int qq = 0; qq < 3; ++qq) lds_load(F6[3 + qq] + o, Bs + qq * G::NE + c * NCB + c0);
+                }
+            };
+            if (tid >= WE && tid - WE < NB1) stage_b(tid - WE, w64 - WE);
+            if (NB2 > 0 && tid < NB2) stage_b(NB1 + tid, NB1 + w64);
         }
-        auto stage_b = [&](int u, int c0) {  // B column u; the wave's first lane has column c0
-            const int b = u / G::EX, a = u - b * G::EX;
-            const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
-#pragma unroll
-            for (int c = 0; c < G::EZ; ++c) {
-                const uint32_t o = col + plane_of(c);
-#pragma unroll
-                for (int qq = 0; qq < 3; ++qq) lds_load(F6[3 + qq] + o, Bs + qq * G::NE + c * NCB + c0);
-            }
-        };
-        if (tid >= WE && tid - WE < NB1) stage_b(tid - WE, w64 - WE);
-        if (NB2 > 0 && tid < NB2) stage_b(NB1 + tid, NB1 + w64);
         static_assert(G::NTAB <= SST, "one table entry per thread");
         if (P.und_kind && tid < G::NTAB) {  // planes t0z - 1 ...: table entries t0z ...
             int k = tid;
@@ -905,7 +958,7 @@ __global__ void __launch_bounds__(SST, 3) k_split_step(Params P, StepCtx S, cons
                 const int bc = k / G::EX, a = k - bc * G::EX, c = bc / G::EY, b = bc - c * G::EY;
                 const float *ex = Fs + a + G::FX * (b + G::FY * c), *ey = ex + G::NF, *ez = ey + G::NF;
                 float B3[3];
-                half_curl_b(ex, ey, ez, 1, G::FX, G::FX * G::FY, I.t0z - 1 + c == P.nz - 1, hb, B3);
+                half_curl_b(ex, ey, ez, 1, G::FS, G::FX * G::FY, I.t0z - 1 + c == P.nz - 1, hb, B3);
                 Bs[k] += B3[0];
                 Bs[G::NE + k] += B3[1];
                 Bs[2 * G::NE + k] += B3[2];
@@ -972,18 +1025,20 @@ __global__ void __launch_bounds__(SST, 3) k_split_step(Params P, StepCtx S, cons
                     // one base index per component, the node offsets are immediates; the values
                     // are added biased (to_fixed_as) and unbiased when the flush reads the sums
                     const int bx = li + e.base[0] + 2, by = lj + e.base[1] + 2, bz = lk + e.base[2] + 2;
-                    const int jb[3] = {bx + G::XX * (by + G::XY * bz), G::NJX + bx + G::YX * (by + G::YY * bz),
-                                       G::NJX + G::NJY + bx + G::ZX * (by + G::ZY * bz)};
-                    esk_visit<DEP, true>(e, fq, P.fscale, [&](int c, int m, int a, int b, long long iv) {
+                    const int jb[3] = {bx + G::XS * by + G::XX * G::XY * bz,
+                                       G::NJX + bx + G::YS * by + G::YX * G::YY * bz,
+                                       G::NJX + G::NJY + bx + G::ZS * by + G::ZX * G::ZY * bz};
+                    auto add = [&](int c, int m, int a, int b, long long iv) {
                         int off;
                         if (c == 0)  // (m, a, b) along (x, y, z)
-                            off = m + G::XX * (a + G::XY * b);
+                            off = m + G::XS * a + G::XX * G::XY * b;
                         else if (c == 1)  // (y, z, x)
-                            off = b + G::YX * (m + G::YY * a);
+                            off = b + G::YS * m + G::YX * G::YY * a;
                         else  // (z, x, y)
-                            off = a + G::ZX * (b + G::ZY * m);
+                            off = a + G::ZS * b + G::ZX * G::ZY * m;
                         atomicAdd((unsigned long long *)&Js[jb[c] + off], (unsigned long long)iv);
-                    });
+                    };
+                    esk_visit<DEP, true, G::FLAT>(e, fq, P.fscale, add);
                 }
                 store_at(IO.out, act, reserve_slot_of(act, tk), ob0, ocap, act ? pack_cell(P, q.i, q.j, q.l) : 0,
                          q.o, q.u, q.w, flags, REC ? iop.id[I.sp].out : nullptr, q.id);
@@ -1011,7 +1066,25 @@ __global__ void __launch_bounds__(SST, 3) k_split_step(Params P, StepCtx S, cons
         // flush nonzero LDS currents (unbiased) with global 64-bit integer atomics, clearing the boxes.
         // Thread t takes columns t and t + SST of the three boxes' (x, y) footprints and walks
         // their planes: a column's global offset is formed once, a plane's is wave-uniform.
-        if (C.bin >= 0) {
+        if constexpr (G::FLAT) {
+            // one row of nodes per box: a thread per node
+            if (C.bin >= 0) {
+                const uint32_t pl = (uint32_t)P.nx;
+                for (int e = tid; e < G::NJ; e += SST) {
+                    const long long sum = Js[e];
+                    if (sum == 0) continue;
+                    Js[e] = 0;
+                    const long long v = unbias48(sum);
+                    const int h = e < G::NJX ? e : e < G::NJX + G::NJY ? e - G::NJX : e - G::NJX - G::NJY;
+                    const int X = e < G::NJX ? G::XX : G::YX, z = h / X, x = h - z * X, l = C.t0z - 2 + z;
+                    if (v == 0 || l < 0 || l >= P.nz) continue;
+                    long long *J = e < G::NJX ? Jx : e < G::NJX + G::NJY ? Jy : Jz;
+                    atomicAdd((unsigned long long *)&J[near_cell32<true>(P, C.t0x - 2 + x, 0, 0) +
+                                                       pl * (uint32_t)ring_plane(l, S.k0r, P.nz)],
+                              (unsigned long long)v);
+                }
+            }
+        } else if (C.bin >= 0) {
             constexpr int CX = G::XX * G::XY, CY = G::YX * G::YY, CZ = G::ZX * G::ZY, NCOL = CX + CY + CZ;
             constexpr int NPMAX = G::XZ > G::ZZ ? G::XZ : G::ZZ;
             static_assert(NCOL <= 2 * SST && G::XZ == G::YZ, "two columns per thread");
@@ -1079,6 +1152,16 @@ static StepKernel step_kernel(int tx, int ty, int tz, int dep, bool rec) {
 }
 
 bool split_tile_supported(int tx, int ty, int tz) { return step_kernel(tx, ty, tz, 0, false) != nullptr; }
+
+// LDS and threads of one workgroup
+static void step_shape(int tx, int ty, int tz, int &lds, int &threads) {
+    lds = threads = 0;
+#define PIC_PICK(a, b, c)                                              \
+    static_assert(TileGeom<a, b, c>::LDS + 256 <= 160 * 1024, "LDS"); \
+    if (tx == a && ty == b && tz == c) lds = TileGeom<a, b, c>::LDS, threads = TileGeom<a, b, c>::NT;
+    PIC_SPLIT_TILES(PIC_PICK)
+#undef PIC_PICK
+}
 
 // overflow tails of the previous step: untiled path, one particle per thread,
 // persistent grid over the tail lengths read on the device
@@ -1319,14 +1402,14 @@ void split_setup(Ctx &c) {
     X->qnext = (int32_t *)(((uintptr_t)(X->tabS + P.nz + 2) + 255) & ~(uintptr_t)255);
     X->qstart = X->qnext + 8 * QPAD;  // its own 256-byte block
     X->nslab = P.ntz % 8 == 0 ? 8 : 1;  // workgroups are dispatched round-robin over the 8 XCDs
-    X->lds_bytes = lds_bytes_of(P);
+    step_shape(P.tx, P.ty, P.tz, X->lds_bytes, X->threads);
     // deposit: option 0 = wave-pruned windows, 1 = whole components, 2 = zero-skipping
     X->kern = step_kernel(P.tx, P.ty, P.tz, c.opt.variant == 0 ? 2 : (c.opt.variant == 1 ? 1 : 0), c.record != 0);
     const void *kern = (const void *)X->kern;
     (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, X->lds_bytes);
     // persistent grid: resident workgroups per CU as registers and LDS allow, or as requested
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, SST, X->lds_bytes) != hipSuccess || per_cu < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, X->threads, X->lds_bytes) != hipSuccess || per_cu < 1)
         per_cu = 1;
     if (c.opt.wg_per_cu > 0) per_cu = std::min(per_cu, c.opt.wg_per_cu);
     int dev = 0, ncu = 256;
@@ -1645,7 +1728,7 @@ void split_step(Ctx &c, const StepCtx &S) {
                            X.tabS);
     timing_end(c, 2, t1);
     hipEvent_t t2 = timing_begin(c);
-    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(SST), X.lds_bytes, c.st, P, S, X.items, X.qstart, X.qnext, X.nslab,
+    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(X.threads), X.lds_bytes, c.st, P, S, X.items, X.qstart, X.qnext, X.nslab,
                        IOPair{{species_io(c, 0, cur, X.s[0].bin_slots), species_io(c, 1, cur, X.s[1].bin_slots)},
                               {species_ids(c, 0, cur), species_ids(c, 1, cur)}},
                        f,

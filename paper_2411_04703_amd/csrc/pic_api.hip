@@ -181,9 +181,6 @@ static pic_status derive_params(const pic_grid *g, const pic_frame *f, const pic
         P.lgx = lg(t[0]);
         P.lgy = lg(t[1]);
         P.lgz = lg(t[2]);
-        // LDS of one workgroup: staged E, B (+halo) in FP32, int64 current boxes, field table
-        if (split_lds_bytes(t[0], t[1], t[2]) > 160 * 1024)
-            return fail(err, PIC_EINVAL, "options: tile too large for 160 KiB of LDS");
         P.tx = t[0];
         P.ty = t[1];
         P.tz = t[2];

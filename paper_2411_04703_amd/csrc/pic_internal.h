@@ -145,7 +145,6 @@ void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma
 // FP32 split particles (k_split32.hip)
 void split_setup(Ctx &c);
 bool split_tile_supported(int tx, int ty, int tz);  // tiles the FP32 step kernel is built for
-int split_lds_bytes(int tx, int ty, int tz);         // LDS of one FP32 step-kernel workgroup
 uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint64_t bins_bytes, int record);
 void split_export64(const Ctx &c, Part64 beam, Part64 plasma, hipStream_t st);  // record mode: particles to slots
 pic_status split_copy_state(Ctx &c, char *dev, bool save);  // snapshot <-> context (device buffer)
