@@ -32,7 +32,7 @@
 namespace pic {
 
 constexpr int ST = 512;    // threads per workgroup of the auxiliary kernels
-constexpr int CH = 9216;   // particles per work item (bins larger than this are split; measured best of 2304 to 18432)
+constexpr int CH = 9216;   // most particles of a work item (split_chunk)
 constexpr int WT = 512;    // threads of the work-list kernels
 constexpr int QPAD = 64;   // int32 stride of the slab queue counters: one 256-byte block each, apart from
                            // everything else (a counter sharing a cache line with the read-only queue
@@ -56,11 +56,12 @@ struct SplitState {
     int4 *items;
     int32_t *nitems, *next;
     int64_t items_cap;
+    int chunk;             // particles per work item (split_chunk)
     int64_t *scan_part;
     int32_t *tmpcnt;       // 2 x nbins
     int64_t *tmpoff;       // nbins + 2: a store's BinRanks
     int grid;              // persistent grid of the step kernel
-    void (*kern)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, struct IOPair, FieldsT<float>,
+    void (*kern)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, int, struct IOPair, FieldsT<float>,
                  long long *, long long *, long long *, int32_t *, const double *, const float *,
                  const float *);  // its instantiation (tile, deposit variant)
     int lds_bytes, threads;  // of its workgroup
@@ -814,7 +815,7 @@ struct ItemT {
 
 template <int TX, int TY, int TZ, int DEP, bool REC>
 __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, TZ>::WAVES_PER_SIMD)) k_split_step(Params P, StepCtx S, const int4 *items, const int32_t *qstart,
-                                                      int32_t *qnext, int nslab, IOPair iop, FieldsT<float> f,
+                                                      int32_t *qnext, int nslab, int chunk, IOPair iop, FieldsT<float> f,
                                                       long long *Jx, long long *Jy, long long *Jz, int32_t *flags,
                                                       const double *gtabA, const float *gtabC, const float *gtabS) {
     using G = TileGeom<TX, TY, TZ>;
@@ -854,7 +855,7 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
         I.bin = __builtin_amdgcn_readfirstlane(it.y);
         I.start = __builtin_amdgcn_readfirstlane(it.z);
         const int cnt = __builtin_amdgcn_readfirstlane(it.w);
-        I.end = min(cnt, I.start + CH);
+        I.end = min(cnt, I.start + chunk);
         const int bin = I.bin < 0 ? 0 : I.bin;
         I.t0x = (bin % P.ntx) * TX;
         I.t0y = ((bin / P.ntx) % P.nty) * TY;
@@ -1134,7 +1135,7 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
 // the tiles the step kernel is instantiated for
 #define PIC_SPLIT_TILES(X) X(8, 8, 4) X(8, 8, 8) X(8, 8, 16) X(16, 8, 4) X(16, 16, 4) X(16, 8, 8) X(16, 1, 16)
 
-using StepKernel = void (*)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, IOPair,
+using StepKernel = void (*)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, int, IOPair,
                             FieldsT<float>, long long *, long long *, long long *, int32_t *, const double *,
                             const float *, const float *);
 
@@ -1163,6 +1164,20 @@ static void step_shape(int tx, int ty, int tz, int &lds, int &threads) {
 #undef PIC_PICK
 }
 
+// Particles per work item for n particles in all: whole rounds of the workgroup, at most CH.  A bin
+// of more is shared out, which costs each part a staging and a flush of the tile (about 3 us; with
+// every bin of 2048 in parts of 768, 128 x 128 x 512 takes 1.92 ms for 1.21).  Where the step is a
+// few rounds a workgroup, the parts of the largest bins decide how long it is: 64 x 64 x 256 with a
+// beam of a million takes 308 us in parts of 9216, 232 of 4608, 229 of 2304, 279 of 1536; 24 x 40 x
+// 64 44 us in parts of 2304, 27 of 768; 32 x 32 x 64 with 16384 particles 35 us of 1536, 25 of 768.
+// A quarter of what a workgroup of the 256 CUs has to do gives 2304, 768 and 768 there.
+int split_chunk(const Params &P, int64_t n) {
+    int lds, threads;
+    step_shape(P.tx, P.ty, P.tz, lds, threads);
+    const int64_t wgs = P.ty == 1 ? 512 : 256;
+    return threads * (int)std::min<int64_t>(std::max<int64_t>(n / (4 * wgs * threads), 1), CH / threads);
+}
+
 // overflow tails of the previous step: untiled path, one particle per thread,
 // persistent grid over the tail lengths read on the device
 __global__ void __launch_bounds__(256) k_split_overflow(Params P, StepCtx S, const SpeciesIO *ios, const IdIO *iids,
@@ -1187,7 +1202,7 @@ __global__ void __launch_bounds__(256) k_split_overflow(Params P, StepCtx S, con
 }
 
 // ---------------------------------------------------------------- rebin (no physics)
-__global__ void __launch_bounds__(ST) k_rebin(Params P, const int4 *items, const int32_t *nitems, int32_t *next,
+__global__ void __launch_bounds__(ST) k_rebin(Params P, int chunk, const int4 *items, const int32_t *nitems, int32_t *next,
                                               const SpeciesIO *ios, const IdIO *iids, int32_t *flags) {
     __shared__ int s_item;
     const int tid = threadIdx.x;
@@ -1202,7 +1217,7 @@ __global__ void __launch_bounds__(ST) k_rebin(Params P, const int4 *items, const
         const SpeciesIO &IO = ios[it.x];
         const int bin = it.y, start = it.z, cnt = it.w;
         const int64_t b0 = bin < 0 ? IO.in_ovf_start : IO.in_off[bin];
-        const int end = min(cnt, start + CH);
+        const int end = min(cnt, start + chunk);
         for (int base = start; base < end; base += ST) {
             int k = base + tid;
             bool act = k < end;
@@ -1215,11 +1230,11 @@ __global__ void __launch_bounds__(ST) k_rebin(Params P, const int4 *items, const
 }
 
 // ---------------------------------------------------------------- work list
-// items (species, bin, first particle, bin count) for every CH-chunk of every
+// items (species, bin, first particle, bin count) for every chunk of every
 // non-empty bin of the input buffer, then the overflow tails (bin = -1).
 // Three kernels: per-block item counts, single-thread scan of the block
 // totals, per-block writes.  They also clear the output counters.
-__device__ inline int items_of(int n) { return (n + CH - 1) / CH; }
+__device__ inline int items_of(int n, int chunk) { return (n + chunk - 1) / chunk; }
 
 // Work-list entry e (0 <= e < 2 nbins) in slab-major order: the bins form
 // nslab slabs of whole z layers (bins are numbered z-major), and within a slab
@@ -1231,14 +1246,14 @@ __device__ inline void entry_of(int e, int nbins, int nslab, int &sp, int &bin) 
 }
 
 __global__ void k_wl_count(const int64_t *off0, const int32_t *cnt0, const int64_t *off1, const int32_t *cnt1,
-                           int nbins, int nslab, int64_t *part) {
+                           int nbins, int nslab, int chunk, int64_t *part) {
     __shared__ int64_t s[WT];
     int e = blockIdx.x * WT + threadIdx.x;
     int v = 0;
     if (e < 2 * nbins) {
         int sp, bin;
         entry_of(e, nbins, nslab, sp, bin);
-        v = items_of(sp ? bin_count(off1, cnt1, bin) : bin_count(off0, cnt0, bin));
+        v = items_of(sp ? bin_count(off1, cnt1, bin) : bin_count(off0, cnt0, bin), chunk);
     }
     s[threadIdx.x] = v;
     __syncthreads();
@@ -1251,7 +1266,7 @@ __global__ void k_wl_count(const int64_t *off0, const int32_t *cnt0, const int64
 
 __global__ void k_wl_scan(int64_t *part, int nblk, const int32_t *ovf0, int64_t ocap0, const int32_t *ovf1,
                           int64_t ocap1, int32_t *nitems, int32_t *next, int4 *items, int64_t items_cap,
-                          int32_t *clr0, int32_t *clr1, int32_t *qnext, int32_t *qstart, int nslab) {
+                          int32_t *clr0, int32_t *clr1, int32_t *qnext, int32_t *qstart, int nslab, int chunk) {
     if (threadIdx.x != 0) return;
     int64_t acc = 0;
     for (int b = 0; b < nblk; ++b) {
@@ -1262,8 +1277,8 @@ __global__ void k_wl_scan(int64_t *part, int nblk, const int32_t *ovf0, int64_t 
     for (int q = 0; q < nslab; ++q) qnext[q * QPAD] = 0;
     qstart[nslab] = (int32_t)min(acc, items_cap);  // the slab queues end before the overflow items
     int o0 = (int)min((int64_t)*ovf0, ocap0), o1 = (int)min((int64_t)*ovf1, ocap1);
-    for (int k = 0; k < items_of(o0) && acc < items_cap; ++k) items[acc++] = make_int4(0, -1, k * CH, o0);
-    for (int k = 0; k < items_of(o1) && acc < items_cap; ++k) items[acc++] = make_int4(1, -1, k * CH, o1);
+    for (int k = 0; k < items_of(o0, chunk) && acc < items_cap; ++k) items[acc++] = make_int4(0, -1, k * chunk, o0);
+    for (int k = 0; k < items_of(o1, chunk) && acc < items_cap; ++k) items[acc++] = make_int4(1, -1, k * chunk, o1);
     *nitems = (int32_t)min(acc, items_cap);
     *next = 0;
     *clr0 = 0;
@@ -1271,7 +1286,7 @@ __global__ void k_wl_scan(int64_t *part, int nblk, const int32_t *ovf0, int64_t 
 }
 
 __global__ void k_wl_write(const int64_t *off0, const int32_t *cnt0, const int64_t *off1, const int32_t *cnt1,
-                           int nbins, int nslab, const int64_t *part, int4 *items, int64_t items_cap, int32_t *zero0,
+                           int nbins, int nslab, int chunk, const int64_t *part, int4 *items, int64_t items_cap, int32_t *zero0,
                            int32_t *zero1, int32_t *qstart) {
     __shared__ int64_t s[WT];
     int e = blockIdx.x * WT + threadIdx.x;
@@ -1280,7 +1295,7 @@ __global__ void k_wl_write(const int64_t *off0, const int32_t *cnt0, const int64
         entry_of(e, nbins, nslab, sp, bin);
         c = sp ? bin_count(off1, cnt1, bin) : bin_count(off0, cnt0, bin);
     }
-    v = items_of(c);
+    v = items_of(c, chunk);
     s[threadIdx.x] = v;
     __syncthreads();
     for (int k = 1; k < WT; k <<= 1) {  // inclusive scan in the block
@@ -1291,7 +1306,7 @@ __global__ void k_wl_write(const int64_t *off0, const int32_t *cnt0, const int64
     }
     int64_t o = part[blockIdx.x] + s[threadIdx.x] - v;
     for (int k = 0; k < v; ++k)
-        if (o + k < items_cap) items[o + k] = make_int4(sp, bin, k * CH, c);
+        if (o + k < items_cap) items[o + k] = make_int4(sp, bin, k * chunk, c);
     if (e < 2 * nbins) {
         if (sp) zero1[bin] = 0;
         else zero0[bin] = 0;
@@ -1308,11 +1323,11 @@ static void build_worklist(Ctx &c, int cur, int64_t in_cap0, int64_t in_cap1) {
     int o = cur ^ 1;
     Store &b = X.s[0], &p = X.s[1];
     hipLaunchKernelGGL(k_wl_count, dim3(nblk), dim3(WT), 0, c.st, b.off[cur], b.cnt[cur], p.off[cur], p.cnt[cur], nb,
-                       X.nslab, X.scan_part);
+                       X.nslab, X.chunk, X.scan_part);
     hipLaunchKernelGGL(k_wl_scan, dim3(1), dim3(64), 0, c.st, X.scan_part, nblk, b.ovf[cur], in_cap0, p.ovf[cur],
-                       in_cap1, X.nitems, X.next, X.items, X.items_cap, b.ovf[o], p.ovf[o], X.qnext, X.qstart, X.nslab);
+                       in_cap1, X.nitems, X.next, X.items, X.items_cap, b.ovf[o], p.ovf[o], X.qnext, X.qstart, X.nslab, X.chunk);
     hipLaunchKernelGGL(k_wl_write, dim3(nblk), dim3(WT), 0, c.st, b.off[cur], b.cnt[cur], p.off[cur], p.cnt[cur], nb,
-                       X.nslab, X.scan_part, X.items, X.items_cap, b.cnt[o], p.cnt[o], X.qstart);
+                       X.nslab, X.chunk, X.scan_part, X.items, X.items_cap, b.cnt[o], p.cnt[o], X.qstart);
 }
 
 static IdIO species_ids(Ctx &c, int sp, int cur) {
@@ -1390,6 +1405,7 @@ void split_setup(Ctx &c) {
     X->next = ovfs + 5;
     char *wl = A + c.split_off_wl;
     X->items_cap = c.split_items_cap;
+    X->chunk = c.split_chunk;
     X->items = (int4 *)wl;
     X->scan_part = (int64_t *)(wl + 16 * (uint64_t)X->items_cap);
     X->tmpcnt = (int32_t *)(X->scan_part + nblocks(2 * nb, WT) + 8);
@@ -1635,7 +1651,7 @@ static pic_status bins_from_flat(Ctx &c) {
     }
     // the flat lists are read as overflow tails that start at slot 0 and may fill the whole buffer
     build_worklist(c, 1, X.s[0].bin_slots + X.s[0].ovf_cap, X.s[1].bin_slots + X.s[1].ovf_cap);
-    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.items, X.nitems, X.next, X.ios + 4, X.iids + 4,
+    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.chunk, X.items, X.nitems, X.next, X.ios + 4, X.iids + 4,
                        c.dflags);
     for (int sp = 0; sp < 2; ++sp) PIC_HIP(c, hipMemsetAsync(X.s[sp].ovf[1], 0, 4, c.st));
     c.cur32 = 0;
@@ -1728,7 +1744,7 @@ void split_step(Ctx &c, const StepCtx &S) {
                            X.tabS);
     timing_end(c, 2, t1);
     hipEvent_t t2 = timing_begin(c);
-    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(X.threads), X.lds_bytes, c.st, P, S, X.items, X.qstart, X.qnext, X.nslab,
+    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(X.threads), X.lds_bytes, c.st, P, S, X.items, X.qstart, X.qnext, X.nslab, X.chunk,
                        IOPair{{species_io(c, 0, cur, X.s[0].bin_slots), species_io(c, 1, cur, X.s[1].bin_slots)},
                               {species_ids(c, 0, cur), species_ids(c, 1, cur)}},
                        f,
@@ -1905,7 +1921,7 @@ pic_status split_check(Ctx &c) {
         if (s != PIC_OK) return s;
     }
     build_worklist(c, cur, X.s[0].ovf_cap, X.s[1].ovf_cap);
-    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.items, X.nitems, X.next, X.ios + 2 * cur,
+    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.chunk, X.items, X.nitems, X.next, X.ios + 2 * cur,
                        X.iids + 2 * cur, c.dflags);
     for (int sp = 0; sp < 2; ++sp) {
         pic_status s = upload_layout(c, sp, lay[sp], cur);

@@ -36,6 +36,7 @@ struct Plan {
     pic_derived d;
     int precision, record, check_every;
     int64_t cap_b, cap_p, ovf_b, ovf_p;
+    int chunk;
     uint64_t off[40];
     uint64_t arena, state;
 };
@@ -266,7 +267,8 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         off[12] = take(sb * (uint64_t)(cp + pl.ovf_p) * 2);
         uint64_t bins_bytes = 8 * (uint64_t)(nbins + 1) * 4 + 4 * (uint64_t)nbins * 4 + 256;
         off[13] = take(bins_bytes);
-        int64_t items_cap = (cb + cp + pl.ovf_b + pl.ovf_p) / 4096 + 2 * nbins + 64;
+        pl.chunk = split_chunk(P, pl.cap_b + pl.cap_p);
+        int64_t items_cap = (cb + cp + pl.ovf_b + pl.ovf_p) / pl.chunk + 2 * nbins + 64;
         uint64_t wl_bytes = 16 * (uint64_t)(P.nz + 8) + 256 + 16 * (uint64_t)items_cap + 8 * (uint64_t)((2 * nbins) / 512 + 16) +
                             4 * (uint64_t)(2 * nbins + 8) + 8 * (uint64_t)(nbins + 8) + 4096 + 4096;
         off[14] = take(wl_bytes);
@@ -652,6 +654,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->split_bins_bytes = off[23];
         c->split_off_wl = off[14];
         c->split_items_cap = (int64_t)off[24];
+        c->split_chunk = pl.chunk;
         c->nb_slots = b->n_macro;  // ids: beam particle k is FP64 record slot k; plasma ids count up
         c->np_slots = 0;
         split_setup(*c);

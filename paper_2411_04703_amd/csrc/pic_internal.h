@@ -89,6 +89,7 @@ struct Ctx {
     // FP32 split mode: host-side state of the binned stores (k_split32.hip)
     void *split = nullptr;
     int64_t split_slots_b = 0, split_slots_p = 0, split_items_cap = 0;
+    int split_chunk = 0;
     uint64_t split_off_b = 0, split_off_p = 0, split_off_bins = 0, split_bins_bytes = 0, split_off_wl = 0;
 
     // scratch
@@ -145,6 +146,7 @@ void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma
 // FP32 split particles (k_split32.hip)
 void split_setup(Ctx &c);
 bool split_tile_supported(int tx, int ty, int tz);  // tiles the FP32 step kernel is built for
+int split_chunk(const Params &P, int64_t n);         // particles per work item of the FP32 step
 uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint64_t bins_bytes, int record);
 void split_export64(const Ctx &c, Part64 beam, Part64 plasma, hipStream_t st);  // record mode: particles to slots
 pic_status split_copy_state(Ctx &c, char *dev, bool save);  // snapshot <-> context (device buffer)
