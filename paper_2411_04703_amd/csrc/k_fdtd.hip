@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, FieldsT<T> f
         f.E[1][o] += dt * ((bx - Bx[ol]) - (bz - Bz[oi]) - (T)jy);
     }
     if (l != P.nz - 1) {
-        double jt = jz + jvalue<JT>(jion[l], P.finv);
+        double jt = jz + (jion ? jvalue<JT>(jion[l], P.finv) : 0.0);
         f.E[2][o] += dt * ((by - By[oi]) - (bx - Bx[oj]) - (T)jt);
     }
 }
@@ -93,12 +93,12 @@ __global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, FieldsT<T> f
 // since a static-face Mur condition at a face that jumps forward every step or
 // two is unstable with plasma streaming in.  When the window shifts after this
 // step, the back plane becomes the new (empty) front plane instead: E and B
-// there are zeroed.  Also clears the ion current profile for the next step.
+// there are zeroed.  Also clears the ion current profile for the next step (where there is one to clear).
 template <typename T, typename JT>
 __global__ void k_mur_shift(Params P, int k0r, int shift, int front_mur, FieldsT<T> f, const T *murbuf, JT *jion,
                             T cm) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < P.nz) jion[s] = JT(0);
+    if (jion && s < P.nz) jion[s] = JT(0);
     if (s >= P.plane) return;
     int64_t pl = P.plane;
     int p0 = k0r, p1 = ring_plane(1, k0r, P.nz), pm = ring_plane(P.nz - 2, k0r, P.nz),
@@ -116,6 +116,89 @@ __global__ void k_mur_shift(Params P, int k0r, int shift, int front_mur, FieldsT
             f.B[c][p0 * pl + s] = T(0);
         }
     }
+}
+
+// The field part of an FP32 step in one pass: B by a full step (B^(n-1/2) -> B^(n+1/2), what k_bhalf
+// does with h = dt), E by a step with the new B and the currents, the Mur faces and the shift (as
+// k_eupdate and k_mur_shift), from the fields `f` into `g`.  A thread forms the new B of its cell and
+// the six components of it that E needs from the neighbours before it (loads that hit in L1), so that
+// nothing waits for a whole pass over B; the old fields stay as they are, which is why `g` is a second
+// set.  The threads of planes 1 and nz - 2 hold what the Mur faces beside them need and write those.
+// The currents are cleared where they are not zero.
+// Bound: HBM, 96 bytes a cell for 120 in two passes.  Workgroups go round the 8 XCDs, so that workgroup
+// k works on block k / 8 of the (k mod 8)th eighth of the planes and neighbours share an L2.
+template <typename T, typename JT>
+__global__ void __launch_bounds__(256) k_fields(Params P, int k0r, int shift, int front_mur, int nbx, FieldsT<T> f,
+                                                FieldsT<T> g, JT *Jx, JT *Jy, JT *Jz, const JT *jion, T dt, T cm) {
+    uint32_t w = blockIdx.x;
+    if (gridDim.x % 8 == 0) w = (w % 8) * (gridDim.x / 8) + w / 8;
+    const int p = (int)(w / (uint32_t)nbx), s = (int)(w % (uint32_t)nbx) * 256 + (int)threadIdx.x;
+    if (s >= P.plane) return;
+    const int j = s / P.nx, i = s - j * P.nx;
+    int l = p - k0r;
+    if (l < 0) l += P.nz;
+    const uint32_t pl = (uint32_t)P.plane;
+    const uint32_t x0 = (uint32_t)i, xp = i + 1 == P.nx ? 0 : x0 + 1, xm = i == 0 ? P.nx - 1 : x0 - 1;
+    const uint32_t y0 = (uint32_t)(j * P.nx), yp = j + 1 == P.ny ? 0 : y0 + P.nx, ym = j == 0 ? (P.ny - 1) * P.nx : y0 - P.nx;
+    const uint32_t z0 = pl * (uint32_t)p, zp = p + 1 == P.nz ? 0 : z0 + pl, zm = p == 0 ? pl * (P.nz - 1) : z0 - pl;
+    const T *Ex = f.E[0], *Ey = f.E[1], *Ez = f.E[2], *Bx = f.B[0], *By = f.B[1], *Bz = f.B[2];
+    const uint32_t o = x0 + y0 + z0, oxm = xm + y0 + z0, oym = x0 + ym + z0, ozm = x0 + y0 + zm;
+    const bool top = l == P.nz - 1;
+    auto step_b = [&](T b, T d1, T d2) { return fma(-dt, d1 - d2, b); };
+    const T ex = Ex[o], ey = Ey[o], ez = Ez[o];
+    T bx = Bx[o], by = By[o], bz = Bz[o];
+    if (!top) {
+        const uint32_t ozp = x0 + y0 + zp;
+        bx = step_b(bx, Ez[x0 + yp + z0] - ez, Ey[ozp] - ey);
+        by = step_b(by, Ex[ozp] - ex, Ez[xp + y0 + z0] - ez);
+    }
+    bz = step_b(bz, Ey[xp + y0 + z0] - ey, Ex[x0 + yp + z0] - ex);
+    const JT ix = Jx[o], iy = Jy[o], iz = Jz[o];
+    if (ix != JT(0)) Jx[o] = JT(0);
+    if (iy != JT(0)) Jy[o] = JT(0);
+    if (iz != JT(0)) Jz[o] = JT(0);
+    T nx = ex, ny = ey, nz = ez;
+    if (!top) {
+        const T exm = Ex[oxm], ezm = Ez[oxm], eyn = Ey[oym], ezn = Ez[oym];  // at i - 1, at j - 1
+        const T byx = step_b(By[oxm], Ex[xm + y0 + zp] - exm, ez - ezm);
+        const T bxy = step_b(Bx[oym], ez - ezn, Ey[x0 + ym + zp] - eyn);
+        if (l != 0) {
+            const T exn = Ex[oym], eym = Ey[oxm], exz = Ex[ozm], eyz = Ey[ozm], ezz = Ez[ozm];
+            const T bzx = step_b(Bz[oxm], ey - eym, Ex[xm + yp + z0] - exm);
+            const T bzy = step_b(Bz[oym], Ey[xp + ym + z0] - eyn, ex - exn);
+            const T bxz = step_b(Bx[ozm], Ez[x0 + yp + zm] - ezz, ey - eyz);
+            const T byz = step_b(By[ozm], ex - exz, Ez[xp + y0 + zm] - ezz);
+            nx = fma(dt, (bz - bzy) - (by - byz) - (T)jvalue<JT>(ix, P.finv), ex);
+            ny = fma(dt, (bx - bxz) - (bz - bzx) - (T)jvalue<JT>(iy, P.finv), ey);
+            if (l == 1 && !shift) {
+                g.E[0][ozm] = fma(cm, nx - exz, ex);
+                g.E[1][ozm] = fma(cm, ny - eyz, ey);
+            }
+            if (l == P.nz - 2 && front_mur) {
+                g.E[0][x0 + y0 + zp] = fma(cm, nx - Ex[x0 + y0 + zp], ex);
+                g.E[1][x0 + y0 + zp] = fma(cm, ny - Ey[x0 + y0 + zp], ey);
+            }
+        }
+        const double jt = jvalue<JT>(iz, P.finv) + (jion ? jvalue<JT>(jion[l], P.finv) : 0.0);
+        nz = fma(dt, (by - byx) - (bx - bxy) - (T)jt, ez);
+    }
+    if (l == 0 && shift) nx = ny = nz = bx = by = bz = T(0);  // the new front plane enters empty
+    if (!(l == 0 && !shift) && !(top && front_mur)) {
+        g.E[0][o] = nx;
+        g.E[1][o] = ny;
+    }
+    g.E[2][o] = nz;
+    g.B[0][o] = bx;
+    g.B[1][o] = by;
+    g.B[2][o] = bz;
+}
+
+void launch_fields32(const Params &P, int k0r, int shift, int front_mur, FieldsT<float> f, FieldsT<float> g,
+                     long long *J[3], const long long *jion, float dt, hipStream_t st) {
+    const int nbx = nblocks(P.plane, 256);
+    const float cm = (dt - 1.0f) / (dt + 1.0f);
+    hipLaunchKernelGGL((k_fields<float, long long>), dim3((unsigned)(nbx * P.nz)), dim3(256), 0, st, P, k0r, shift,
+                       front_mur, nbx, f, g, J[0], J[1], J[2], jion, dt, cm);
 }
 
 template <typename T>
@@ -181,9 +264,11 @@ __global__ void k_ion64(Params P, int64_t sh_lo, int64_t ns, double t0, double t
         if (v[m] != 0.0 && lb + m >= 0 && lb + m < P.nz) atomicAdd(&jion[lb + m], v[m]);
 }
 
+// FP32 mode; next: the profile of the following step, cleared
 __global__ void k_ion_fixed(Params P, int64_t sh_lo, int64_t ns, double t0, double t1, int64_t k0, long long *jion,
-                            int32_t *flags) {
+                            long long *next, int32_t *flags) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < P.nz) next[q] = 0;
     if (q >= ns) return;
     double v[4];
     int lb;
@@ -204,9 +289,9 @@ void launch_ion64(const Params &P, int64_t sh_lo, int64_t ns, double t0, double 
 }
 
 void launch_ion_fixed(const Params &P, int64_t sh_lo, int64_t ns, double t0, double t1, int64_t k0,
-                      long long *jion, int32_t *flags, hipStream_t st) {
-    if (ns <= 0) return;
-    hipLaunchKernelGGL(k_ion_fixed, dim3(nblocks(ns, 128)), dim3(128), 0, st, P, sh_lo, ns, t0, t1, k0, jion, flags);
+                      long long *jion, long long *next, int32_t *flags, hipStream_t st) {
+    hipLaunchKernelGGL(k_ion_fixed, dim3(nblocks(std::max<int64_t>(ns, P.nz), 128)), dim3(128), 0, st, P, sh_lo, ns,
+                       t0, t1, k0, jion, next, flags);
 }
 
 }  // namespace pic

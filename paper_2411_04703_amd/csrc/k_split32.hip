@@ -49,28 +49,35 @@ struct Store {
     int64_t n_flat;        // init only
 };
 
+// The work list of a step: items (species, bin, first particle, bin count), one for every chunk of every
+// non-empty bin of the input buffer.  The bins form nslab slabs of whole z layers (one per XCD when they
+// divide evenly; bins are numbered z-major); queue 2 s + species holds slab s's items of a species, in
+// a region of its own, count[q] of them.
+struct WorkList {
+    int4 *items;
+    int32_t *count, *count_next;  // count_next: the following list's, cleared when this one is built
+    int32_t *next;                // claimed items of each queue (stride QPAD)
+    int nslab, chunk, cap[2];     // cap: most items of a queue, by species
+    __device__ int base(int q) const { return (q >> 1) * (cap[0] + cap[1]) + (q & 1 ? cap[0] : 0); }
+};
+
 struct SpeciesIO;
 
 struct SplitState {
     Store s[2];            // 0 beam, 1 plasma
-    int4 *items;
-    int32_t *nitems, *next;
-    int64_t items_cap;
-    int chunk;             // particles per work item (split_chunk)
-    int64_t *scan_part;
+    WorkList work;         // of the next step
+    int32_t *qcount[2];    // its item counts and the following list's, alternately
     int32_t *tmpcnt;       // 2 x nbins
     int64_t *tmpoff;       // nbins + 2: a store's BinRanks
     int grid;              // persistent grid of the step kernel
-    void (*kern)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, int, struct IOPair, FieldsT<float>,
-                 long long *, long long *, long long *, int32_t *, const double *, const float *,
+    void (*kern)(Params, StepCtx, WorkList, struct IOPair, FieldsT<float>, long long *, long long *, long long *,
+                 int32_t *, const double *, const float *,
                  const float *);  // its instantiation (tile, deposit variant)
     int lds_bytes, threads;  // of its workgroup
     SpeciesIO *ios;        // device descriptors: [cur 0][2], [cur 1][2], [flat init][2]
     struct IdIO *iids;     // their record-mode id arrays, same order
     double *tabA;          // undulator phase table of the step, entry l + 1 for logical plane l (nz + 2)
     float *tabC, *tabS;
-    int nslab;             // work queues: slabs of whole bin layers (one per XCD when they divide evenly)
-    int32_t *qnext, *qstart;  // per-slab item counters (stride QPAD); slab q's items are [qstart[q], qstart[q + 1])
 };
 
 static SplitState &SS(Ctx &c) { return *static_cast<SplitState *>(c.split); }
@@ -342,11 +349,6 @@ __device__ inline void ext_plane(const Params &P, int64_t k0, int l, double t, d
 }
 
 // per step: ext_plane of every logical plane -1 .. nz (entry l + 1)
-__global__ void k_ext_table(Params P, StepCtx S, double *tabA, float *tabC, float *tabS) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < P.nz + 2) ext_plane(P, S.k0, e - 1, S.t, tabA[e], tabC[e], tabS[e]);
-}
-
 __device__ inline void ext32(const Params &P, double a_l, float cphi, float sphi, float oz, float E[3], float B[3]) {
     double a = a_l + P.gR * (double)oz;
     double env, denv;
@@ -814,16 +816,15 @@ struct ItemT {
 };
 
 template <int TX, int TY, int TZ, int DEP, bool REC>
-__global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, TZ>::WAVES_PER_SIMD)) k_split_step(Params P, StepCtx S, const int4 *items, const int32_t *qstart,
-                                                      int32_t *qnext, int nslab, int chunk, IOPair iop, FieldsT<float> f,
-                                                      long long *Jx, long long *Jy, long long *Jz, int32_t *flags,
-                                                      const double *gtabA, const float *gtabC, const float *gtabS) {
+__global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, TZ>::WAVES_PER_SIMD))
+k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long long *Jx, long long *Jy, long long *Jz,
+             int32_t *flags, const double *gtabA, const float *gtabC, const float *gtabS) {
     using G = TileGeom<TX, TY, TZ>;
     constexpr int SST = G::NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_item, s_qstart[9];
-    const int tid = threadIdx.x;
-    if (tid <= nslab) s_qstart[tid] = qstart[tid];  // constant during the launch
+    __shared__ int s_item, s_count[16];
+    const int tid = threadIdx.x, nq = 2 * W.nslab;
+    if (tid < nq) s_count[tid] = W.count[tid];  // constant during the launch
     float *Fs = (float *)smem;
     float *Bs = Fs + 3 * G::NF;
     long long *Js = (long long *)(smem + G::EBYTES);
@@ -834,33 +835,33 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
     for (int k = tid; k < G::NJ; k += SST) Js[k] = 0;  // cleared once; every flush clears what it reads
     __syncthreads();
 
-    // Work queues: one per z slab of bins; this workgroup's XCD's slab first, then the others'
-    // (work stealing).  Thread 0 keeps one claim on queue q in flight: the counter value for
-    // the item after the current one, claimed when the current one starts and resolved when it
-    // ends, so the atomic's round trip is hidden behind the item's work.
-    int q = (int)(blockIdx.x % (unsigned)nslab), hops = 0, claim = 0;
+    // Work queues: a slab's beam, whose large bins take longest, then its plasma; this workgroup's
+    // XCD's slab first, then the others' (work stealing).  Thread 0 keeps one claim on queue q in
+    // flight: the counter value for the item after the current one, claimed when the current one
+    // starts and resolved when it ends, so the atomic's round trip is hidden behind the item's work.
+    int q = 2 * (int)(blockIdx.x % (unsigned)W.nslab), hops = 0, claim = 0;
     auto resolve = [&]() -> int {  // thread 0: the claimed item, or the next queue's, or -1
-        int k = s_qstart[q] + claim;
-        while (k >= s_qstart[q + 1]) {
-            q = q + 1 == nslab ? 0 : q + 1;
-            if (++hops >= nslab) return -1;
-            k = s_qstart[q] + atomicAdd(&qnext[q * QPAD], 1);
+        while (claim >= s_count[q]) {
+            do {
+                q = q + 1 == nq ? 0 : q + 1;
+                if (++hops >= nq) return -1;
+            } while (s_count[q] == 0);
+            claim = atomicAdd(&W.next[q * QPAD], 1);
         }
-        return k;
+        return W.base(q) + claim;
     };
     auto decode = [&](int item) -> ItemT {
         ItemT I;
-        const int4 it = items[item];
+        const int4 it = W.items[item];
         I.sp = __builtin_amdgcn_readfirstlane(it.x);
         I.bin = __builtin_amdgcn_readfirstlane(it.y);
         I.start = __builtin_amdgcn_readfirstlane(it.z);
         const int cnt = __builtin_amdgcn_readfirstlane(it.w);
-        I.end = min(cnt, I.start + chunk);
-        const int bin = I.bin < 0 ? 0 : I.bin;
-        I.t0x = (bin % P.ntx) * TX;
-        I.t0y = ((bin / P.ntx) % P.nty) * TY;
-        I.t0z = (bin / (P.ntx * P.nty)) * TZ;
-        I.b0 = I.bin < 0 ? 0 : gbl(iop.s[I.sp].in_off)[bin];
+        I.end = min(cnt, I.start + W.chunk);
+        I.t0x = (I.bin % P.ntx) * TX;
+        I.t0y = ((I.bin / P.ntx) % P.nty) * TY;
+        I.t0z = (I.bin / (P.ntx * P.nty)) * TZ;
+        I.b0 = gbl(iop.s[I.sp].in_off)[I.bin];
         return I;
     };
     // E^n and B^(n-1/2) of an item's tile (box node (a, b, c) <-> absolute node
@@ -932,7 +933,7 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
     };
 
     if (tid == 0) {
-        claim = atomicAdd(&qnext[q * QPAD], 1);
+        if (s_count[q] > 0) claim = atomicAdd(&W.next[q * QPAD], 1);
         const int first = resolve();
         s_item = first;
     }
@@ -942,10 +943,8 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
     PRaw nx;  // this thread's particle of the next round
     if (cur >= 0) {
         I = decode(cur);
-        if (I.bin >= 0) {
-            stage(I);
-            if (I.start + tid < I.end) load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
-        }
+        stage(I);
+        if (I.start + tid < I.end) load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
     }
 
     while (cur >= 0) {
@@ -953,100 +952,96 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         const SpeciesIO &IO = iop.s[I.sp];
-        if (I.bin >= 0) {  // overflow tails (bin < 0) are k_split_overflow's
-            // B^n = B^(n-1/2) - (dt/2) curl E^n on the B box (the first half of the Yee B update)
-            for (int k = tid; k < G::NE; k += SST) {
-                const int bc = k / G::EX, a = k - bc * G::EX, c = bc / G::EY, b = bc - c * G::EY;
-                const float *ex = Fs + a + G::FX * (b + G::FY * c), *ey = ex + G::NF, *ez = ey + G::NF;
-                float B3[3];
-                half_curl_b(ex, ey, ez, 1, G::FS, G::FX * G::FY, I.t0z - 1 + c == P.nz - 1, hb, B3);
-                Bs[k] += B3[0];
-                Bs[G::NE + k] += B3[1];
-                Bs[2 * G::NE + k] += B3[2];
-            }
+        // B^n = B^(n-1/2) - (dt/2) curl E^n on the B box (the first half of the Yee B update)
+        for (int k = tid; k < G::NE; k += SST) {
+            const int bc = k / G::EX, a = k - bc * G::EX, c = bc / G::EY, b = bc - c * G::EY;
+            const float *ex = Fs + a + G::FX * (b + G::FY * c), *ey = ex + G::NF, *ez = ey + G::NF;
+            float B3[3];
+            half_curl_b(ex, ey, ez, 1, G::FS, G::FX * G::FY, I.t0z - 1 + c == P.nz - 1, hb, B3);
+            Bs[k] += B3[0];
+            Bs[G::NE + k] += B3[1];
+            Bs[2 * G::NE + k] += B3[2];
         }
         __syncthreads();  // (also publishes s_item)
         // the item after this one, resolved by thread 0 at the top of this one: its descriptor
         // loads are in flight during the rounds
-        if (I.bin >= 0) {
-            const LdsBoxT<G> box{Fs};
-            for (int base = I.start; base < I.end; base += SST) {
-                // pushed: advanced (deposits its current); act: still in the band (appended)
-                bool act = base + tid < I.end, pushed = false;
-                PState q;
-                float X0[3] = {0.0f, 0.0f, 0.0f}, X1[3] = {0.0f, 0.0f, 0.0f};
-                double fq = 0.0;
-                int li = 0, lj = 0, lk = 0;
-                if (act) {
-                    unpack_raw(P, nx, q);
-                    li = q.i - I.t0x;
-                    lj = q.j - I.t0y;
-                    lk = q.l - I.t0z;
-                    const bool inside = li >= 0 && li < TX && lj >= 0 && lj < TY && lk >= 0 && lk < TZ &&
-                                        q.o[0] >= -0.5f && q.o[0] < 0.5f && q.o[1] >= -0.5f &&
-                                        q.o[1] < 0.5f && q.o[2] >= -0.5f && q.o[2] < 0.5f;
-                    if (!inside) {
-                        // cannot happen: every binned particle was appended to the bin of its cell
-                        atomicOr(flags, DFLAG_BIN_LOST);
+        const LdsBoxT<G> box{Fs};
+        for (int base = I.start; base < I.end; base += SST) {
+            // pushed: advanced (deposits its current); act: still in the band (appended)
+            bool act = base + tid < I.end, pushed = false;
+            PState q;
+            float X0[3] = {0.0f, 0.0f, 0.0f}, X1[3] = {0.0f, 0.0f, 0.0f};
+            double fq = 0.0;
+            int li = 0, lj = 0, lk = 0;
+            if (act) {
+                unpack_raw(P, nx, q);
+                li = q.i - I.t0x;
+                lj = q.j - I.t0y;
+                lk = q.l - I.t0z;
+                const bool inside = li >= 0 && li < TX && lj >= 0 && lj < TY && lk >= 0 && lk < TZ &&
+                                    q.o[0] >= -0.5f && q.o[0] < 0.5f && q.o[1] >= -0.5f &&
+                                    q.o[1] < 0.5f && q.o[2] >= -0.5f && q.o[2] < 0.5f;
+                if (!inside) {
+                    // cannot happen: every binned particle was appended to the bin of its cell
+                    atomicOr(flags, DFLAG_BIN_LOST);
+                    act = false;
+                } else {
+                    float EB[6];
+                    gather6(box, q.o, li, lj, lk, EB);
+                    if (!advance(P, EB, P.und_kind != 0, tabA[lk + 1], tabC[lk + 1], tabS[lk + 1], q, X1)) {
+                        atomicOr(flags, DFLAG_NONFINITE);
                         act = false;
                     } else {
-                        float EB[6];
-                        gather6(box, q.o, li, lj, lk, EB);
-                        if (!advance(P, EB, P.und_kind != 0, tabA[lk + 1], tabC[lk + 1], tabS[lk + 1], q, X1)) {
-                            atomicOr(flags, DFLAG_NONFINITE);
-                            act = false;
-                        } else {
-                            fq = (double)q.w / P.dt;
-                            if (!fixed_ok(fq, P.fscale)) {
-                                atomicOr(flags, DFLAG_FIXED_OVERFLOW);
-                                fq = 0.0;
-                            }
-                            for (int d = 0; d < 3; ++d) {
-                                X0[d] = q.o[d];
-                                q.o[d] = X1[d];
-                            }
-                            pushed = true;
-                            act = renormalise(P, S, q);
+                        fq = (double)q.w / P.dt;
+                        if (!fixed_ok(fq, P.fscale)) {
+                            atomicOr(flags, DFLAG_FIXED_OVERFLOW);
+                            fq = 0.0;
                         }
+                        for (int d = 0; d < 3; ++d) {
+                            X0[d] = q.o[d];
+                            q.o[d] = X1[d];
+                        }
+                        pushed = true;
+                        act = renormalise(P, S, q);
                     }
                 }
-                // destination slot: the reservation's atomic is in flight during the deposit,
-                // and so are the loads of the next round's particles
-                const int bin = act ? bin_of(P, q.i, q.j, q.l) : 0;
-                const SlotTicket tk = reserve_issue(act, bin, IO.out.cnt);
-                const int64_t ob0 = gbl(IO.out.off)[bin], ocap = gbl(IO.out.off)[bin + 1] - ob0;
-                {  // every lane loads (a clamped index past the item's end), so the waits stay static
-                    const int nb = min(base + SST + tid, I.end - 1);
-                    load_raw(IO.in, I.b0 + nb, nx, REC ? iop.id[I.sp].in : nullptr);
-                }
-                if (pushed) {
-                    Esk e;
-                    esk_setup(X0, X1, e);
-                    // LDS current boxes, origin t0 - 2: box index of offset r is l + r + 2;
-                    // one base index per component, the node offsets are immediates; the values
-                    // are added biased (to_fixed_as) and unbiased when the flush reads the sums
-                    const int bx = li + e.base[0] + 2, by = lj + e.base[1] + 2, bz = lk + e.base[2] + 2;
-                    const int jb[3] = {bx + G::XS * by + G::XX * G::XY * bz,
-                                       G::NJX + bx + G::YS * by + G::YX * G::YY * bz,
-                                       G::NJX + G::NJY + bx + G::ZS * by + G::ZX * G::ZY * bz};
-                    auto add = [&](int c, int m, int a, int b, long long iv) {
-                        int off;
-                        if (c == 0)  // (m, a, b) along (x, y, z)
-                            off = m + G::XS * a + G::XX * G::XY * b;
-                        else if (c == 1)  // (y, z, x)
-                            off = b + G::YS * m + G::YX * G::YY * a;
-                        else  // (z, x, y)
-                            off = a + G::ZS * b + G::ZX * G::ZY * m;
-                        atomicAdd((unsigned long long *)&Js[jb[c] + off], (unsigned long long)iv);
-                    };
-                    esk_visit<DEP, true, G::FLAT>(e, fq, P.fscale, add);
-                }
-                store_at(IO.out, act, reserve_slot_of(act, tk), ob0, ocap, act ? pack_cell(P, q.i, q.j, q.l) : 0,
-                         q.o, q.u, q.w, flags, REC ? iop.id[I.sp].out : nullptr, q.id);
             }
+            // destination slot: the reservation's atomic is in flight during the deposit,
+            // and so are the loads of the next round's particles
+            const int bin = act ? bin_of(P, q.i, q.j, q.l) : 0;
+            const SlotTicket tk = reserve_issue(act, bin, IO.out.cnt);
+            const int64_t ob0 = gbl(IO.out.off)[bin], ocap = gbl(IO.out.off)[bin + 1] - ob0;
+            {  // every lane loads (a clamped index past the item's end), so the waits stay static
+                const int nb = min(base + SST + tid, I.end - 1);
+                load_raw(IO.in, I.b0 + nb, nx, REC ? iop.id[I.sp].in : nullptr);
+            }
+            if (pushed) {
+                Esk e;
+                esk_setup(X0, X1, e);
+                // LDS current boxes, origin t0 - 2: box index of offset r is l + r + 2;
+                // one base index per component, the node offsets are immediates; the values
+                // are added biased (to_fixed_as) and unbiased when the flush reads the sums
+                const int bx = li + e.base[0] + 2, by = lj + e.base[1] + 2, bz = lk + e.base[2] + 2;
+                const int jb[3] = {bx + G::XS * by + G::XX * G::XY * bz,
+                                   G::NJX + bx + G::YS * by + G::YX * G::YY * bz,
+                                   G::NJX + G::NJY + bx + G::ZS * by + G::ZX * G::ZY * bz};
+                auto add = [&](int c, int m, int a, int b, long long iv) {
+                    int off;
+                    if (c == 0)  // (m, a, b) along (x, y, z)
+                        off = m + G::XS * a + G::XX * G::XY * b;
+                    else if (c == 1)  // (y, z, x)
+                        off = b + G::YS * m + G::YX * G::YY * a;
+                    else  // (z, x, y)
+                        off = a + G::ZS * b + G::ZX * G::ZY * m;
+                    atomicAdd((unsigned long long *)&Js[jb[c] + off], (unsigned long long)iv);
+                };
+                esk_visit<DEP, true, G::FLAT>(e, fq, P.fscale, add);
+            }
+            store_at(IO.out, act, reserve_slot_of(act, tk), ob0, ocap, act ? pack_cell(P, q.i, q.j, q.l) : 0,
+                     q.o, q.u, q.w, flags, REC ? iop.id[I.sp].out : nullptr, q.id);
         }
         if (tid == 0) {
-            claim = atomicAdd(&qnext[q * QPAD], 1);
+            claim = atomicAdd(&W.next[q * QPAD], 1);
             s_item = resolve();
         }
         // every deposit of this item is in the current boxes
@@ -1058,34 +1053,30 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
         // the next item's fields and first particles are on their way during this item's flush
         if (next >= 0) {
             I = N;
-            if (I.bin >= 0) {
-                stage(I);
-                if (I.start + tid < I.end)
-                    load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
-            }
+            stage(I);
+            if (I.start + tid < I.end)
+                load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
         }
         // flush nonzero LDS currents (unbiased) with global 64-bit integer atomics, clearing the boxes.
         // Thread t takes columns t and t + SST of the three boxes' (x, y) footprints and walks
         // their planes: a column's global offset is formed once, a plane's is wave-uniform.
         if constexpr (G::FLAT) {
             // one row of nodes per box: a thread per node
-            if (C.bin >= 0) {
-                const uint32_t pl = (uint32_t)P.nx;
-                for (int e = tid; e < G::NJ; e += SST) {
-                    const long long sum = Js[e];
-                    if (sum == 0) continue;
-                    Js[e] = 0;
-                    const long long v = unbias48(sum);
-                    const int h = e < G::NJX ? e : e < G::NJX + G::NJY ? e - G::NJX : e - G::NJX - G::NJY;
-                    const int X = e < G::NJX ? G::XX : G::YX, z = h / X, x = h - z * X, l = C.t0z - 2 + z;
-                    if (v == 0 || l < 0 || l >= P.nz) continue;
-                    long long *J = e < G::NJX ? Jx : e < G::NJX + G::NJY ? Jy : Jz;
-                    atomicAdd((unsigned long long *)&J[near_cell32<true>(P, C.t0x - 2 + x, 0, 0) +
-                                                       pl * (uint32_t)ring_plane(l, S.k0r, P.nz)],
-                              (unsigned long long)v);
-                }
+            const uint32_t pl = (uint32_t)P.nx;
+            for (int e = tid; e < G::NJ; e += SST) {
+                const long long sum = Js[e];
+                if (sum == 0) continue;
+                Js[e] = 0;
+                const long long v = unbias48(sum);
+                const int h = e < G::NJX ? e : e < G::NJX + G::NJY ? e - G::NJX : e - G::NJX - G::NJY;
+                const int X = e < G::NJX ? G::XX : G::YX, z = h / X, x = h - z * X, l = C.t0z - 2 + z;
+                if (v == 0 || l < 0 || l >= P.nz) continue;
+                long long *J = e < G::NJX ? Jx : e < G::NJX + G::NJY ? Jy : Jz;
+                atomicAdd((unsigned long long *)&J[near_cell32<true>(P, C.t0x - 2 + x, 0, 0) +
+                                                   pl * (uint32_t)ring_plane(l, S.k0r, P.nz)],
+                          (unsigned long long)v);
             }
-        } else if (C.bin >= 0) {
+        } else {
             constexpr int CX = G::XX * G::XY, CY = G::YX * G::YY, CZ = G::ZX * G::ZY, NCOL = CX + CY + CZ;
             constexpr int NPMAX = G::XZ > G::ZZ ? G::XZ : G::ZZ;
             static_assert(NCOL <= 2 * SST && G::XZ == G::YZ, "two columns per thread");
@@ -1135,9 +1126,8 @@ __global__ void __launch_bounds__((TileGeom<TX, TY, TZ>::NT), (TileGeom<TX, TY, 
 // the tiles the step kernel is instantiated for
 #define PIC_SPLIT_TILES(X) X(8, 8, 4) X(8, 8, 8) X(8, 8, 16) X(16, 8, 4) X(16, 16, 4) X(16, 8, 8) X(16, 1, 16)
 
-using StepKernel = void (*)(Params, StepCtx, const int4 *, const int32_t *, int32_t *, int, int, IOPair,
-                            FieldsT<float>, long long *, long long *, long long *, int32_t *, const double *,
-                            const float *, const float *);
+using StepKernel = void (*)(Params, StepCtx, WorkList, IOPair, FieldsT<float>, long long *, long long *, long long *,
+                            int32_t *, const double *, const float *, const float *);
 
 // record mode has one instantiation per tile (the wave-pruned deposit: every
 // variant gives the same integer currents)
@@ -1164,170 +1154,151 @@ static void step_shape(int tx, int ty, int tz, int &lds, int &threads) {
 #undef PIC_PICK
 }
 
+// Slabs of the work queues: workgroups are dispatched round-robin over the 8 XCDs.
+static int queue_slabs(const Params &P) { return P.ntz % 8 == 0 ? 8 : 1; }
+// Most items of one slab's queue of a species with `slots` slots in its bins.
+static int queue_cap(const Params &P, int64_t slots, int chunk) {
+    return (int)(P.nbins / queue_slabs(P) + slots / chunk + 1);
+}
+uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, int chunk) {
+    return 16 * (uint64_t)queue_slabs(P) *
+           (uint64_t)((int64_t)queue_cap(P, slots_b, chunk) + queue_cap(P, slots_p, chunk));
+}
+
 // Particles per work item for n particles in all: whole rounds of the workgroup, at most CH.  A bin
-// of more is shared out, which costs each part a staging and a flush of the tile (about 3 us; with
-// every bin of 2048 in parts of 768, 128 x 128 x 512 takes 1.92 ms for 1.21).  Where the step is a
-// few rounds a workgroup, the parts of the largest bins decide how long it is: 64 x 64 x 256 with a
-// beam of a million takes 308 us in parts of 9216, 232 of 4608, 229 of 2304, 279 of 1536; 24 x 40 x
-// 64 44 us in parts of 2304, 27 of 768; 32 x 32 x 64 with 16384 particles 35 us of 1536, 25 of 768.
-// A quarter of what a workgroup of the 256 CUs has to do gives 2304, 768 and 768 there.
+// of more is shared out.  An item costs its staging and flush (about 9 us on 16 x 8 x 8, more where
+// parts of a bin flush to the same cells at a time) besides 8 us a round, so that 128 x 128 x 512, every
+// bin of 2048 in parts of 768, takes 1.92 ms for 1.21.  Where the step is a few rounds a workgroup, the
+// parts of the largest bins (the beam's) decide how long it is.  Kernel times in us for parts of
+//                                                         768 1536 2304 3072 4608 6144 9216
+//   32 x 32 x 64, beam of 16384                            25   35                       35
+//   24 x 40 x 64, plasma of 2 a cell                       27   38   44                  44
+//   40 x 24 x 144, plasma of 2 a cell                           56   54   63   85  108  151
+//   64 x 64 x 256, beam of 1.0 M, plasma of 2 a cell      347  279  229       232       308
+//   48 x 32 x 460, beam of 2.4 M, plasma of 2 a cell           455  375  337  298  286  288
+//   96 x 32 x 296, beam of 2.4 M, plasma and ions              635  530  472  382  366  355
+// So: two fifths of what a workgroup of the 256 CUs has to do (768, 768, 768, 4608, 5376, 9216 here),
+// but a plasma bin in no more parts than there are workgroups for all of them (2304 in the third).
 int split_chunk(const Params &P, int64_t n) {
     int lds, threads;
     step_shape(P.tx, P.ty, P.tz, lds, threads);
     const int64_t wgs = P.ty == 1 ? 512 : 256;
-    return threads * (int)std::min<int64_t>(std::max<int64_t>(n / (4 * wgs * threads), 1), CH / threads);
+    const int64_t plasma = P.has_plasma ? sheet_particles(P) / P.plane * P.ppz * P.tx * P.ty * P.tz : 0;
+    const int64_t part = plasma / std::max<int64_t>(1, wgs / P.nbins);
+    const int64_t rounds = std::max(2 * n / (5 * wgs * threads), (part + threads - 1) / threads);
+    return threads * (int)std::min<int64_t>(std::max<int64_t>(rounds, 1), CH / threads);
 }
 
 // overflow tails of the previous step: untiled path, one particle per thread,
-// persistent grid over the tail lengths read on the device
-__global__ void __launch_bounds__(256) k_split_overflow(Params P, StepCtx S, const SpeciesIO *ios, const IdIO *iids,
-                                                        FieldsT<float> f, long long *Jx, long long *Jy, long long *Jz,
-                                                        int32_t *flags) {
+// workgroup w of n, over the tail lengths read on the device
+__device__ inline void push_tails(const Params &P, const StepCtx &S, const IOPair &iop, const FieldsT<float> &f,
+                                  long long *Jx, long long *Jy, long long *Jz, int32_t *flags, int w, int nw) {
     const float *F6[6] = {f.E[0], f.E[1], f.E[2], f.B[0], f.B[1], f.B[2]};
     for (int sp = 0; sp < 2; ++sp) {
-        const SpeciesIO &IO = ios[sp];
+        const SpeciesIO &IO = iop.s[sp];
         const int n = (int)min((int64_t)*IO.in_ovf, IO.in_ovf_cap);
-        for (int base = blockIdx.x * 256; base < n; base += gridDim.x * 256) {
+        for (int base = w * (int)blockDim.x; base < n; base += nw * (int)blockDim.x) {
             int k = base + threadIdx.x;
             bool act = k < n;
             PState q;
             if (act) {
-                load_particle(IO.in, IO.in_ovf_start + k, P, q, iids[sp].in);
+                load_particle(IO.in, IO.in_ovf_start + k, P, q, iop.id[sp].in);
                 act = particle_global(P, S, F6, Jx, Jy, Jz, q, flags);
             }
             append(IO.out, act, act ? bin_of(P, q.i, q.j, q.l) : 0, act ? pack_cell(P, q.i, q.j, q.l) : 0, q.o,
-                   q.u, q.w, flags, iids[sp].out, q.id);
+                   q.u, q.w, flags, iop.id[sp].out, q.id);
         }
     }
 }
 
 // ---------------------------------------------------------------- rebin (no physics)
-__global__ void __launch_bounds__(ST) k_rebin(Params P, int chunk, const int4 *items, const int32_t *nitems, int32_t *next,
-                                              const SpeciesIO *ios, const IdIO *iids, int32_t *flags) {
-    __shared__ int s_item;
-    const int tid = threadIdx.x;
-    const int total = *nitems;
-    for (;;) {
-        if (tid == 0) s_item = atomicAdd(next, 1);
-        __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= total) break;
-        const int4 it = items[item];
-        const SpeciesIO &IO = ios[it.x];
-        const int bin = it.y, start = it.z, cnt = it.w;
-        const int64_t b0 = bin < 0 ? IO.in_ovf_start : IO.in_off[bin];
-        const int end = min(cnt, start + chunk);
+// the work list's items and the overflow tails into the output bins
+__global__ void __launch_bounds__(ST) k_rebin(Params P, WorkList W, const SpeciesIO *ios, const IdIO *iids,
+                                              int32_t *flags) {
+    auto move = [&](int sp, int64_t b0, int start, int end) {
+        const SpeciesIO &IO = ios[sp];
         for (int base = start; base < end; base += ST) {
-            int k = base + tid;
+            int k = base + (int)threadIdx.x;
             bool act = k < end;
             PState q;
-            if (act) load_particle(IO.in, b0 + k, P, q, iids[it.x].in);
+            if (act) load_particle(IO.in, b0 + k, P, q, iids[sp].in);
             append(IO.out, act, act ? bin_of(P, q.i, q.j, q.l) : 0, act ? pack_cell(P, q.i, q.j, q.l) : 0, q.o,
-                   q.u, q.w, flags, iids[it.x].out, q.id);
+                   q.u, q.w, flags, iids[sp].out, q.id);
         }
+    };
+    for (int q = 0; q < 2 * W.nslab; ++q)
+        for (int k = blockIdx.x; k < W.count[q]; k += gridDim.x) {
+            const int4 it = W.items[W.base(q) + k];
+            move(it.x, ios[it.x].in_off[it.y], it.z, min(it.w, it.z + W.chunk));
+        }
+    for (int sp = 0; sp < 2; ++sp) {
+        const int n = (int)min((int64_t)*ios[sp].in_ovf, ios[sp].in_ovf_cap);
+        for (int start = blockIdx.x * ST; start < n; start += gridDim.x * ST)
+            move(sp, ios[sp].in_ovf_start, start, min(n, start + ST));
     }
 }
 
 // ---------------------------------------------------------------- work list
-// items (species, bin, first particle, bin count) for every chunk of every
-// non-empty bin of the input buffer, then the overflow tails (bin = -1).
-// Three kernels: per-block item counts, single-thread scan of the block
-// totals, per-block writes.  They also clear the output counters.
-__device__ inline int items_of(int n, int chunk) { return (n + chunk - 1) / chunk; }
-
-// Work-list entry e (0 <= e < 2 nbins) in slab-major order: the bins form
-// nslab slabs of whole z layers (bins are numbered z-major), and within a slab
-// the beam's bins come before the plasma's.
-__device__ inline void entry_of(int e, int nbins, int nslab, int &sp, int &bin) {
-    const int bps = nbins / nslab, s = e / (2 * bps), r = e - s * 2 * bps;
-    sp = r >= bps ? 1 : 0;
-    bin = s * bps + (r - sp * bps);
-}
-
-__global__ void k_wl_count(const int64_t *off0, const int32_t *cnt0, const int64_t *off1, const int32_t *cnt1,
-                           int nbins, int nslab, int chunk, int64_t *part) {
-    __shared__ int64_t s[WT];
-    int e = blockIdx.x * WT + threadIdx.x;
-    int v = 0;
-    if (e < 2 * nbins) {
-        int sp, bin;
-        entry_of(e, nbins, nslab, sp, bin);
-        v = items_of(sp ? bin_count(off1, cnt1, bin) : bin_count(off0, cnt0, bin), chunk);
+// What a step needs before its particles, in one launch: workgroups below nwl build the work list, a
+// block's items in one reservation of its queue, and clear the output counts; those after them form the
+// undulator's phase table.  (An exact scan took three launches, one of them a serial pass over the
+// blocks: 26 us at 65536 entries; the order within a queue is free, since the currents are integer sums.)
+__global__ void __launch_bounds__(WT) k_step_prep(Params P, StepCtx S, WorkList W, const int64_t *off0,
+                                                  const int32_t *cnt0, const int64_t *off1, const int32_t *cnt1,
+                                                  int32_t *zero0, int32_t *zero1, int32_t *ovf0, int32_t *ovf1,
+                                                  int nwl, double *tabA, float *tabC, float *tabS) {
+    const int b = blockIdx.x, t = threadIdx.x;
+    if (b >= nwl) {
+        const int e = (b - nwl) * WT + t;
+        if (e < P.nz + 2) ext_plane(P, S.k0, e - 1, S.t, tabA[e], tabC[e], tabS[e]);
+        return;
     }
-    s[threadIdx.x] = v;
+    __shared__ int ws[WT / 64], first;
+    const int bps = P.nbins / W.nslab, per = nwl / (2 * W.nslab), q = b / per, sp = q & 1, e = (b - q * per) * WT + t;
+    if (t == 0 && b == q * per) {
+        W.next[q * QPAD] = 0;
+        W.count_next[q] = 0;
+    }
+    if (t == 0 && b == 0) *ovf0 = *ovf1 = 0;
+    const int bin = (q >> 1) * bps + e;
+    int c = 0;
+    if (e < bps) {
+        c = bin_count(sp ? off1 : off0, sp ? cnt1 : cnt0, bin);
+        (sp ? zero1 : zero0)[bin] = 0;
+    }
+    const int v = (c + W.chunk - 1) / W.chunk;
+    int pos = v;
+    for (int k = 1; k < 64; k <<= 1) {
+        const int u = __shfl_up(pos, k);
+        if ((t & 63) >= k) pos += u;
+    }
+    if ((t & 63) == 63) ws[t >> 6] = pos;
     __syncthreads();
-    for (int h = WT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) s[threadIdx.x] += s[threadIdx.x + h];
-        __syncthreads();
+    if (t == 0) {
+        int n = 0;
+        for (int w = 0; w < WT / 64; ++w) n += ws[w];
+        first = n ? atomicAdd(&W.count[q], n) : 0;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
-}
-
-__global__ void k_wl_scan(int64_t *part, int nblk, const int32_t *ovf0, int64_t ocap0, const int32_t *ovf1,
-                          int64_t ocap1, int32_t *nitems, int32_t *next, int4 *items, int64_t items_cap,
-                          int32_t *clr0, int32_t *clr1, int32_t *qnext, int32_t *qstart, int nslab, int chunk) {
-    if (threadIdx.x != 0) return;
-    int64_t acc = 0;
-    for (int b = 0; b < nblk; ++b) {
-        int64_t v = part[b];
-        part[b] = acc;
-        acc += v;
-    }
-    for (int q = 0; q < nslab; ++q) qnext[q * QPAD] = 0;
-    qstart[nslab] = (int32_t)min(acc, items_cap);  // the slab queues end before the overflow items
-    int o0 = (int)min((int64_t)*ovf0, ocap0), o1 = (int)min((int64_t)*ovf1, ocap1);
-    for (int k = 0; k < items_of(o0, chunk) && acc < items_cap; ++k) items[acc++] = make_int4(0, -1, k * chunk, o0);
-    for (int k = 0; k < items_of(o1, chunk) && acc < items_cap; ++k) items[acc++] = make_int4(1, -1, k * chunk, o1);
-    *nitems = (int32_t)min(acc, items_cap);
-    *next = 0;
-    *clr0 = 0;
-    *clr1 = 0;
-}
-
-__global__ void k_wl_write(const int64_t *off0, const int32_t *cnt0, const int64_t *off1, const int32_t *cnt1,
-                           int nbins, int nslab, int chunk, const int64_t *part, int4 *items, int64_t items_cap, int32_t *zero0,
-                           int32_t *zero1, int32_t *qstart) {
-    __shared__ int64_t s[WT];
-    int e = blockIdx.x * WT + threadIdx.x;
-    int v = 0, c = 0, sp = 0, bin = 0;
-    if (e < 2 * nbins) {
-        entry_of(e, nbins, nslab, sp, bin);
-        c = sp ? bin_count(off1, cnt1, bin) : bin_count(off0, cnt0, bin);
-    }
-    v = items_of(c, chunk);
-    s[threadIdx.x] = v;
     __syncthreads();
-    for (int k = 1; k < WT; k <<= 1) {  // inclusive scan in the block
-        int64_t t = (int)threadIdx.x >= k ? s[threadIdx.x - k] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
-    }
-    int64_t o = part[blockIdx.x] + s[threadIdx.x] - v;
-    for (int k = 0; k < v; ++k)
-        if (o + k < items_cap) items[o + k] = make_int4(sp, bin, k * chunk, c);
-    if (e < 2 * nbins) {
-        if (sp) zero1[bin] = 0;
-        else zero0[bin] = 0;
-        const int bps = nbins / nslab;
-        if (e % (2 * bps) == 0) qstart[e / (2 * bps)] = (int32_t)min(o, items_cap);  // first entry of a slab
-    }
+    pos += first - v;
+    for (int w = 0; w < (t >> 6); ++w) pos += ws[w];
+    for (int k = 0; k < v; ++k)  // cap bounds what a queue can hold
+        if (pos + k < W.cap[sp]) W.items[W.base(q) + pos + k] = make_int4(sp, bin, k * W.chunk, c);
 }
 
-// in_cap0/1: how many overflow-tail particles the input buffer can hold
-static void build_worklist(Ctx &c, int cur, int64_t in_cap0, int64_t in_cap1) {
+// the work list of buffer cur (and, with S, the step's table), the counts of the other buffer cleared
+static void build_worklist(Ctx &c, int cur, const StepCtx *S) {
     SplitState &X = SS(c);
-    int nb = c.P.nbins;
-    int nblk = nblocks(2 * (int64_t)nb, WT);
-    int o = cur ^ 1;
+    const int o = cur ^ 1;
     Store &b = X.s[0], &p = X.s[1];
-    hipLaunchKernelGGL(k_wl_count, dim3(nblk), dim3(WT), 0, c.st, b.off[cur], b.cnt[cur], p.off[cur], p.cnt[cur], nb,
-                       X.nslab, X.chunk, X.scan_part);
-    hipLaunchKernelGGL(k_wl_scan, dim3(1), dim3(64), 0, c.st, X.scan_part, nblk, b.ovf[cur], in_cap0, p.ovf[cur],
-                       in_cap1, X.nitems, X.next, X.items, X.items_cap, b.ovf[o], p.ovf[o], X.qnext, X.qstart, X.nslab, X.chunk);
-    hipLaunchKernelGGL(k_wl_write, dim3(nblk), dim3(WT), 0, c.st, b.off[cur], b.cnt[cur], p.off[cur], p.cnt[cur], nb,
-                       X.nslab, X.chunk, X.scan_part, X.items, X.items_cap, b.cnt[o], p.cnt[o], X.qstart);
+    std::swap(X.qcount[0], X.qcount[1]);
+    X.work.count = X.qcount[0];
+    X.work.count_next = X.qcount[1];
+    const int nwl = 2 * X.work.nslab * nblocks(c.P.nbins / X.work.nslab, WT);
+    const int ntab = S && c.P.und_kind ? nblocks(c.P.nz + 2, WT) : 0;
+    hipLaunchKernelGGL(k_step_prep, dim3(nwl + ntab), dim3(WT), 0, c.st, c.P, S ? *S : StepCtx{}, X.work, b.off[cur],
+                       b.cnt[cur], p.off[cur], p.cnt[cur], b.cnt[o], p.cnt[o], b.ovf[o], p.ovf[o], nwl, X.tabA,
+                       X.tabC, X.tabS);
 }
 
 static IdIO species_ids(Ctx &c, int sp, int cur) {
@@ -1401,23 +1372,23 @@ void split_setup(Ctx &c) {
             X->s[sp].cnt[k] = cnts + (2 * sp + k) * nb;
             X->s[sp].ovf[k] = ovfs + (2 * sp + k);
         }
-    X->nitems = ovfs + 4;
-    X->next = ovfs + 5;
     char *wl = A + c.split_off_wl;
-    X->items_cap = c.split_items_cap;
-    X->chunk = c.split_chunk;
-    X->items = (int4 *)wl;
-    X->scan_part = (int64_t *)(wl + 16 * (uint64_t)X->items_cap);
-    X->tmpcnt = (int32_t *)(X->scan_part + nblocks(2 * nb, WT) + 8);
+    X->work.items = (int4 *)wl;
+    X->work.chunk = c.split_chunk;
+    X->work.nslab = queue_slabs(P);
+    X->work.cap[0] = queue_cap(P, X->s[0].bin_slots, c.split_chunk);
+    X->work.cap[1] = queue_cap(P, X->s[1].bin_slots, c.split_chunk);
+    X->tmpcnt = (int32_t *)(wl + split_items_bytes(P, X->s[0].bin_slots, X->s[1].bin_slots, c.split_chunk));
     X->tmpoff = (int64_t *)(X->tmpcnt + 2 * nb + 8);
     X->ios = (SpeciesIO *)(((uintptr_t)(X->tmpoff + nb + 8) + 15) & ~(uintptr_t)15);
     X->iids = (IdIO *)(X->ios + 6);
     X->tabA = (double *)(((uintptr_t)(X->iids + 6) + 15) & ~(uintptr_t)15);
     X->tabC = (float *)(X->tabA + P.nz + 2);
     X->tabS = X->tabC + P.nz + 2;
-    X->qnext = (int32_t *)(((uintptr_t)(X->tabS + P.nz + 2) + 255) & ~(uintptr_t)255);
-    X->qstart = X->qnext + 8 * QPAD;  // its own 256-byte block
-    X->nslab = P.ntz % 8 == 0 ? 8 : 1;  // workgroups are dispatched round-robin over the 8 XCDs
+    X->work.next = (int32_t *)(((uintptr_t)(X->tabS + P.nz + 2) + 255) & ~(uintptr_t)255);
+    X->qcount[0] = X->work.next + 16 * QPAD;  // 256-byte blocks of their own
+    X->qcount[1] = X->qcount[0] + QPAD;
+    (void)hipMemsetAsync(X->qcount[0], 0, 2 * 4 * QPAD, c.st);
     step_shape(P.tx, P.ty, P.tz, X->lds_bytes, X->threads);
     // deposit: option 0 = wave-pruned windows, 1 = whole components, 2 = zero-skipping
     X->kern = step_kernel(P.tx, P.ty, P.tz, c.opt.variant == 0 ? 2 : (c.opt.variant == 1 ? 1 : 0), c.record != 0);
@@ -1529,10 +1500,17 @@ __global__ void k_beam_init32(Params P, const double *g, int64_t n, double sx, d
 
 // plasma sheets [l0, l0 + nsheets) at time t, window origin k0: appended to bins
 // of `out` (bins == true) or to a flat list counted by out.ovf (bins == false)
-__global__ void k_inject32(Params P, int64_t l0, int64_t total, double t, int64_t k0, OutStore out, int bins,
-                           int32_t *flags, int32_t *out_id, int64_t id0) {
-    int64_t q = (int64_t)blockIdx.x * ST + threadIdx.x;
-    bool act = q < total;
+struct Sheets {
+    int64_t l0, total;  // first sheet, particles
+    double t;
+    int64_t k0, id0;
+};
+// particle q of them, by a whole wave
+__device__ inline void inject(const Params &P, const Sheets &H, int64_t q, const OutStore &out, int bins,
+                              int32_t *flags, int32_t *out_id) {
+    const int64_t l0 = H.l0, k0 = H.k0, id0 = H.id0;
+    const double t = H.t;
+    bool act = q < H.total;
     PState s;
     int key = 0;
     if (act) {
@@ -1579,6 +1557,22 @@ __global__ void k_inject32(Params P, int64_t l0, int64_t total, double t, int64_
             if (out_id) out_id[r] = s.id;
         }
     }
+}
+
+__global__ void __launch_bounds__(ST) k_inject32(Params P, Sheets H, OutStore out, int bins, int32_t *flags,
+                                                 int32_t *out_id) {
+    inject(P, H, (int64_t)blockIdx.x * ST + threadIdx.x, out, bins, flags, out_id);
+}
+
+// What follows the tiled particles, in one launch: the first ntail workgroups push the overflow tails,
+// the others add the sheets that enter at the front (both append to the output bins).
+__global__ void __launch_bounds__(256) k_step_tails(Params P, StepCtx S, IOPair iop, FieldsT<float> f, long long *Jx,
+                                                    long long *Jy, long long *Jz, int32_t *flags, int ntail,
+                                                    Sheets H) {
+    if ((int)blockIdx.x < ntail)
+        push_tails(P, S, iop, f, Jx, Jy, Jz, flags, blockIdx.x, ntail);
+    else
+        inject(P, H, (int64_t)(blockIdx.x - ntail) * 256 + threadIdx.x, iop.s[1].out, 1, flags, iop.id[1].out);
 }
 
 __global__ void k_count_bins(Params P, Part32 flat, int64_t n, int32_t *cnt) {
@@ -1650,9 +1644,8 @@ static pic_status bins_from_flat(Ctx &c) {
         X.s[sp].n_flat = nflat[sp];
     }
     // the flat lists are read as overflow tails that start at slot 0 and may fill the whole buffer
-    build_worklist(c, 1, X.s[0].bin_slots + X.s[0].ovf_cap, X.s[1].bin_slots + X.s[1].ovf_cap);
-    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.chunk, X.items, X.nitems, X.next, X.ios + 4, X.iids + 4,
-                       c.dflags);
+    build_worklist(c, 1, nullptr);
+    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.work, X.ios + 4, X.iids + 4, c.dflags);
     for (int sp = 0; sp < 2; ++sp) PIC_HIP(c, hipMemsetAsync(X.s[sp].ovf[1], 0, 4, c.st));
     c.cur32 = 0;
     PIC_HIP(c, hipStreamSynchronize(c.st));
@@ -1682,11 +1675,10 @@ void split_beam_init(Ctx &c, const double *normals_dev) {
     c.bw = cnt > 0 ? vz / cnt : 0.0;
 }
 
-// inject the nonzero-weight sheets of [l0, l1) at time t: one launch per run of
-// consecutive nonzero-weight sheets, whose particles take the next ids (the
-// slots the FP64 record layout gives them, in the same order)
-static pic_status inject_runs32(Ctx &c, int64_t l0, int64_t l1, double t, int64_t k0, const OutStore &o,
-                                int32_t *o_id, int bins) {
+// the runs of consecutive nonzero-weight sheets of [l0, l1) at time t, whose particles take the next
+// ids (the slots the FP64 record layout gives them, in the same order): fn of each
+template <typename F>
+static pic_status sheet_runs(Ctx &c, int64_t l0, int64_t l1, double t, int64_t k0, F &&fn) {
     const Params &P = c.P;
     const int64_t per = sheet_particles(P);
     int64_t l = l0;
@@ -1700,8 +1692,7 @@ static pic_status inject_runs32(Ctx &c, int64_t l0, int64_t l1, double t, int64_
                 c.err = "record mode: more than 2^31 plasma particles over the run";
                 return PIC_ERANGE;
             }
-            hipLaunchKernelGGL(k_inject32, dim3(nblocks(total, ST)), dim3(ST), 0, c.st, P, a, total, t, k0, o, bins,
-                               c.dflags, o_id, c.np_slots);
+            fn(Sheets{a, total, t, k0, c.np_slots});
             c.np_slots += total;
         }
     }
@@ -1719,70 +1710,90 @@ pic_status split_plasma_fill(Ctx &c) {
         o.ovf = X.s[1].ovf[1];
         o.bin_slots = X.s[1].bin_slots;
         o.ovf_cap = X.s[1].ovf_cap;
-        pic_status st = inject_runs32(c, c.sh_lo, c.sh_hi, 0.0, 0, o, X.s[1].id[1], 0);
+        pic_status st = sheet_runs(c, c.sh_lo, c.sh_hi, 0.0, 0, [&](const Sheets &H) {
+            hipLaunchKernelGGL(k_inject32, dim3(nblocks(H.total, ST)), dim3(ST), 0, c.st, P, H, o, 0, c.dflags,
+                               X.s[1].id[1]);
+        });
         if (st != PIC_OK) return st;
     }
     return bins_from_flat(c);
 }
 
 // ---------------------------------------------------------------- the step
-void split_step(Ctx &c, const StepCtx &S) {
-    SplitState &X = SS(c);
-    const Params &P = c.P;
+static FieldsT<float> fields_of(const Ctx &c) {
     FieldsT<float> f;
     for (int k = 0; k < 3; ++k) {
         f.E[k] = c.E32[k];
         f.B[k] = c.B32[k];
     }
-    int cur = c.cur32;
-    // the first B half step is formed inside the particle kernel (B^n in LDS); the field state between
-    // steps stays (E^n, B^(n-1/2)), and after the push one full B step replaces the two halves
+    return f;
+}
+
+static IOPair io_pair(Ctx &c, int cur) {
+    const SplitState &X = SS(c);
+    return IOPair{{species_io(c, 0, cur, X.s[0].bin_slots), species_io(c, 1, cur, X.s[1].bin_slots)},
+                  {species_ids(c, 0, cur), species_ids(c, 1, cur)}};
+}
+
+// The first B half step is formed inside the particle kernel (B^n in LDS); the field state between
+// steps stays (E^n, B^(n-1/2)), and after the push one full B step replaces the two halves.
+void split_push(Ctx &c, const StepCtx &S) {
+    SplitState &X = SS(c);
+    const Params &P = c.P;
     hipEvent_t t1 = timing_begin(c);
-    build_worklist(c, cur, 0, 0);  // overflow tails go to k_split_overflow
-    if (P.und_kind)
-        hipLaunchKernelGGL(k_ext_table, dim3(nblocks(P.nz + 2, 256)), dim3(256), 0, c.st, P, S, X.tabA, X.tabC,
-                           X.tabS);
+    build_worklist(c, c.cur32, &S);
+    if (P.ions) launch_ion_fixed(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jioni, c.jionn, c.dflags, c.st);
     timing_end(c, 2, t1);
     hipEvent_t t2 = timing_begin(c);
-    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(X.threads), X.lds_bytes, c.st, P, S, X.items, X.qstart, X.qnext, X.nslab, X.chunk,
-                       IOPair{{species_io(c, 0, cur, X.s[0].bin_slots), species_io(c, 1, cur, X.s[1].bin_slots)},
-                              {species_ids(c, 0, cur), species_ids(c, 1, cur)}},
-                       f,
-                       c.Ji[0], c.Ji[1], c.Ji[2], c.dflags, X.tabA, X.tabC, X.tabS);
-    hipLaunchKernelGGL(k_split_overflow, dim3(256), dim3(256), 0, c.st, P, S, X.ios + 2 * cur, X.iids + 2 * cur, f,
-                       c.Ji[0], c.Ji[1],
-                       c.Ji[2], c.dflags);
+    hipLaunchKernelGGL(X.kern, dim3(X.grid), dim3(X.threads), X.lds_bytes, c.st, P, S, X.work, io_pair(c, c.cur32),
+                       fields_of(c), c.Ji[0], c.Ji[1], c.Ji[2], c.dflags, X.tabA, X.tabC, X.tabS);
     timing_end(c, 0, t2);
+}
+
+// the overflow tails, and the sheets [l0, l1) that enter at the step's end, into the output buffer; then swap
+pic_status split_tails_and_swap(Ctx &c, const StepCtx &S, int64_t l0, int64_t l1) {
+    const Params &P = c.P;
+    constexpr int NTAIL = 256;
+    const IOPair io = io_pair(c, c.cur32);
+    int ntail = NTAIL;  // in the first launch
+    auto launch = [&](const Sheets &H) {
+        hipLaunchKernelGGL(k_step_tails, dim3(ntail + nblocks(H.total, 256)), dim3(256), 0, c.st, P, S, io,
+                           fields_of(c), c.Ji[0], c.Ji[1], c.Ji[2], c.dflags, ntail, H);
+        ntail = 0;
+    };
+    hipEvent_t t = timing_begin(c);
+    pic_status st = P.has_plasma ? sheet_runs(c, l0, l1, S.t1, S.k0n, launch) : PIC_OK;
+    if (ntail) launch(Sheets{});
+    timing_end(c, 0, t);
+    if (st == PIC_OK) c.cur32 ^= 1;
+    return st;
+}
+
+void split_fields(Ctx &c, const StepCtx &S) {
+    const Params &P = c.P;
+    const FieldsT<float> f = fields_of(c);
+    const long long *ion = P.ions ? c.jioni : nullptr;
     hipEvent_t t3 = timing_begin(c);
-    if (P.ions) launch_ion_fixed(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jioni, c.dflags, c.st);
     launch_neutraliser_current(c, S);
     timing_end(c, 2, t3);
     hipEvent_t t4 = timing_begin(c);
-    launch_bhalf<float>(P, S.k0r, f, (float)P.dt, (float *)c.murbuf, c.st);  // B^(n-1/2) -> B^(n+1/2)
-    launch_eupdate<float, long long>(P, S.k0r, f, c.Ji, c.jioni, (float)P.dt, c.st);
-    launch_mur_shift<float, long long>(P, S.k0r, S.shift, c.bw <= 0.0, f, (const float *)c.murbuf, c.jioni,
-                                       (float)P.dt, c.st);
-    timing_end(c, 1, t4);
-}
-
-// inject sheets [l0, l1) at time t into the output buffer (after split_step), then swap
-pic_status split_inject_and_swap(Ctx &c, int64_t l0, int64_t l1, double t, int64_t k0n) {
-    SplitState &X = SS(c);
-    const Params &P = c.P;
-    int o = c.cur32 ^ 1;
-    if (P.has_plasma && l1 > l0) {
-        OutStore out;
-        out.buf = X.s[1].buf[o];
-        out.off = X.s[1].off[o];
-        out.cnt = X.s[1].cnt[o];
-        out.ovf = X.s[1].ovf[o];
-        out.bin_slots = X.s[1].bin_slots;
-        out.ovf_cap = X.s[1].ovf_cap;
-        pic_status st = inject_runs32(c, l0, l1, t, k0n, out, X.s[1].id[o], 1);
-        if (st != PIC_OK) return st;
+    if (c.E32n[0]) {
+        FieldsT<float> g;
+        for (int k = 0; k < 3; ++k) {
+            g.E[k] = c.E32n[k];
+            g.B[k] = c.B32n[k];
+        }
+        launch_fields32(P, S.k0r, S.shift, c.bw <= 0.0, f, g, c.Ji, ion, (float)P.dt, c.st);
+        std::swap(c.E32, c.E32n);
+        std::swap(c.B32, c.B32n);
+    } else {
+        launch_bhalf<float>(P, S.k0r, f, (float)P.dt, (float *)c.murbuf, c.st);  // B^(n-1/2) -> B^(n+1/2)
+        launch_eupdate<float, long long>(P, S.k0r, f, c.Ji, ion, (float)P.dt, c.st);
+        launch_mur_shift<float, long long>(P, S.k0r, S.shift, c.bw <= 0.0, f, (const float *)c.murbuf, nullptr,
+                                           (float)P.dt, c.st);
     }
-    c.cur32 = o;
-    return PIC_OK;
+    std::swap(c.jioni, c.jionn);
+    timing_end(c, 1, t4);
 }
 
 // ---------------------------------------------------------------- record mode export
@@ -1920,9 +1931,9 @@ pic_status split_check(Ctx &c) {
         pic_status s = upload_layout(c, sp, lay[sp], o);
         if (s != PIC_OK) return s;
     }
-    build_worklist(c, cur, X.s[0].ovf_cap, X.s[1].ovf_cap);
-    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.chunk, X.items, X.nitems, X.next, X.ios + 2 * cur,
-                       X.iids + 2 * cur, c.dflags);
+    build_worklist(c, cur, nullptr);
+    hipLaunchKernelGGL(k_rebin, dim3(X.grid), dim3(ST), 0, c.st, P, X.work, X.ios + 2 * cur, X.iids + 2 * cur,
+                       c.dflags);
     for (int sp = 0; sp < 2; ++sp) {
         pic_status s = upload_layout(c, sp, lay[sp], cur);
         if (s != PIC_OK) return s;

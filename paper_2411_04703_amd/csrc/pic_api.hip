@@ -31,6 +31,11 @@ static pic_status fail(std::string *err, pic_status s, const std::string &msg) {
 }
 
 // ---------------------------------------------------------------- derivation
+// FP32 grids up to this many cells hold E and B twice, so that a step updates them in one pass
+// (k_fields); 24 bytes a cell, 3.2 GB at the limit.  Larger grids keep the memory for cells and
+// update in place, in two passes and one over the faces.
+constexpr int64_t FIELDS_TWICE = (int64_t)1 << 27;
+
 struct Plan {
     Params P;
     pic_derived d;
@@ -250,8 +255,9 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         pl.cap_p = P.has_plasma ? fill : 0;
         for (int k = 0; k < 6; ++k) off[k] = take(4 * P.nc);  // E B float
         for (int k = 6; k < 9; ++k) off[k] = take(8 * P.nc);  // J int64
-        off[9] = take(8 * P.nz);
+        off[9] = take(2 * 8 * P.nz);  // jion, twice
         off[10] = take(4 * 8 * (uint64_t)P.plane);
+        if (P.nc <= FIELDS_TWICE) off[28] = take(6 * al256(4 * P.nc));  // E B of the next step
         // particle double buffers with bin slack and an overflow tail (k_split32.hip)
         int64_t nbins = P.nbins;
         // bin slack: the beam pinches and moves between re-layouts, so its bins get 1/2 of their count as
@@ -268,14 +274,12 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         uint64_t bins_bytes = 8 * (uint64_t)(nbins + 1) * 4 + 4 * (uint64_t)nbins * 4 + 256;
         off[13] = take(bins_bytes);
         pl.chunk = split_chunk(P, pl.cap_b + pl.cap_p);
-        int64_t items_cap = (cb + cp + pl.ovf_b + pl.ovf_p) / pl.chunk + 2 * nbins + 64;
-        uint64_t wl_bytes = 16 * (uint64_t)(P.nz + 8) + 256 + 16 * (uint64_t)items_cap + 8 * (uint64_t)((2 * nbins) / 512 + 16) +
-                            4 * (uint64_t)(2 * nbins + 8) + 8 * (uint64_t)(nbins + 8) + 4096 + 4096;
+        uint64_t wl_bytes = 16 * (uint64_t)(P.nz + 8) + 256 + split_items_bytes(P, cb, cp, pl.chunk) +
+                            4 * (uint64_t)(2 * nbins + 8) + 8 * (uint64_t)(nbins + 8) + 8192 + 4096;
         off[14] = take(wl_bytes);
         off[20] = cb;  // slot capacities (not offsets)
         off[21] = cp;
         off[23] = bins_bytes;
-        off[24] = items_cap;
     }
     int64_t nmax = std::max<int64_t>({pl.cap_b, pl.cap_p, P.nc, 1});
     off[15] = take(8 * 32 * (uint64_t)(nblocks(nmax, 256) + 16));  // reduction partials
@@ -361,7 +365,7 @@ static pic_status end_of_step_sheets(Ctx &c, const StepCtx &S) {
         if (c.sh_lo > c.sh_hi) c.sh_lo = c.sh_hi;
     }
     if (c.precision == PIC_FP64_PLAIN) return c.P.has_plasma ? inject_range64(c, l0, c.sh_hi, S.t1) : PIC_OK;
-    return split_inject_and_swap(c, l0, c.sh_hi, S.t1, S.k0n);  // FP32: append to the output bins, then swap
+    return split_tails_and_swap(c, S, l0, c.sh_hi);  // FP32: append to the output bins, then swap
 }
 
 static pic_status check_flags(Ctx &c) {
@@ -597,8 +601,13 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
             c->E32[k] = (float *)(A + off[k]);
             c->B32[k] = (float *)(A + off[3 + k]);
             c->Ji[k] = (long long *)(A + off[6 + k]);
+            if (off[28]) {
+                c->E32n[k] = (float *)(A + off[28] + k * al256(4 * P.nc));
+                c->B32n[k] = (float *)(A + off[28] + (3 + k) * al256(4 * P.nc));
+            }
         }
         c->jioni = (long long *)(A + off[9]);
+        c->jionn = c->jioni + P.nz;
         if (e == hipSuccess) e = hipMemsetAsync(A + off[0], 0, off[9] - off[0], c->st);
     }
     if (e != hipSuccess) {
@@ -653,7 +662,6 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->split_off_bins = off[13];
         c->split_bins_bytes = off[23];
         c->split_off_wl = off[14];
-        c->split_items_cap = (int64_t)off[24];
         c->split_chunk = pl.chunk;
         c->nb_slots = b->n_macro;  // ids: beam particle k is FP64 record slot k; plasma ids count up
         c->np_slots = 0;
@@ -703,12 +711,11 @@ pic_status pic_step(pic_ctx *c, int32_t nsteps) {
             s = step64(*c);
         } else {
             StepCtx S = make_step_ctx(*c);
-            split_step(*c, S);
+            split_push(*c, S);
             c->step += 1;
             c->k0 = S.k0n;
-            hipEvent_t ti = timing_begin(*c);
             s = end_of_step_sheets(*c, S);
-            timing_end(*c, 2, ti);
+            split_fields(*c, S);
             if (s == PIC_OK && c->step % c->check_every == 0) s = split_check(*c);
         }
         if (s == PIC_OK && c->probe_on) probe_step(*c);

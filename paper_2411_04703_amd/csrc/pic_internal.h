@@ -74,9 +74,10 @@ struct Ctx {
     // fields: FP64 mode uses E64/B64/J64, FP32 mode E32/B32 and J as int64 fixed point
     double *E64[3] = {}, *B64[3] = {}, *J64[3] = {};
     float *E32[3] = {}, *B32[3] = {};
+    float *E32n[3] = {}, *B32n[3] = {};  // the set the next step writes (null: updated in place)
     long long *Ji[3] = {};
     double *jion64 = nullptr;
-    long long *jioni = nullptr;
+    long long *jioni = nullptr, *jionn = nullptr;  // ion profile of the next step (zero between steps), of the last
     void *murbuf = nullptr;
 
     // particles
@@ -88,7 +89,7 @@ struct Ctx {
     int64_t ovf_cap_b = 0, ovf_cap_p = 0;
     // FP32 split mode: host-side state of the binned stores (k_split32.hip)
     void *split = nullptr;
-    int64_t split_slots_b = 0, split_slots_p = 0, split_items_cap = 0;
+    int64_t split_slots_b = 0, split_slots_p = 0;
     int split_chunk = 0;
     uint64_t split_off_b = 0, split_off_p = 0, split_off_bins = 0, split_bins_bytes = 0, split_off_wl = 0;
 
@@ -126,8 +127,10 @@ void launch_mur_shift(const Params &P, int k0r, int shift, int front_mur, Fields
                       T dt, hipStream_t st);
 void launch_ion64(const Params &P, int64_t sh_lo, int64_t nsheets, double t0, double t1, int64_t k0, double *jion,
                   hipStream_t st);
+void launch_fields32(const Params &P, int k0r, int shift, int front_mur, FieldsT<float> f, FieldsT<float> g,
+                     long long *J[3], const long long *jion, float dt, hipStream_t st);
 void launch_ion_fixed(const Params &P, int64_t sh_lo, int64_t nsheets, double t0, double t1, int64_t k0,
-                      long long *jion, int32_t *flags, hipStream_t st);
+                      long long *jion, long long *next, int32_t *flags, hipStream_t st);
 
 // FP64 plain particles (k_plain64.hip)
 void launch_beam_init64(const Params &P, const double *normals, int64_t n, const double sig[5], double gB,
@@ -147,14 +150,16 @@ void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma
 void split_setup(Ctx &c);
 bool split_tile_supported(int tx, int ty, int tz);  // tiles the FP32 step kernel is built for
 int split_chunk(const Params &P, int64_t n);         // particles per work item of the FP32 step
+uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, int chunk);
 uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint64_t bins_bytes, int record);
 void split_export64(const Ctx &c, Part64 beam, Part64 plasma, hipStream_t st);  // record mode: particles to slots
 pic_status split_copy_state(Ctx &c, char *dev, bool save);  // snapshot <-> context (device buffer)
 void split_free(Ctx &c);
 void split_beam_init(Ctx &c, const double *normals_dev);
 pic_status split_plasma_fill(Ctx &c);  // also builds the initial bins of both species
-void split_step(Ctx &c, const StepCtx &S);
-pic_status split_inject_and_swap(Ctx &c, int64_t l0, int64_t l1, double t, int64_t k0n);
+void split_push(Ctx &c, const StepCtx &S);    // particles and currents of a step
+void split_fields(Ctx &c, const StepCtx &S);  // then E and B
+pic_status split_tails_and_swap(Ctx &c, const StepCtx &S, int64_t l0, int64_t l1);
 pic_status split_check(Ctx &c);  // bin capacity check + re-layout (synchronising)
 void split_read(Ctx &c, int species, double *dst7, int32_t *alive, int64_t *n);
 void split_probe(Ctx &c, double *acc);  // lab-frame probe over the binned beam
