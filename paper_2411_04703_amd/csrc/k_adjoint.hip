@@ -688,7 +688,7 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
                        nE[1], nE[2]);
     // ion current: n0 dL/dn0 += <lam_Jz, J_ion>
     Sum2 gn{0.0, 0.0}, gK{0.0, 0.0};
-    Sum2 *const part = (Sum2 *)c.red;
+    Sum2 *const part = (Sum2 *)c.adj_part;
     if (P.ions && c.sh_hi > c.sh_lo) {
         launch_ion64(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jion64, c.st);
         hipLaunchKernelGGL(k_ion_dot, dim3(256), dim3(AT), 0, c.st, P, S.k0r, c.J64[2], c.jion64, part);
@@ -702,7 +702,7 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
     const Species64 b{c.b64.x, (int64_t)cb, c.nb_slots}, p{c.p64.x, (int64_t)cp, c.np_slots};
     const int64_t n = b.n + p.n;
     if (n > 0) {
-        const int grid = c.ncu;
+        const int grid = std::min(c.ncu, 512);
         const bool flat = tiles64_flat(P);
         tiles64_build(c, b, p, grid);
         hipLaunchKernelGGL(k_adj_dead, dim3(nblocks(n, AT)), dim3(AT), 0, c.st, n, c.tiles.key, b.n, Lb.x[0], b.cap,

@@ -285,6 +285,7 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
     off[15] = take(8 * 32 * (uint64_t)(nblocks(nmax, 256) + 16));  // reduction partials
     off[16] = take(8 * P.nc);                                       // previous Gauss residual
     off[17] = pl.record ? take(8 * 6 * P.nc) : 0;                   // adjoint scratch
+    off[29] = pl.record ? take(16 * (uint64_t)ADJ_PARTS) : 0;       // its partial sums
     off[18] = take(8 * 6 * (uint64_t)std::max<int64_t>(b->n_macro, 1));  // normals staging
     off[19] = take(256);                                            // device flags + lab-probe sums
     off[22] = take(8 * 2 * (uint64_t)(nblocks(nmax, 256) + 4));     // scan scratch
@@ -571,6 +572,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
     c->red_cap = (int64_t)(32 * (nblocks(std::max<int64_t>({pl.cap_b, pl.cap_p, P.nc, 1}), 256) + 16));
     c->rprev = (double *)(A + off[16]);
     c->adj = pl.record ? (double *)(A + off[17]) : nullptr;
+    c->adj_part = pl.record ? A + off[29] : nullptr;
     c->stage = (double *)(A + off[18]);
     c->dflags = (int32_t *)(A + off[19]);
     c->probe_acc = (double *)(A + off[19] + 64);  // same 256-byte block: flags, then the probe's sums

@@ -41,6 +41,9 @@ struct TileList {
     int4 *items;            // (bin, first entry, end entry, 0): at most `chunk` particles of one bin
     int32_t *nitems, *qnext;
 };
+// partial sums of a reverse step: one of each of 256 workgroups, two of each of up to 512
+enum : int { ADJ_PARTS = 256 + 2 * 512 };
+
 struct Ctx {
     Params P;
     int precision = 0, record = 0, device = 0, check_every = 64;
@@ -100,6 +103,7 @@ struct Ctx {
     int64_t rprev_k0 = 0;
     int have_rprev = 0;
     double *adj = nullptr;       // adjoint scratch: lEn[3], Bn[3]
+    void *adj_part = nullptr;    // and its partial sums, ADJ_PARTS of 16 bytes
     double *stage = nullptr;     // normals staging (init)
     int32_t *dflags = nullptr;   // device error flags
     int64_t *i64scratch = nullptr;
