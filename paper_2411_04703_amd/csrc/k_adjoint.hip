@@ -127,9 +127,17 @@ __global__ void __launch_bounds__(AT) k_adj_e(Params P, int k0r, int shift, int 
     lBz[o] += dt * (e[0] - ex_j1 - e[1] + ey_i1);
 }
 
-// lam_E += transpose of (B <- B - h curl E) applied to lam_B
+// The step's last pass: the new lam_E to its place, and the scratch in J and the ion profile cleared.
+struct AdjLast {
+    double *lE[3], *J[3], *jion;
+};
+
+// lam_E += transpose of (B <- B - h curl E) applied to lam_B.  LAST: into its place, with what goes with
+// it (one pass for this one, three copies and four fills).
+template <bool LAST>
 __global__ void __launch_bounds__(AT) k_adj_bhalf(Params P, int k0r, double h, const double *lBx, const double *lBy,
-                                                  const double *lBz, double *nEx, double *nEy, double *nEz) {
+                                                  const double *lBz, double *nEx, double *nEy, double *nEz,
+                                                  AdjLast A) {
     int64_t o = (int64_t)blockIdx.x * AT + threadIdx.x;
     if (o >= P.nc) return;
     int i, j, p;
@@ -140,9 +148,14 @@ __global__ void __launch_bounds__(AT) k_adj_bhalf(Params P, int k0r, double h, c
         return a[cell_index(P, ii, jj, ring_plane(ll, k0r, P.nz))];
     };
     auto bz = [&](int ii, int jj, int ll) -> double { return lBz[cell_index(P, ii, jj, ring_plane(ll, k0r, P.nz))]; };
-    nEx[o] += h * (bxy(lBy, i, j, l) - bxy(lBy, i, j, l - 1) - bz(i, j, l) + bz(i, j - 1, l));
-    nEy[o] += h * (bz(i, j, l) - bz(i - 1, j, l) - bxy(lBx, i, j, l) + bxy(lBx, i, j, l - 1));
-    nEz[o] += h * (bxy(lBx, i, j, l) - bxy(lBx, i, j - 1, l) - bxy(lBy, i, j, l) + bxy(lBy, i - 1, j, l));
+    double *d[3] = {LAST ? A.lE[0] : nEx, LAST ? A.lE[1] : nEy, LAST ? A.lE[2] : nEz};
+    d[0][o] = nEx[o] + h * (bxy(lBy, i, j, l) - bxy(lBy, i, j, l - 1) - bz(i, j, l) + bz(i, j - 1, l));
+    d[1][o] = nEy[o] + h * (bz(i, j, l) - bz(i - 1, j, l) - bxy(lBx, i, j, l) + bxy(lBx, i, j, l - 1));
+    d[2][o] = nEz[o] + h * (bxy(lBx, i, j, l) - bxy(lBx, i, j - 1, l) - bxy(lBy, i, j, l) + bxy(lBy, i - 1, j, l));
+    if (LAST) {
+        for (int k = 0; k < 3; ++k) A.J[k][o] = 0.0;
+        if (o < P.nz) A.jion[o] = 0.0;
+    }
 }
 
 __global__ void k_zero_plane(int64_t plane, int p, double *a0, double *a1, double *a2, double *b0, double *b1,
@@ -665,14 +678,13 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
     if (np1 > c.np_slots)
         hipLaunchKernelGGL(k_zero_slots, dim3(nblocks(np1 - c.np_slots, AT)), dim3(AT), 0, c.st, Lp, c.np_slots, np1);
     // B^n = B^{n-1/2} - (dt/2) curl E^n
-    for (int k = 0; k < 3; ++k)
-        PIC_HIP(c, hipMemcpyAsync(Bn[k], c.B64[k], 8 * P.nc, hipMemcpyDeviceToDevice, c.st));
-    FieldsT<double> fn;
+    FieldsT<double> f, fn;
     for (int k = 0; k < 3; ++k) {
-        fn.E[k] = c.E64[k];
+        f.E[k] = fn.E[k] = c.E64[k];
+        f.B[k] = c.B64[k];
         fn.B[k] = Bn[k];
     }
-    launch_bhalf<double>(P, S.k0r, fn, 0.5 * P.dt, nullptr, c.st);
+    launch_bhalf<double>(P, S.k0r, f, fn, 0.5 * P.dt, nullptr, c.st);
     // window shift: the back plane became the empty front plane
     if (S.shift)
         hipLaunchKernelGGL(k_zero_plane, dim3(nblocks(P.plane, 256)), dim3(256), 0, c.st, (int64_t)P.plane, S.k0r,
@@ -684,19 +696,17 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
                        lE[2], nE[0], nE[1],
                        nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1], c.J64[2]);
     // second half step
-    hipLaunchKernelGGL(k_adj_bhalf, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2], nE[0],
-                       nE[1], nE[2]);
-    // ion current: n0 dL/dn0 += <lam_Jz, J_ion>
-    Sum2 gn{0.0, 0.0}, gK{0.0, 0.0};
+    const AdjLast last{{lE[0], lE[1], lE[2]}, {c.J64[0], c.J64[1], c.J64[2]}, c.jion64};
+    hipLaunchKernelGGL(k_adj_bhalf<false>, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2],
+                       nE[0], nE[1], nE[2], last);
+    // the partial sums, read back together at the end: the ions' (none: zero), then the particles'
     Sum2 *const part = (Sum2 *)c.adj_part;
+    int parts = 0, ion_parts = 0;
+    // ion current: n0 dL/dn0 += <lam_Jz, J_ion>
     if (P.ions && c.sh_hi > c.sh_lo) {
         launch_ion64(P, c.sh_lo, c.sh_hi - c.sh_lo, S.t, S.t1, S.k0, c.jion64, c.st);
-        hipLaunchKernelGGL(k_ion_dot, dim3(256), dim3(AT), 0, c.st, P, S.k0r, c.J64[2], c.jion64, part);
-        std::vector<Sum2> h(256);
-        PIC_HIP(c, hipMemcpyAsync(h.data(), part, sizeof(Sum2) * 256, hipMemcpyDeviceToHost, c.st));
-        PIC_HIP(c, hipMemsetAsync(c.jion64, 0, 8 * P.nz, c.st));
-        PIC_HIP(c, hipStreamSynchronize(c.st));
-        for (const Sum2 &v : h) gn.add(v.hi, v.lo);
+        parts = ion_parts = 256;
+        hipLaunchKernelGGL(k_ion_dot, dim3(ion_parts), dim3(AT), 0, c.st, P, S.k0r, c.J64[2], c.jion64, part);
     }
     // particles
     const Species64 b{c.b64.x, (int64_t)cb, c.nb_slots}, p{c.p64.x, (int64_t)cp, c.np_slots};
@@ -710,28 +720,25 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
         const Bounds64 W(P, S.k0, S.k0n);
         auto launch = [&](auto kernel, int lds) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(PT), lds, c.st, P, S, W, b, p, c.tiles, Lb.x[0], Lp.x[0], fn,
-                               nE[0], nE[1], nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1], c.J64[2], part);
+                               nE[0], nE[1], nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1], c.J64[2], part + ion_parts);
         };
         if (flat)
             launch(k_adj_particles<Geom2D>, adj_lds<Geom2D>());
         else
             launch(k_adj_particles<Geom3D>, adj_lds<Geom3D>());
-        std::vector<Sum2> h(2 * (size_t)grid);
-        PIC_HIP(c, hipMemcpyAsync(h.data(), part, sizeof(Sum2) * h.size(), hipMemcpyDeviceToHost, c.st));
-        PIC_HIP(c, hipStreamSynchronize(c.st));
-        for (int k = 0; k < grid; ++k) {
-            gK.add(h[2 * k].hi, h[2 * k].lo);
-            gn.add(h[2 * k + 1].hi, h[2 * k + 1].lo);
-        }
+        parts += 2 * grid;
     }
     // first half step, then the new lam_E
-    hipLaunchKernelGGL(k_adj_bhalf, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2], nE[0],
-                       nE[1], nE[2]);
-    for (int k = 0; k < 3; ++k) {
-        PIC_HIP(c, hipMemcpyAsync(lE[k], nE[k], 8 * P.nc, hipMemcpyDeviceToDevice, c.st));
-        PIC_HIP(c, hipMemsetAsync(c.J64[k], 0, 8 * P.nc, c.st));
-    }
+    hipLaunchKernelGGL(k_adj_bhalf<true>, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2],
+                       nE[0], nE[1], nE[2], last);
+    Sum2 h[ADJ_PARTS], gn{0.0, 0.0}, gK{0.0, 0.0};
+    if (parts) PIC_HIP(c, hipMemcpyAsync(h, part, sizeof(Sum2) * parts, hipMemcpyDeviceToHost, c.st));
     PIC_HIP(c, hipStreamSynchronize(c.st));
+    for (int k = 0; k < ion_parts; ++k) gn.add(h[k].hi, h[k].lo);
+    for (int k = ion_parts; k < parts; k += 2) {
+        gK.add(h[k].hi, h[k].lo);
+        gn.add(h[k + 1].hi, h[k + 1].lo);
+    }
     grad[0] += gK.value();
     grad[1] += gn.value();
     return PIC_OK;

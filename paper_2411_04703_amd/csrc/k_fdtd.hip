@@ -31,8 +31,9 @@ __device__ inline bool plane_cell(const Params &P, int &i, int &j) {
     return true;
 }
 
+// g: where the new B goes (f itself, or another set beside E)
 template <typename T>
-__global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, T h, T *murbuf) {
+__global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf) {
     int i, j;
     if (!plane_cell(P, i, j)) return;
     const int p = (int)blockIdx.y;
@@ -43,12 +44,15 @@ __global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, 
     int64_t oj = o + ((j + 1 == P.ny) ? (int64_t)(1 - P.ny) * P.nx : P.nx);
     const T *Ex = f.E[0], *Ey = f.E[1], *Ez = f.E[2];
     T ex = Ex[o], ey = Ey[o], ez = Ez[o];
+    T bx = f.B[0][o], by = f.B[1][o];
     if (l != P.nz - 1) {
         int64_t ol = o + ((p + 1 == P.nz) ? -(int64_t)(P.nz - 1) * P.plane : (int64_t)P.plane);
-        f.B[0][o] -= h * ((Ez[oj] - ez) - (Ey[ol] - ey));
-        f.B[1][o] -= h * ((Ex[ol] - ex) - (Ez[oi] - ez));
+        bx -= h * ((Ez[oj] - ez) - (Ey[ol] - ey));
+        by -= h * ((Ex[ol] - ex) - (Ez[oi] - ez));
     }
-    f.B[2][o] -= h * ((Ey[oi] - ey) - (Ex[oj] - ex));
+    g.B[0][o] = bx;
+    g.B[1][o] = by;
+    g.B[2][o] = f.B[2][o] - h * ((Ey[oi] - ey) - (Ex[oj] - ex));
     if (murbuf) {
         int q = l == 0 ? 0 : l == 1 ? 1 : l == P.nz - 2 ? 2 : l == P.nz - 1 ? 3 : -1;
         if (q >= 0) {
@@ -202,8 +206,8 @@ void launch_fields32(const Params &P, int k0r, int shift, int front_mur, FieldsT
 }
 
 template <typename T>
-void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, T h, T *murbuf, hipStream_t st) {
-    hipLaunchKernelGGL(k_bhalf<T>, dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, f, h, murbuf);
+void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf, hipStream_t st) {
+    hipLaunchKernelGGL(k_bhalf<T>, dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, f, g, h, murbuf);
 }
 
 template <typename T, typename JT>
@@ -221,8 +225,8 @@ void launch_mur_shift(const Params &P, int k0r, int shift, int front_mur, Fields
                        murbuf, jion, cm);
 }
 
-template void launch_bhalf<double>(const Params &, int, FieldsT<double>, double, double *, hipStream_t);
-template void launch_bhalf<float>(const Params &, int, FieldsT<float>, float, float *, hipStream_t);
+template void launch_bhalf<double>(const Params &, int, FieldsT<double>, FieldsT<double>, double, double *, hipStream_t);
+template void launch_bhalf<float>(const Params &, int, FieldsT<float>, FieldsT<float>, float, float *, hipStream_t);
 template void launch_eupdate<double, double>(const Params &, int, FieldsT<double>, double *[3], const double *,
                                              double, hipStream_t);
 template void launch_eupdate<float, long long>(const Params &, int, FieldsT<float>, long long *[3],

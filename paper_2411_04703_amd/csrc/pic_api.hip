@@ -423,7 +423,7 @@ static pic_status step64(Ctx &c) {
     }
     const Params &P = c.P;
     hipEvent_t t0 = timing_begin(c);
-    launch_bhalf<double>(P, S.k0r, f, 0.5 * P.dt, nullptr, c.st);
+    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, nullptr, c.st);
     timing_end(c, 1, t0);
     hipEvent_t t1 = timing_begin(c);
     step64_particles(c, S, f);
@@ -433,7 +433,7 @@ static pic_status step64(Ctx &c) {
     launch_neutraliser_current(c, S);
     timing_end(c, 2, t2);
     hipEvent_t t3 = timing_begin(c);
-    launch_bhalf<double>(P, S.k0r, f, 0.5 * P.dt, (double *)c.murbuf, c.st);
+    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, (double *)c.murbuf, c.st);
     launch_eupdate<double, double>(P, S.k0r, f, c.J64, c.jion64, P.dt, c.st);
     launch_mur_shift<double, double>(P, S.k0r, S.shift, c.bw <= 0.0, f, (const double *)c.murbuf, c.jion64, P.dt,
                                      c.st);

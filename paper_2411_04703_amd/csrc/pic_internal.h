@@ -123,7 +123,7 @@ void timing_end(Ctx &c, int cls, hipEvent_t start);
 // ---------------------------------------------------------------- launchers
 // FDTD (k_fdtd.hip)
 template <typename T>
-void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, T h, T *murbuf, hipStream_t st);
+void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf, hipStream_t st);
 template <typename T, typename JT>
 void launch_eupdate(const Params &P, int k0r, FieldsT<T> f, JT *J[3], const JT *jion, T dt, hipStream_t st);
 template <typename T, typename JT>
