@@ -1357,7 +1357,7 @@ void split_setup(Ctx &c) {
         int64_t slots = s.bin_slots + s.ovf_cap;
         char *b = A + (sp ? c.split_off_p : c.split_off_b);
         for (int k = 0; k < 2; ++k) {
-            char *bk = b + k * slot_bytes(c) * (uint64_t)slots;
+            char *bk = b + k * split_buffer_bytes(slot_bytes(c), slots);
             s.buf[k] = carve32(bk, slots);
             s.id[k] = c.record ? (int32_t *)(bk + 32 * (uint64_t)slots) : nullptr;
         }
@@ -1847,25 +1847,15 @@ uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint6
     return 6 * a256(4 * (uint64_t)nc) + a256(sb * (uint64_t)slots_b) + a256(sb * (uint64_t)slots_p) + a256(bins_bytes);
 }
 
-pic_status split_copy_state(Ctx &c, char *dev, bool save) {
+void split_state_pieces(Ctx &c, StatePieces &s) {
     SplitState &X = SS(c);
-    uint64_t o = 0;
-    auto mv = [&](void *mine, uint64_t bytes) -> pic_status {
-        PIC_HIP(c, hipMemcpyAsync(save ? dev + o : mine, save ? (const void *)mine : (const void *)(dev + o), bytes,
-                                  hipMemcpyDeviceToDevice, c.st));
-        o += a256(bytes);
-        return PIC_OK;
-    };
-    pic_status st;
-    for (int k = 0; k < 3; ++k)
-        if ((st = mv(c.E32[k], 4 * (uint64_t)c.P.nc)) != PIC_OK) return st;
-    for (int k = 0; k < 3; ++k)
-        if ((st = mv(c.B32[k], 4 * (uint64_t)c.P.nc)) != PIC_OK) return st;
+    for (int k = 0; k < 3; ++k) s.add(c.E32[k], 4 * (uint64_t)c.P.nc);
+    for (int k = 0; k < 3; ++k) s.add(c.B32[k], 4 * (uint64_t)c.P.nc);
     for (int sp = 0; sp < 2; ++sp) {
         Store &S = X.s[sp];
-        if ((st = mv(S.buf[c.cur32].cell, slot_bytes(c) * (uint64_t)(S.bin_slots + S.ovf_cap))) != PIC_OK) return st;
+        s.add(S.buf[c.cur32].cell, slot_bytes(c) * (uint64_t)(S.bin_slots + S.ovf_cap));
     }
-    return mv(c.arena + c.split_off_bins, c.split_bins_bytes);
+    s.add(c.arena + c.split_off_bins, c.split_bins_bytes);
 }
 
 // periodic host check: re-lay out the bins when any overflowed or is nearly full

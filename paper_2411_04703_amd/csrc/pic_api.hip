@@ -269,8 +269,8 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         pl.ovf_p = std::max<int64_t>(8192, pl.cap_p / 8);
         pl.cap_b = b->n_macro;
         const uint64_t sb = pl.record ? 36 : 32;  // record mode: + the particle id
-        off[11] = take(sb * (uint64_t)(cb + pl.ovf_b) * 2);
-        off[12] = take(sb * (uint64_t)(cp + pl.ovf_p) * 2);
+        off[11] = take(2 * split_buffer_bytes(sb, cb + pl.ovf_b));
+        off[12] = take(2 * split_buffer_bytes(sb, cp + pl.ovf_p));
         uint64_t bins_bytes = 8 * (uint64_t)(nbins + 1) * 4 + 4 * (uint64_t)nbins * 4 + 256;
         off[13] = take(bins_bytes);
         pl.chunk = split_chunk(P, pl.cap_b + pl.cap_p);
@@ -968,53 +968,87 @@ struct StateHeader {
     double bw, win_x0, win_t0;
 };
 
+static StatePieces state_pieces(Ctx &c) {
+    StatePieces s;
+    if (c.precision == PIC_FP64_PLAIN) {
+        s.add(c.E64[0], 8 * 6 * (uint64_t)c.P.nc);
+        s.add(c.b64.x, 60 * (uint64_t)std::max<int64_t>(c.cap_b, 1));
+        s.add(c.p64.x, 60 * (uint64_t)std::max<int64_t>(c.cap_p, 1));
+    } else {
+        split_state_pieces(c, s);
+    }
+    return s;
+}
+
+// One launch for a whole snapshot: a copy of each piece and the header by itself took some 10 us each
+// (0.1 ms of a small run's restore; the large ones run at the copy rate either way).  A workgroup moves 16
+// KB a round, four loads of a thread in flight; every piece starts on 16 bytes and is a multiple of 4.
+__global__ void __launch_bounds__(256) k_state_copy(StatePieces s, char *dev, int save, StateHeader h) {
+    const uint64_t t = threadIdx.x;
+    if (save && blockIdx.x == 0 && t == 0) *(StateHeader *)dev = h;
+    for (int k = 0; k < s.n; ++k) {
+        const char *src = save ? s.mine[k] : dev + s.at[k];
+        char *dst = save ? dev + s.at[k] : s.mine[k];
+        const uint64_t n16 = s.bytes[k] / 16;
+        const uint4 *a = (const uint4 *)src;
+        uint4 *b = (uint4 *)dst;
+        for (uint64_t i = (uint64_t)blockIdx.x * 1024 + t; i - t < n16; i += (uint64_t)gridDim.x * 1024) {
+            if (i - t + 1024 <= n16) {
+                const uint4 v0 = a[i], v1 = a[i + 256], v2 = a[i + 512], v3 = a[i + 768];
+                b[i] = v0;
+                b[i + 256] = v1;
+                b[i + 512] = v2;
+                b[i + 768] = v3;
+            } else {
+                for (uint64_t e = i; e < n16; e += 256) b[e] = a[e];
+            }
+        }
+        if (blockIdx.x == 0 && t < (s.bytes[k] - 16 * n16) / 4)
+            ((uint32_t *)(dst + 16 * n16))[t] = ((const uint32_t *)(src + 16 * n16))[t];
+    }
+}
+
+// the pieces between the context and a snapshot; one by one where the caller's buffer is not on 16 bytes
+static pic_status copy_state(Ctx &c, char *dev, const StateHeader *save) {
+    const StatePieces s = state_pieces(c);
+    if (((uintptr_t)dev & 15) == 0) {
+        uint64_t bytes = 0;
+        for (int k = 0; k < s.n; ++k) bytes += s.bytes[k];
+        const dim3 grid((unsigned)std::min<uint64_t>(std::max<uint64_t>(bytes / (64 * 256), 1), 8192));
+        hipLaunchKernelGGL(k_state_copy, grid, dim3(256), 0, c.st, s, dev, save != nullptr,
+                           save ? *save : StateHeader{});
+        PIC_HIP(c, hipGetLastError());
+        return PIC_OK;
+    }
+    if (save) PIC_HIP(c, hipMemcpyAsync(dev, save, sizeof *save, hipMemcpyHostToDevice, c.st));
+    for (int k = 0; k < s.n; ++k)
+        PIC_HIP(c, hipMemcpyAsync(save ? dev + s.at[k] : s.mine[k], save ? s.mine[k] : dev + s.at[k], s.bytes[k],
+                                  hipMemcpyDeviceToDevice, c.st));
+    return PIC_OK;
+}
+
 pic_status pic_get_state(pic_ctx *c, void *dst) {
     if (!c || !dst) return PIC_EINVAL;
-    char *d = (char *)dst;
-    StateHeader h = {0x5049435354415445ull, c->state_bytes, c->step, c->k0, c->sh_lo, c->sh_hi,
-                     c->nb_slots, c->np_slots, c->cur32, c->precision, c->bw, c->win_x0, c->win_t0};
-    PIC_HIP(*c, hipMemcpyAsync(d, &h, sizeof h, hipMemcpyHostToDevice, c->st));
-    uint64_t o = 256;
-    const Params &P = c->P;
-    if (c->precision == PIC_FP64_PLAIN) {
-        PIC_HIP(*c, hipMemcpyAsync(d + o, c->E64[0], 8 * 6 * P.nc, hipMemcpyDeviceToDevice, c->st));
-        o += al256(8 * 6 * P.nc);
-        uint64_t bb = 60 * (uint64_t)std::max<int64_t>(c->cap_b, 1), pb = 60 * (uint64_t)std::max<int64_t>(c->cap_p, 1);
-        PIC_HIP(*c, hipMemcpyAsync(d + o, c->b64.x, bb, hipMemcpyDeviceToDevice, c->st));
-        o += al256(bb);
-        PIC_HIP(*c, hipMemcpyAsync(d + o, c->p64.x, pb, hipMemcpyDeviceToDevice, c->st));
-    } else {
-        pic_status st = split_copy_state(*c, d + o, true);
-        if (st != PIC_OK) return st;
-    }
+    const StateHeader h = {0x5049435354415445ull, c->state_bytes, c->step, c->k0, c->sh_lo, c->sh_hi,
+                           c->nb_slots, c->np_slots, c->cur32, c->precision, c->bw, c->win_x0, c->win_t0};
+    pic_status st = copy_state(*c, (char *)dst, &h);
+    if (st != PIC_OK) return st;
     PIC_HIP(*c, hipStreamSynchronize(c->st));
     return PIC_OK;
 }
 
 pic_status pic_set_state(pic_ctx *c, const void *src) {
     if (!c || !src) return PIC_EINVAL;
-    const char *d = (const char *)src;
     StateHeader h;
-    PIC_HIP(*c, hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, c->st));
+    PIC_HIP(*c, hipMemcpyAsync(&h, src, sizeof h, hipMemcpyDeviceToHost, c->st));
     PIC_HIP(*c, hipStreamSynchronize(c->st));
     if (h.magic != 0x5049435354415445ull || h.bytes != c->state_bytes || h.precision != c->precision) {
         c->err = "pic_set_state: snapshot does not belong to this configuration";
         return PIC_ESTATE;
     }
-    const Params &P = c->P;
-    uint64_t o = 256;
-    if (c->precision == PIC_FP64_PLAIN) {
-        PIC_HIP(*c, hipMemcpyAsync(c->E64[0], d + o, 8 * 6 * P.nc, hipMemcpyDeviceToDevice, c->st));
-        o += al256(8 * 6 * P.nc);
-        uint64_t bb = 60 * (uint64_t)std::max<int64_t>(c->cap_b, 1), pb = 60 * (uint64_t)std::max<int64_t>(c->cap_p, 1);
-        PIC_HIP(*c, hipMemcpyAsync(c->b64.x, d + o, bb, hipMemcpyDeviceToDevice, c->st));
-        o += al256(bb);
-        PIC_HIP(*c, hipMemcpyAsync(c->p64.x, d + o, pb, hipMemcpyDeviceToDevice, c->st));
-    } else {
-        c->cur32 = h.cur32;  // the snapshot's particles go to the buffer they came from
-        pic_status st = split_copy_state(*c, (char *)d + o, false);
-        if (st != PIC_OK) return st;
-    }
+    if (c->precision != PIC_FP64_PLAIN) c->cur32 = h.cur32;  // the particles go to the buffer they came from
+    pic_status st = copy_state(*c, (char *)src, nullptr);
+    if (st != PIC_OK) return st;
     c->step = h.step;
     c->k0 = h.k0;
     c->sh_lo = h.sh_lo;

@@ -157,7 +157,23 @@ int split_chunk(const Params &P, int64_t n);         // particles per work item 
 uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, int chunk);
 uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint64_t bins_bytes, int record);
 void split_export64(const Ctx &c, Part64 beam, Part64 plasma, hipStream_t st);  // record mode: particles to slots
-pic_status split_copy_state(Ctx &c, char *dev, bool save);  // snapshot <-> context (device buffer)
+// A snapshot's pieces, in the context and in the snapshot's buffer (256-byte steps), copied by one launch.
+struct StatePieces {
+    enum { MOST = 10 };
+    char *mine[MOST];
+    uint64_t at[MOST], bytes[MOST];
+    int n = 0;
+    uint64_t end = 256;  // after the header
+    void add(void *p, uint64_t b) {
+        mine[n] = (char *)p;
+        at[n] = end;
+        bytes[n++] = b;
+        end += (b + 255) & ~(uint64_t)255;
+    }
+};
+void split_state_pieces(Ctx &c, StatePieces &s);
+// one of a species' two particle buffers (each starts on 16 bytes: a snapshot is copied in those)
+inline uint64_t split_buffer_bytes(uint64_t slot, int64_t slots) { return (slot * (uint64_t)slots + 15) & ~(uint64_t)15; }
 void split_free(Ctx &c);
 void split_beam_init(Ctx &c, const double *normals_dev);
 pic_status split_plasma_fill(Ctx &c);  // also builds the initial bins of both species
