@@ -49,12 +49,17 @@ struct Store {
     int64_t n_flat;        // init only
 };
 
-// The work list of a step: items (species, bin, first particle, bin count), one for every chunk of every
-// non-empty bin of the input buffer.  The bins form nslab slabs of whole z layers (one per XCD when they
+// A work item: particles [start, end) of a bin, which are the input slots from b0 on.
+struct alignas(32) Item {
+    int sp, bin, start, end;
+    int64_t b0;
+};
+
+// The work list of a step: one item for every chunk of every non-empty bin of the input buffer.  The bins form nslab slabs of whole z layers (one per XCD when they
 // divide evenly; bins are numbered z-major); queue 2 s + species holds slab s's items of a species, in
 // a region of its own, count[q] of them.
 struct WorkList {
-    int4 *items;
+    Item *items;
     int32_t *count, *count_next;  // count_next: the following list's, cleared when this one is built
     int32_t *next;                // claimed items of each queue (stride QPAD)
     int nslab, chunk, cap[2];     // cap: most items of a queue, by species
@@ -822,7 +827,8 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
     using G = TileGeom<TX, TY, TZ>;
     constexpr int SST = G::NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_item, s_count[16];
+    __shared__ Item s_next;
+    __shared__ int s_count[16];
     const int tid = threadIdx.x, nq = 2 * W.nslab;
     if (tid < nq) s_count[tid] = W.count[tid];  // constant during the launch
     float *Fs = (float *)smem;
@@ -836,32 +842,34 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
     __syncthreads();
 
     // Work queues: a slab's beam, whose large bins take longest, then its plasma; this workgroup's
-    // XCD's slab first, then the others' (work stealing).  Thread 0 keeps one claim on queue q in
-    // flight: the counter value for the item after the current one, claimed when the current one
-    // starts and resolved when it ends, so the atomic's round trip is hidden behind the item's work.
+    // XCD's slab first, then the others' (work stealing).  At an item's end thread 0 claims the next
+    // one, loads it and leaves it in s_next: one load for all of it where every thread loading its own
+    // took two, one after the other (128 x 128 x 512: 1138 -> 1097 us; 2048 x 1 x 4096: 1186 -> 1133).
+    // Claiming when the last round starts, to hide the atomic, cost registers in the rounds and gave
+    // 1104 and 1266 us.
     int q = 2 * (int)(blockIdx.x % (unsigned)W.nslab), hops = 0, claim = 0;
-    auto resolve = [&]() -> int {  // thread 0: the claimed item, or the next queue's, or -1
+    auto resolve = [&]() -> Item {  // thread 0: the claimed item, or the next queue's, or none (end 0)
         while (claim >= s_count[q]) {
             do {
                 q = q + 1 == nq ? 0 : q + 1;
-                if (++hops >= nq) return -1;
+                if (++hops >= nq) return Item{};
             } while (s_count[q] == 0);
             claim = atomicAdd(&W.next[q * QPAD], 1);
         }
-        return W.base(q) + claim;
+        return W.items[W.base(q) + claim];
     };
-    auto decode = [&](int item) -> ItemT {
+    auto decode = [&]() -> ItemT {
         ItemT I;
-        const int4 it = W.items[item];
-        I.sp = __builtin_amdgcn_readfirstlane(it.x);
-        I.bin = __builtin_amdgcn_readfirstlane(it.y);
-        I.start = __builtin_amdgcn_readfirstlane(it.z);
-        const int cnt = __builtin_amdgcn_readfirstlane(it.w);
-        I.end = min(cnt, I.start + W.chunk);
+        I.sp = __builtin_amdgcn_readfirstlane(s_next.sp);
+        I.bin = __builtin_amdgcn_readfirstlane(s_next.bin);
+        I.start = __builtin_amdgcn_readfirstlane(s_next.start);
+        I.end = __builtin_amdgcn_readfirstlane(s_next.end);
         I.t0x = (I.bin % P.ntx) * TX;
         I.t0y = ((I.bin / P.ntx) % P.nty) * TY;
         I.t0z = (I.bin / (P.ntx * P.nty)) * TZ;
-        I.b0 = gbl(iop.s[I.sp].in_off)[I.bin];
+        const int64_t b0 = s_next.b0;
+        I.b0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b0 >> 32)) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)b0));
         return I;
     };
     // E^n and B^(n-1/2) of an item's tile (box node (a, b, c) <-> absolute node
@@ -934,20 +942,17 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
 
     if (tid == 0) {
         if (s_count[q] > 0) claim = atomicAdd(&W.next[q * QPAD], 1);
-        const int first = resolve();
-        s_item = first;
+        s_next = resolve();
     }
     __syncthreads();
-    int cur = __builtin_amdgcn_readfirstlane(s_item);
-    ItemT I{};
+    ItemT I = decode();
     PRaw nx;  // this thread's particle of the next round
-    if (cur >= 0) {
-        I = decode(cur);
+    if (I.end > 0) {
         stage(I);
         if (I.start + tid < I.end) load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
     }
 
-    while (cur >= 0) {
+    while (I.end > 0) {
         // the staged boxes have landed, and the previous item's flush has cleared the current boxes
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -962,9 +967,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
             Bs[G::NE + k] += B3[1];
             Bs[2 * G::NE + k] += B3[2];
         }
-        __syncthreads();  // (also publishes s_item)
-        // the item after this one, resolved by thread 0 at the top of this one: its descriptor
-        // loads are in flight during the rounds
+        __syncthreads();
         const LdsBoxT<G> box{Fs};
         for (int base = I.start; base < I.end; base += SST) {
             // pushed: advanced (deposits its current); act: still in the band (appended)
@@ -1042,17 +1045,14 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
         }
         if (tid == 0) {
             claim = atomicAdd(&W.next[q * QPAD], 1);
-            s_item = resolve();
+            s_next = resolve();
         }
         // every deposit of this item is in the current boxes
         __syncthreads();
-        const int next = __builtin_amdgcn_readfirstlane(s_item);
-        ItemT N{};
-        if (next >= 0) N = decode(next);
         const ItemT C = I;
+        I = decode();
         // the next item's fields and first particles are on their way during this item's flush
-        if (next >= 0) {
-            I = N;
+        if (I.end > 0) {
             stage(I);
             if (I.start + tid < I.end)
                 load_raw(iop.s[I.sp].in, I.b0 + I.start + tid, nx, REC ? iop.id[I.sp].in : nullptr);
@@ -1119,7 +1119,6 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
                 }
             }
         }
-        cur = next;
     }
 }
 
@@ -1161,7 +1160,7 @@ static int queue_cap(const Params &P, int64_t slots, int chunk) {
     return (int)(P.nbins / queue_slabs(P) + slots / chunk + 1);
 }
 uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, int chunk) {
-    return 16 * (uint64_t)queue_slabs(P) *
+    return sizeof(Item) * (uint64_t)queue_slabs(P) *
            (uint64_t)((int64_t)queue_cap(P, slots_b, chunk) + queue_cap(P, slots_p, chunk));
 }
 
@@ -1228,8 +1227,8 @@ __global__ void __launch_bounds__(ST) k_rebin(Params P, WorkList W, const Specie
     };
     for (int q = 0; q < 2 * W.nslab; ++q)
         for (int k = blockIdx.x; k < W.count[q]; k += gridDim.x) {
-            const int4 it = W.items[W.base(q) + k];
-            move(it.x, ios[it.x].in_off[it.y], it.z, min(it.w, it.z + W.chunk));
+            const Item it = W.items[W.base(q) + k];
+            move(it.sp, it.b0, it.start, it.end);
         }
     for (int sp = 0; sp < 2; ++sp) {
         const int n = (int)min((int64_t)*ios[sp].in_ovf, ios[sp].in_ovf_cap);
@@ -1262,7 +1261,9 @@ __global__ void __launch_bounds__(WT) k_step_prep(Params P, StepCtx S, WorkList 
     if (t == 0 && b == 0) *ovf0 = *ovf1 = 0;
     const int bin = (q >> 1) * bps + e;
     int c = 0;
+    int64_t b0 = 0;
     if (e < bps) {
+        b0 = (sp ? off1 : off0)[bin];
         c = bin_count(sp ? off1 : off0, sp ? cnt1 : cnt0, bin);
         (sp ? zero1 : zero0)[bin] = 0;
     }
@@ -1283,7 +1284,8 @@ __global__ void __launch_bounds__(WT) k_step_prep(Params P, StepCtx S, WorkList 
     pos += first - v;
     for (int w = 0; w < (t >> 6); ++w) pos += ws[w];
     for (int k = 0; k < v; ++k)  // cap bounds what a queue can hold
-        if (pos + k < W.cap[sp]) W.items[W.base(q) + pos + k] = make_int4(sp, bin, k * W.chunk, c);
+        if (pos + k < W.cap[sp])
+            W.items[W.base(q) + pos + k] = Item{sp, bin, k * W.chunk, min(c, (k + 1) * W.chunk), b0};
 }
 
 // the work list of buffer cur (and, with S, the step's table), the counts of the other buffer cleared
@@ -1373,7 +1375,7 @@ void split_setup(Ctx &c) {
             X->s[sp].ovf[k] = ovfs + (2 * sp + k);
         }
     char *wl = A + c.split_off_wl;
-    X->work.items = (int4 *)wl;
+    X->work.items = (Item *)wl;
     X->work.chunk = c.split_chunk;
     X->work.nslab = queue_slabs(P);
     X->work.cap[0] = queue_cap(P, X->s[0].bin_slots, c.split_chunk);
