@@ -13,13 +13,14 @@
 // along z, interpolated linearly between planes.
 //
 // Solver: a DFT along x and along y (the periodic operator is diagonal there;
-// one workgroup per grid line, the line and its twiddles in LDS), a
+// lines of a workgroup and their twiddles in LDS), a
 // tridiagonal solve along z per transverse mode (one thread per mode), and the
 // inverse DFTs.  It runs once, at t' = 0 (window origin 0), on scratch that the
 // current arrays provide: they are zero between steps and are cleared again
 // afterwards.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pic_internal.h"
@@ -31,67 +32,131 @@ constexpr int IT = 256;
 // in-place DFT of n-point lines of the split complex array (re, im): line L
 // starts at (L % na) * sa + (L / na) * sb, its elements se apart;
 // X[m] = scale * sum_t x[t] exp(sign 2 pi i m t / n)
+// A workgroup holds `groups` times R consecutive lines in LDS, [t][line], and the twiddles; a thread forms X[m]
+// of R lines, so that a twiddle read does for R lines and the lines' reads are the same for all m.
+// One line a workgroup left three quarters of its threads idle at 64 points and read the lines along y
+// 8 bytes a row: 47 us a pass at 64 x 64 x 256, 34 so.
+template <int R>
 __global__ void __launch_bounds__(IT) k_dft_lines(double *re, double *im, int n, int64_t se, int na, int64_t sa,
-                                                  int64_t sb, double sign, double scale) {
+                                                  int64_t sb, int64_t lines, int groups, double sign, double scale) {
     extern __shared__ double sm[];
-    double *xr = sm, *xi = sm + n, *cs = sm + 2 * n, *sn = sm + 3 * n;
-    const int64_t L = blockIdx.x;
-    const int64_t base = (L % na) * sa + (L / na) * sb;
-    for (int t = threadIdx.x; t < n; t += IT) {
-        xr[t] = re[base + t * se];
-        xi[t] = im[base + t * se];
+    const int LB = groups * R, tid = threadIdx.x;
+    double2 *tw = (double2 *)sm;                       // [n]
+    double *xr = sm + 2 * n, *xi = xr + (int64_t)n * LB;  // [n][LB]
+    const int64_t L0 = (int64_t)blockIdx.x * LB;
+    const int nl = (int)min((int64_t)LB, lines - L0);
+    auto base = [&](int j) { return ((L0 + j) % na) * sa + ((L0 + j) / na) * sb; };
+    for (int e = tid; e < n * LB; e += IT) {  // along the shorter stride
+        const int t = se == 1 ? e % n : e / LB, j = se == 1 ? e / n : e % LB;
+        const int64_t o = base(min(j, nl - 1)) + t * se;
+        xr[t * LB + j] = re[o];
+        xi[t * LB + j] = im[o];
+    }
+    for (int t = tid; t < n; t += IT) {
         double s, c;
         sincospi(2.0 * t / n, &s, &c);
-        cs[t] = c;
-        sn[t] = sign * s;
+        tw[t] = make_double2(c, sign * s);
     }
     __syncthreads();
-    for (int m = threadIdx.x; m < n; m += IT) {
-        double ar = 0.0, ai = 0.0;
+    const int mt = min(n, IT), g = tid / mt;
+    if (g >= groups) return;
+    for (int m = tid - g * mt; m < n; m += mt) {
+        double ar[R], ai[R];
+        for (int r = 0; r < R; ++r) ar[r] = ai[r] = 0.0;
         int k = 0;  // m t mod n
+        const double *pr = xr + g * R, *pi = xi + g * R;
         for (int t = 0; t < n; ++t) {
-            const double c = cs[k], s = sn[k];
-            ar += xr[t] * c - xi[t] * s;
-            ai += xr[t] * s + xi[t] * c;
+            const double2 w = tw[k];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                ar[r] += pr[r] * w.x - pi[r] * w.y;
+                ai[r] += pr[r] * w.y + pi[r] * w.x;
+            }
+            pr += LB;
+            pi += LB;
             k += m;
             if (k >= n) k -= n;
         }
-        re[base + m * se] = ar * scale;
-        im[base + m * se] = ai * scale;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (g * R + r >= nl) continue;
+            const int64_t o = base(g * R + r) + m * se;
+            re[o] = ar[r] * scale;
+            im[o] = ai[r] * scale;
+        }
     }
+}
+
+// lines of n points each, four to a thread where the LDS of one workgroup (64 KB) holds them
+static void dft_lines(hipStream_t st, double *re, double *im, int n, int64_t se, int na, int64_t sa, int64_t sb,
+                      int64_t lines, double sign, double scale) {
+    const int groups = std::max(1, IT / n);
+    auto lds = [&](int r) { return 16 * n * (groups * r + 1); };
+    const int R = lds(4) <= 64 * 1024 ? 4 : 1;
+    const dim3 grid((unsigned)((lines + groups * R - 1) / (groups * R)));
+    if (R == 4)
+        hipLaunchKernelGGL(k_dft_lines<4>, grid, dim3(IT), lds(4), st, re, im, n, se, na, sa, sb, lines, groups, sign,
+                           scale);
+    else
+        hipLaunchKernelGGL(k_dft_lines<1>, grid, dim3(IT), lds(1), st, re, im, n, se, na, sa, sb, lines, groups, sign,
+                           scale);
 }
 
 // one transverse mode (kx, ky) per thread: g2 phi[l-1] + (lam - 2 g2) phi[l] + g2 phi[l+1] = -rho[l],
 // phi[-1] = 0, and above the top face phi[nz] = 0 or, with an open top, phi[nz] = phi[nz-1] (no
 // field through it); forward elimination (coefficients kept in cp), then back substitution
-__global__ void __launch_bounds__(IT) k_tri_z(Params P, double *re, double *im, double *cp, double g2, int open_top) {
-    const int64_t q = (int64_t)blockIdx.x * IT + threadIdx.x;
+// The planes are loaded eight ahead of the recurrence, which is what is left of the time: with a load in
+// every step 169 us at 64 x 64 x 256 (4096 modes, a wave on every fourth CU), 67 so.
+__global__ void __launch_bounds__(64) k_tri_z(Params P, double *re, double *im, double *cp, double g2, int open_top) {
+    constexpr int U = 8;
+    const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (q >= P.plane) return;
     const int kx = (int)(q % P.nx), ky = (int)(q / P.nx);
     const double sx = sinpi((double)kx / P.nx), sy = sinpi((double)ky / P.ny);
     const double diag = -4.0 * sx * sx - 4.0 * sy * sy - 2.0 * g2;
     const int64_t pl = P.plane;
-    double c = g2 / diag;
-    double dr = -re[q] / diag, di = -im[q] / diag;
-    cp[q] = c;
-    re[q] = dr;
-    im[q] = di;
-    for (int l = 1; l < P.nz; ++l) {
-        const int64_t o = q + (int64_t)l * pl;
-        const double m = (open_top && l == P.nz - 1 ? diag + g2 : diag) - g2 * c;
-        c = g2 / m;
-        dr = (-re[o] - g2 * dr) / m;
-        di = (-im[o] - g2 * di) / m;
-        cp[o] = c;
-        re[o] = dr;
-        im[o] = di;
+    double c = 0.0, dr = 0.0, di = 0.0;  // before plane 0
+    double a[U], b[U], e[U];
+    auto fetch = [&](double *dst, const double *src, int l) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) dst[k] = src[q + (int64_t)max(0, min(l + k, P.nz - 1)) * pl];
+    };
+    fetch(a, re, 0);
+    fetch(b, im, 0);
+    for (int l = 0; l < P.nz; l += U) {
+        double na[U], nb[U];
+        fetch(na, re, l + U);
+        fetch(nb, im, l + U);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (l + k >= P.nz) break;
+            const int64_t o = q + (int64_t)(l + k) * pl;
+            const double m = (open_top && l + k == P.nz - 1 ? diag + g2 : diag) - g2 * c;
+            c = g2 / m;
+            dr = (-a[k] - g2 * dr) / m;
+            di = (-b[k] - g2 * di) / m;
+            cp[o] = c;
+            re[o] = dr;
+            im[o] = di;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) a[k] = na[k], b[k] = nb[k];
     }
-    for (int l = P.nz - 2; l >= 0; --l) {
-        const int64_t o = q + (int64_t)l * pl;
-        dr = re[o] - cp[o] * dr;
-        di = im[o] - cp[o] * di;
-        re[o] = dr;
-        im[o] = di;
+    // back substitution from plane nz - 2 down; plane h + k of the block that starts at h is entry k
+    for (int top = P.nz - 2; top >= 0; top -= U) {
+        const int h = top - U + 1;
+        fetch(a, re, h);
+        fetch(b, im, h);
+        fetch(e, cp, h);
+#pragma unroll
+        for (int k = U - 1; k >= 0; --k) {
+            if (h + k < 0) break;
+            const int64_t o = q + (int64_t)(h + k) * pl;
+            dr = a[k] - e[k] * dr;
+            di = b[k] - e[k] * di;
+            re[o] = dr;
+            im[o] = di;
+        }
     }
 }
 
@@ -155,15 +220,12 @@ static pic_status solve_beam_potential(Ctx &c, double g2, int open_top, double *
     beam_rho(c, re);
     const int64_t pl = P.plane;
     // forward DFT along x (lines over j, l), then along y (lines over i, l)
-    hipLaunchKernelGGL(k_dft_lines, dim3((unsigned)(P.ny * (int64_t)P.nz)), dim3(IT), 32 * P.nx, c.st, re, im, P.nx,
-                       (int64_t)1, P.ny, (int64_t)P.nx, pl, -1.0, 1.0);
-    hipLaunchKernelGGL(k_dft_lines, dim3((unsigned)(P.nx * (int64_t)P.nz)), dim3(IT), 32 * P.ny, c.st, re, im, P.ny,
-                       (int64_t)P.nx, P.nx, (int64_t)1, pl, -1.0, 1.0);
-    hipLaunchKernelGGL(k_tri_z, dim3((unsigned)nblocks(pl, IT)), dim3(IT), 0, c.st, P, re, im, cp, g2, open_top);
-    hipLaunchKernelGGL(k_dft_lines, dim3((unsigned)(P.nx * (int64_t)P.nz)), dim3(IT), 32 * P.ny, c.st, re, im, P.ny,
-                       (int64_t)P.nx, P.nx, (int64_t)1, pl, 1.0, 1.0 / P.ny);
-    hipLaunchKernelGGL(k_dft_lines, dim3((unsigned)(P.ny * (int64_t)P.nz)), dim3(IT), 32 * P.nx, c.st, re, im, P.nx,
-                       (int64_t)1, P.ny, (int64_t)P.nx, pl, 1.0, 1.0 / P.nx);
+    const int64_t lx = (int64_t)P.ny * P.nz, ly = (int64_t)P.nx * P.nz;
+    dft_lines(c.st, re, im, P.nx, 1, P.ny, P.nx, pl, lx, -1.0, 1.0);
+    dft_lines(c.st, re, im, P.ny, P.nx, P.nx, 1, pl, ly, -1.0, 1.0);
+    hipLaunchKernelGGL(k_tri_z, dim3((unsigned)nblocks(pl, 64)), dim3(64), 0, c.st, P, re, im, cp, g2, open_top);
+    dft_lines(c.st, re, im, P.ny, P.nx, P.nx, 1, pl, ly, 1.0, 1.0 / P.ny);
+    dft_lines(c.st, re, im, P.nx, 1, P.ny, P.nx, pl, lx, 1.0, 1.0 / P.nx);
     return PIC_OK;
 }
 
