@@ -127,13 +127,13 @@ __global__ void __launch_bounds__(AT) k_adj_e(Params P, int k0r, int shift, int 
     lBz[o] += dt * (e[0] - ex_j1 - e[1] + ey_i1);
 }
 
-// The step's last pass: the new lam_E to its place, and the scratch in J and the ion profile cleared.
+// The step's last pass: the new lam_E to its place, and the scratch in J cleared.
 struct AdjLast {
-    double *lE[3], *J[3], *jion;
+    double *lE[3], *J[3];
 };
 
 // lam_E += transpose of (B <- B - h curl E) applied to lam_B.  LAST: into its place, with what goes with
-// it (one pass for this one, three copies and four fills).
+// it (one pass for this one, three copies and three fills).
 template <bool LAST>
 __global__ void __launch_bounds__(AT) k_adj_bhalf(Params P, int k0r, double h, const double *lBx, const double *lBy,
                                                   const double *lBz, double *nEx, double *nEy, double *nEz,
@@ -152,10 +152,8 @@ __global__ void __launch_bounds__(AT) k_adj_bhalf(Params P, int k0r, double h, c
     d[0][o] = nEx[o] + h * (bxy(lBy, i, j, l) - bxy(lBy, i, j, l - 1) - bz(i, j, l) + bz(i, j - 1, l));
     d[1][o] = nEy[o] + h * (bz(i, j, l) - bz(i - 1, j, l) - bxy(lBx, i, j, l) + bxy(lBx, i, j, l - 1));
     d[2][o] = nEz[o] + h * (bxy(lBx, i, j, l) - bxy(lBx, i, j - 1, l) - bxy(lBy, i, j, l) + bxy(lBy, i - 1, j, l));
-    if (LAST) {
+    if (LAST)
         for (int k = 0; k < 3; ++k) A.J[k][o] = 0.0;
-        if (o < P.nz) A.jion[o] = 0.0;
-    }
 }
 
 __global__ void k_zero_plane(int64_t plane, int p, double *a0, double *a1, double *a2, double *b0, double *b1,
@@ -684,7 +682,7 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
         f.B[k] = c.B64[k];
         fn.B[k] = Bn[k];
     }
-    launch_bhalf<double>(P, S.k0r, f, fn, 0.5 * P.dt, nullptr, c.st);
+    launch_bhalf<double>(P, S.k0r, f, fn, 0.5 * P.dt, c.jion64, c.st);
     // window shift: the back plane became the empty front plane
     if (S.shift)
         hipLaunchKernelGGL(k_zero_plane, dim3(nblocks(P.plane, 256)), dim3(256), 0, c.st, (int64_t)P.plane, S.k0r,
@@ -696,7 +694,7 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
                        lE[2], nE[0], nE[1],
                        nE[2], lB[0], lB[1], lB[2], c.J64[0], c.J64[1], c.J64[2]);
     // second half step
-    const AdjLast last{{lE[0], lE[1], lE[2]}, {c.J64[0], c.J64[1], c.J64[2]}, c.jion64};
+    const AdjLast last{{lE[0], lE[1], lE[2]}, {c.J64[0], c.J64[1], c.J64[2]}};
     hipLaunchKernelGGL(k_adj_bhalf<false>, dim3(nb), dim3(AT), 0, c.st, P, S.k0r, 0.5 * P.dt, lB[0], lB[1], lB[2],
                        nE[0], nE[1], nE[2], last);
     // the partial sums, read back together at the end: the ions' (none: zero), then the particles'

@@ -347,13 +347,15 @@ pic_status run_diag(Ctx &c, uint32_t mask, double kb, pic_diag_out *o, double *r
     }
     if (mask & PIC_DIAG_GAUSS) {
         const int band = 8;
-        // scratch: rho in J_x (zero between steps), ion profile in the ion-current buffer
+        // scratch: rho in J_x (zero between steps), ion profile in the ion-current buffer (FP32: zero too;
+        // FP64: cleared when a step begins)
         double *rho = plain ? c.J64[0] : (double *)c.Ji[0];
         double *ion = plain ? c.jion64 : (double *)c.jioni;
         if (plain)
             rho64(c, rho, 3);
         else
             split_rho(c, rho, 3);
+        if (plain) PIC_HIP(c, hipMemsetAsync(ion, 0, 8 * P.nz, c.st));
         if (P.ions && c.sh_hi > c.sh_lo)
             hipLaunchKernelGGL(k_rho_ion, dim3(nblocks(c.sh_hi - c.sh_lo, 128)), dim3(128), 0, c.st, P, c.sh_lo,
                                c.sh_hi - c.sh_lo, o->t, c.k0, ion, !plain);

@@ -31,9 +31,9 @@ __device__ inline bool plane_cell(const Params &P, int &i, int &j) {
     return true;
 }
 
-// g: where the new B goes (f itself, or another set beside E)
+// g: where the new B goes (f itself, or another set beside E); profile: an nz-long array to clear, or null
 template <typename T>
-__global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf) {
+__global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *profile) {
     int i, j;
     if (!plane_cell(P, i, j)) return;
     const int p = (int)blockIdx.y;
@@ -53,19 +53,18 @@ __global__ void __launch_bounds__(256) k_bhalf(Params P, int k0r, FieldsT<T> f, 
     g.B[0][o] = bx;
     g.B[1][o] = by;
     g.B[2][o] = f.B[2][o] - h * ((Ey[oi] - ey) - (Ex[oj] - ex));
-    if (murbuf) {
-        int q = l == 0 ? 0 : l == 1 ? 1 : l == P.nz - 2 ? 2 : l == P.nz - 1 ? 3 : -1;
-        if (q >= 0) {
-            int64_t s = (int64_t)i + (int64_t)P.nx * j;
-            murbuf[(2 * q + 0) * (int64_t)P.plane + s] = ex;
-            murbuf[(2 * q + 1) * (int64_t)P.plane + s] = ey;
-        }
-    }
+    if (profile && i == 0 && j == 0) profile[p] = T(0);
 }
 
+// Also the Mur faces: tangential E on logical planes 0 and nz - 1, which no other thread reads or writes,
+// from the threads of the planes beside them, which hold the old and the new value there -- the back
+// face unless the window shifts after this step (k_shift), the front face only while the window is at
+// rest: a moving window's front keeps its tangential E (zero; the planes enter empty), since a
+// static-face Mur condition at a face that jumps forward every step or two is unstable with plasma
+// streaming in.  (As a pass of its own over saved planes it was one more launch a step, 4 us.)
 template <typename T, typename JT>
-__global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, FieldsT<T> f, JT *Jx, JT *Jy, JT *Jz,
-                                                 const JT *jion, T dt) {
+__global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, int shift, int front_mur, FieldsT<T> f, JT *Jx,
+                                                 JT *Jy, JT *Jz, const JT *jion, T dt, T cm) {
     int i, j;
     if (!plane_cell(P, i, j)) return;
     const int p = (int)blockIdx.y;
@@ -82,8 +81,20 @@ __global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, FieldsT<T> f
     Jy[o] = JT(0);
     Jz[o] = JT(0);
     if (l != 0 && l != P.nz - 1) {
-        f.E[0][o] += dt * ((bz - Bz[oj]) - (by - By[ol]) - (T)jx);
-        f.E[1][o] += dt * ((bx - Bx[ol]) - (bz - Bz[oi]) - (T)jy);
+        const T ex = f.E[0][o], ey = f.E[1][o];
+        const T nx = ex + dt * ((bz - Bz[oj]) - (by - By[ol]) - (T)jx);
+        const T ny = ey + dt * ((bx - Bx[ol]) - (bz - Bz[oi]) - (T)jy);
+        f.E[0][o] = nx;
+        f.E[1][o] = ny;
+        if (l == 1 && !shift) {
+            f.E[0][ol] = ex + cm * (nx - f.E[0][ol]);
+            f.E[1][ol] = ey + cm * (ny - f.E[1][ol]);
+        }
+        if (l == P.nz - 2 && front_mur) {
+            const int64_t ot = o + ((p + 1 == P.nz) ? -(int64_t)(P.nz - 1) * P.plane : (int64_t)P.plane);
+            f.E[0][ot] = ex + cm * (nx - f.E[0][ot]);
+            f.E[1][ot] = ey + cm * (ny - f.E[1][ot]);
+        }
     }
     if (l != P.nz - 1) {
         double jt = jz + (jion ? jvalue<JT>(jion[l], P.finv) : 0.0);
@@ -91,40 +102,20 @@ __global__ void __launch_bounds__(256) k_eupdate(Params P, int k0r, FieldsT<T> f
     }
 }
 
-// Mur faces (tangential E on logical planes 0 and nz-1) from the saved
-// pre-update planes -- the front face only while the window is at rest: a
-// moving window's front keeps its tangential E (zero; the planes enter empty),
-// since a static-face Mur condition at a face that jumps forward every step or
-// two is unstable with plasma streaming in.  When the window shifts after this
-// step, the back plane becomes the new (empty) front plane instead: E and B
-// there are zeroed.  Also clears the ion current profile for the next step (where there is one to clear).
-template <typename T, typename JT>
-__global__ void k_mur_shift(Params P, int k0r, int shift, int front_mur, FieldsT<T> f, const T *murbuf, JT *jion,
-                            T cm) {
+// The window shifts after this step: the back plane becomes the new front plane, which enters empty.
+template <typename T>
+__global__ void k_shift(Params P, int k0r, FieldsT<T> f) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (jion && s < P.nz) jion[s] = JT(0);
     if (s >= P.plane) return;
-    int64_t pl = P.plane;
-    int p0 = k0r, p1 = ring_plane(1, k0r, P.nz), pm = ring_plane(P.nz - 2, k0r, P.nz),
-        pt = ring_plane(P.nz - 1, k0r, P.nz);
-    for (int c = 0; c < 2; ++c) {
-        const T *o0 = murbuf + (0 + c) * pl, *o1 = murbuf + (2 + c) * pl;
-        const T *o2 = murbuf + (4 + c) * pl, *o3 = murbuf + (6 + c) * pl;
-        T *F = f.E[c];
-        if (!shift) F[p0 * pl + s] = o1[s] + cm * (F[p1 * pl + s] - o0[s]);
-        if (front_mur) F[pt * pl + s] = o2[s] + cm * (F[pm * pl + s] - o3[s]);
-    }
-    if (shift) {
-        for (int c = 0; c < 3; ++c) {
-            f.E[c][p0 * pl + s] = T(0);
-            f.B[c][p0 * pl + s] = T(0);
-        }
+    for (int c = 0; c < 3; ++c) {
+        f.E[c][k0r * (int64_t)P.plane + s] = T(0);
+        f.B[c][k0r * (int64_t)P.plane + s] = T(0);
     }
 }
 
 // The field part of an FP32 step in one pass: B by a full step (B^(n-1/2) -> B^(n+1/2), what k_bhalf
 // does with h = dt), E by a step with the new B and the currents, the Mur faces and the shift (as
-// k_eupdate and k_mur_shift), from the fields `f` into `g`.  A thread forms the new B of its cell and
+// k_eupdate and k_shift), from the fields `f` into `g`.  A thread forms the new B of its cell and
 // the six components of it that E needs from the neighbours before it (loads that hit in L1), so that
 // nothing waits for a whole pass over B; the old fields stay as they are, which is why `g` is a second
 // set.  The threads of planes 1 and nz - 2 hold what the Mur faces beside them need and write those.
@@ -206,35 +197,25 @@ void launch_fields32(const Params &P, int k0r, int shift, int front_mur, FieldsT
 }
 
 template <typename T>
-void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf, hipStream_t st) {
-    hipLaunchKernelGGL(k_bhalf<T>, dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, f, g, h, murbuf);
+void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *profile, hipStream_t st) {
+    hipLaunchKernelGGL(k_bhalf<T>, dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, f, g, h, profile);
 }
 
 template <typename T, typename JT>
-void launch_eupdate(const Params &P, int k0r, FieldsT<T> f, JT *J[3], const JT *jion, T dt, hipStream_t st) {
-    hipLaunchKernelGGL((k_eupdate<T, JT>), dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, f, J[0], J[1],
-                       J[2], jion, dt);
-}
-
-template <typename T, typename JT>
-void launch_mur_shift(const Params &P, int k0r, int shift, int front_mur, FieldsT<T> f, const T *murbuf, JT *jion,
-                      T dt, hipStream_t st) {
-    int64_t n = P.plane > P.nz ? P.plane : P.nz;
-    T cm = (dt - T(1)) / (dt + T(1));
-    hipLaunchKernelGGL((k_mur_shift<T, JT>), dim3(nblocks(n, 256)), dim3(256), 0, st, P, k0r, shift, front_mur, f,
-                       murbuf, jion, cm);
+void launch_eupdate(const Params &P, int k0r, int shift, int front_mur, FieldsT<T> f, JT *J[3], const JT *jion, T dt,
+                    hipStream_t st) {
+    const T cm = (dt - T(1)) / (dt + T(1));
+    hipLaunchKernelGGL((k_eupdate<T, JT>), dim3(nblocks(P.plane, 256), P.nz), dim3(256), 0, st, P, k0r, shift,
+                       front_mur, f, J[0], J[1], J[2], jion, dt, cm);
+    if (shift) hipLaunchKernelGGL(k_shift<T>, dim3(nblocks(P.plane, 256)), dim3(256), 0, st, P, k0r, f);
 }
 
 template void launch_bhalf<double>(const Params &, int, FieldsT<double>, FieldsT<double>, double, double *, hipStream_t);
 template void launch_bhalf<float>(const Params &, int, FieldsT<float>, FieldsT<float>, float, float *, hipStream_t);
-template void launch_eupdate<double, double>(const Params &, int, FieldsT<double>, double *[3], const double *,
-                                             double, hipStream_t);
-template void launch_eupdate<float, long long>(const Params &, int, FieldsT<float>, long long *[3],
+template void launch_eupdate<double, double>(const Params &, int, int, int, FieldsT<double>, double *[3],
+                                             const double *, double, hipStream_t);
+template void launch_eupdate<float, long long>(const Params &, int, int, int, FieldsT<float>, long long *[3],
                                                const long long *, float, hipStream_t);
-template void launch_mur_shift<double, double>(const Params &, int, int, int, FieldsT<double>, const double *, double *,
-                                               double, hipStream_t);
-template void launch_mur_shift<float, long long>(const Params &, int, int, int, FieldsT<float>, const float *,
-                                                 long long *, float, hipStream_t);
 
 // ---------------------------------------------------------------- ion current
 // Immobile lab ions: the plasma lattice drifting rigidly at -beta_R.  Summed

@@ -1789,10 +1789,8 @@ void split_fields(Ctx &c, const StepCtx &S) {
         std::swap(c.E32, c.E32n);
         std::swap(c.B32, c.B32n);
     } else {
-        launch_bhalf<float>(P, S.k0r, f, f, (float)P.dt, (float *)c.murbuf, c.st);  // B^(n-1/2) -> B^(n+1/2)
-        launch_eupdate<float, long long>(P, S.k0r, f, c.Ji, ion, (float)P.dt, c.st);
-        launch_mur_shift<float, long long>(P, S.k0r, S.shift, c.bw <= 0.0, f, (const float *)c.murbuf, nullptr,
-                                           (float)P.dt, c.st);
+        launch_bhalf<float>(P, S.k0r, f, f, (float)P.dt, nullptr, c.st);  // B^(n-1/2) -> B^(n+1/2)
+        launch_eupdate<float, long long>(P, S.k0r, S.shift, c.bw <= 0.0, f, c.Ji, ion, (float)P.dt, c.st);
     }
     std::swap(c.jioni, c.jionn);
     timing_end(c, 1, t4);

@@ -246,7 +246,6 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         pl.cap_p = P.has_plasma ? fill + (between + 2) * sheets_per_step(P) * sheet : 0;
         for (int k = 0; k < 9; ++k) off[k] = take(8 * P.nc);             // E B J
         off[9] = take(8 * P.nz);                                          // jion
-        off[10] = take(8 * 8 * (uint64_t)P.plane);                        // Mur planes
         off[11] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1));   // beam
         off[12] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));   // plasma
         off[13] = pl.record ? 0 : take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));  // plasma (compaction)
@@ -256,7 +255,6 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         for (int k = 0; k < 6; ++k) off[k] = take(4 * P.nc);  // E B float
         for (int k = 6; k < 9; ++k) off[k] = take(8 * P.nc);  // J int64
         off[9] = take(2 * 8 * P.nz);  // jion, twice
-        off[10] = take(4 * 8 * (uint64_t)P.plane);
         if (P.nc <= FIELDS_TWICE) off[28] = take(6 * al256(4 * P.nc));  // E B of the next step
         // particle double buffers with bin slack and an overflow tail (k_split32.hip)
         int64_t nbins = P.nbins;
@@ -423,7 +421,7 @@ static pic_status step64(Ctx &c) {
     }
     const Params &P = c.P;
     hipEvent_t t0 = timing_begin(c);
-    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, nullptr, c.st);
+    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, c.jion64, c.st);
     timing_end(c, 1, t0);
     hipEvent_t t1 = timing_begin(c);
     step64_particles(c, S, f);
@@ -433,10 +431,8 @@ static pic_status step64(Ctx &c) {
     launch_neutraliser_current(c, S);
     timing_end(c, 2, t2);
     hipEvent_t t3 = timing_begin(c);
-    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, (double *)c.murbuf, c.st);
-    launch_eupdate<double, double>(P, S.k0r, f, c.J64, c.jion64, P.dt, c.st);
-    launch_mur_shift<double, double>(P, S.k0r, S.shift, c.bw <= 0.0, f, (const double *)c.murbuf, c.jion64, P.dt,
-                                     c.st);
+    launch_bhalf<double>(P, S.k0r, f, f, 0.5 * P.dt, nullptr, c.st);
+    launch_eupdate<double, double>(P, S.k0r, S.shift, c.bw <= 0.0, f, c.J64, c.jion64, P.dt, c.st);
     timing_end(c, 1, t3);
     c.step += 1;
     c.k0 = S.k0n;
@@ -577,7 +573,6 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
     c->dflags = (int32_t *)(A + off[19]);
     c->probe_acc = (double *)(A + off[19] + 64);  // same 256-byte block: flags, then the probe's sums
     c->i64scratch = (int64_t *)(A + off[22]);
-    c->murbuf = A + off[10];
     if (o->init_fields == 2) {
         for (int k = 0; k < 3; ++k) c->fc_E[k] = (double *)(A + off[25]) + k * P.nc;
         c->fc_rho = (double *)(A + off[26]);

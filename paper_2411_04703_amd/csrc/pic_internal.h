@@ -81,7 +81,6 @@ struct Ctx {
     long long *Ji[3] = {};
     double *jion64 = nullptr;
     long long *jioni = nullptr, *jionn = nullptr;  // ion profile of the next step (zero between steps), of the last
-    void *murbuf = nullptr;
 
     // particles
     Part64 b64{}, p64{}, p64alt{};
@@ -123,12 +122,10 @@ void timing_end(Ctx &c, int cls, hipEvent_t start);
 // ---------------------------------------------------------------- launchers
 // FDTD (k_fdtd.hip)
 template <typename T>
-void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *murbuf, hipStream_t st);
+void launch_bhalf(const Params &P, int k0r, FieldsT<T> f, FieldsT<T> g, T h, T *profile, hipStream_t st);
 template <typename T, typename JT>
-void launch_eupdate(const Params &P, int k0r, FieldsT<T> f, JT *J[3], const JT *jion, T dt, hipStream_t st);
-template <typename T, typename JT>
-void launch_mur_shift(const Params &P, int k0r, int shift, int front_mur, FieldsT<T> f, const T *murbuf, JT *jion,
-                      T dt, hipStream_t st);
+void launch_eupdate(const Params &P, int k0r, int shift, int front_mur, FieldsT<T> f, JT *J[3], const JT *jion, T dt,
+                    hipStream_t st);  // with the Mur faces and the shift
 void launch_ion64(const Params &P, int64_t sh_lo, int64_t nsheets, double t0, double t1, int64_t k0, double *jion,
                   hipStream_t st);
 void launch_fields32(const Params &P, int k0r, int shift, int front_mur, FieldsT<float> f, FieldsT<float> g,
