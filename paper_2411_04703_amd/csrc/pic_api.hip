@@ -829,12 +829,26 @@ pic_status pic_diag_static(pic_ctx *c, uint32_t mask, double bunch_period_cells,
     return run_diag(*c, mask, kb, out, red, DIAG_STATIC_DOUBLES);
 }
 
-// copy logical planes of a field into dst (double), un-rotating the ring
-__global__ void k_f2d(const float *a, double *b, int64_t n) {
-    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) b[q] = (double)a[q];
+// An FP32 state's fields into an FP64 context, whose currents, ion profile and alive flags are cleared:
+// one launch (twelve took 90 us of a 24 x 40 x 64 hand-over).
+struct Widen {
+    const float *src[6];
+    double *dst[6], *J[3], *jion;
+    int32_t *alive_b, *alive_p;
+    int64_t nc, nz, cap_b, cap_p;
+};
+__global__ void __launch_bounds__(256) k_widen(Widen W) {
+    const int64_t nt = (int64_t)gridDim.x * 256, t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = t; i < W.nc; i += nt) {
+        for (int k = 0; k < 6; ++k) W.dst[k][i] = (double)W.src[k][i];
+        for (int k = 0; k < 3; ++k) W.J[k][i] = 0.0;
+    }
+    for (int64_t i = t; i < W.nz; i += nt) W.jion[i] = 0.0;
+    for (int64_t i = t; i < W.cap_b; i += nt) W.alive_b[i] = 0;
+    for (int64_t i = t; i < W.cap_p; i += nt) W.alive_p[i] = 0;
 }
 
+// copy logical planes of a field into dst (double), un-rotating the ring
 __global__ void k_field_out(const void *src, int isfloat, double *dst, int64_t plane, int nz, int k0r) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= plane * nz) return;
@@ -1107,18 +1121,19 @@ pic_status pic_state_to_fp64(const pic_ctx *src, pic_ctx *dst) {
         return PIC_ENOMEM;
     }
     Ctx &d = *dst;
-    // fields: same ring layout once the window origin is copied
+    // fields: same ring layout once the window origin is copied; particles to their slots, those without
+    // a particle dead
+    Widen W{{}, {}, {}, d.jion64, d.b64.alive, d.p64.alive, B.nc, B.nz, std::max<int64_t>(d.cap_b, 1),
+            std::max<int64_t>(d.cap_p, 1)};
     for (int k = 0; k < 3; ++k) {
-        hipLaunchKernelGGL(k_f2d, dim3(nblocks(B.nc, 256)), dim3(256), 0, d.st, (const float *)src->E32[k], d.E64[k],
-                           B.nc);
-        hipLaunchKernelGGL(k_f2d, dim3(nblocks(B.nc, 256)), dim3(256), 0, d.st, (const float *)src->B32[k], d.B64[k],
-                           B.nc);
-        PIC_HIP(d, hipMemsetAsync(d.J64[k], 0, 8 * (uint64_t)B.nc, d.st));
+        W.src[k] = src->E32[k];
+        W.src[3 + k] = src->B32[k];
+        W.dst[k] = d.E64[k];
+        W.dst[3 + k] = d.B64[k];
+        W.J[k] = d.J64[k];
     }
-    PIC_HIP(d, hipMemsetAsync(d.jion64, 0, 8 * (uint64_t)B.nz, d.st));
-    // particles to their slots; slots without a particle are dead
-    PIC_HIP(d, hipMemsetAsync(d.b64.alive, 0, 4 * (uint64_t)std::max<int64_t>(d.cap_b, 1), d.st));
-    PIC_HIP(d, hipMemsetAsync(d.p64.alive, 0, 4 * (uint64_t)std::max<int64_t>(d.cap_p, 1), d.st));
+    const int64_t most = std::max<int64_t>({W.nc, W.cap_b, W.cap_p});
+    hipLaunchKernelGGL(k_widen, dim3(std::min(nblocks(most, 256), 1 << 20)), dim3(256), 0, d.st, W);
     split_export64(*src, d.b64, d.p64, d.st);
     d.step = src->step;
     d.k0 = src->k0;
