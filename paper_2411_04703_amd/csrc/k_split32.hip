@@ -445,8 +445,10 @@ __device__ inline void esk_setup(const float X0[3], const float X1[3], Esk &e) {
 // DEP 0 visits nonzero contributions only (one branch each); DEP 1 visits all
 // 48 of a component that moves along its axis; DEP 2 leaves out the window's
 // last node along an axis (m = 2, a = 3 or b = 3) when no lane of the wave
-// crosses there (wave-uniform branches).  The values visited differ only by
-// zeros, so the integer current sums are the same.  ROW (with DEP 2), for a grid
+// crosses there (wave-uniform branches), and there only the lanes that cross
+// add: the others' zeros would still collide with them in LDS (128 x 128 x 512,
+// the pinched beam of steps 200 to 224: 1371 -> 1317 us).  The values visited
+// differ only by zeros, so the integer current sums are the same.  ROW (with DEP 2), for a grid
 // of one row along y: the contributions of the window's y nodes all go to that
 // row, so their integers are summed in registers and added once, fn's y offset 0
 // (2048 x 1 x 4096: the step kernel 1.24 -> 1.19 ms).
@@ -476,7 +478,8 @@ __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&
         return 0.5f * (fmaf(e.S0[CA][a], ub[b], e.DS[CA][a] * vb[b]) + fmaf(ua[a], e.S0[CB][b], va[a] * e.DS[CB][b]));
     };
     if (DEP == 2) {
-        const bool m2 = __any(e.cross & (1 << C)), a3 = __any(e.cross & (1 << CA)), b3 = __any(e.cross & (1 << CB));
+        const bool lc = e.cross & (1 << C), la = e.cross & (1 << CA), lb = e.cross & (1 << CB);
+        const bool m2 = __any(lc), a3 = __any(la), b3 = __any(lb);
         if constexpr (ROW && C != 1) {  // y is the cross axis a of J_x and b of J_z, o the other one
             const bool y3 = C == 0 ? a3 : b3, o3 = C == 0 ? b3 : a3;
 #pragma unroll
@@ -511,9 +514,10 @@ __device__ inline void esk_component(const Esk &e, double f, double fscale, F &&
                     fn(C, 0, a, b, s);
                     continue;
                 }
+                if ((a == 3 && !la) || (b == 3 && !lb)) continue;
                 fn(C, 0, a, b, to_fixed_as<BIASED>(A, Pd[0]));
                 fn(C, 1, a, b, to_fixed_as<BIASED>(A, Pd[1]));
-                if (m2) fn(C, 2, a, b, to_fixed_as<BIASED>(A, Pd[2]));
+                if (m2 && lc) fn(C, 2, a, b, to_fixed_as<BIASED>(A, Pd[2]));
             }
         }
         return;

@@ -210,8 +210,9 @@ template <class G, int K> __device__ inline void flush_lds(const Params &P, int 
 }
 
 // One component of the Esirkepov current (the scheme is described at esk_component in k_split32.hip:
-// the same factorisation J_c(m, a, b) = f P_c[m] A_c[a][b], here in FP64): a window's last node only
-// where some lane of the wave crosses a half cell, a component only where some lane moves along it.
+// the same factorisation J_c(m, a, b) = f P_c[m] A_c[a][b], here in FP64): a component only where some
+// lane of the wave moves along it, a window's last node only where some lane crosses a half cell, and
+// there only by the lanes that do (27 x 33 x 70, a step: 41 -> 36 us; 128 x 128 x 512: the same).
 template <class G, int C> __device__ inline void deposit_lds(double *Js, const int jb[3], const double S0[3][4],
                                                              const double DS[3][4], const bool cross[3], double f) {
     constexpr int CA = (C + 1) % 3, CB = (C + 2) % 3;
@@ -235,11 +236,12 @@ template <class G, int C> __device__ inline void deposit_lds(double *Js, const i
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             if (b == 3 && !b3) break;
+            if ((a == 3 && !cross[CA]) || (b == 3 && !cross[CB])) continue;
             const double A = fma(S0[CA][a], ub[b], DS[CA][a] * vb[b]);
             double *e = o + ST[CA] * a + ST[CB] * b;
             atomicAdd(e, A * P[0]);
             atomicAdd(e + ST[C], A * P[1]);
-            if (m2) atomicAdd(e + 2 * ST[C], A * P[2]);
+            if (m2 && cross[C]) atomicAdd(e + 2 * ST[C], A * P[2]);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
