@@ -1168,28 +1168,30 @@ uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, in
            (uint64_t)((int64_t)queue_cap(P, slots_b, chunk) + queue_cap(P, slots_p, chunk));
 }
 
-// Particles per work item for n particles in all: whole rounds of the workgroup, at most CH.  A bin
-// of more is shared out.  An item costs its staging and flush (about 9 us on 16 x 8 x 8, more where
-// parts of a bin flush to the same cells at a time) besides 8 us a round, so that 128 x 128 x 512, every
-// bin of 2048 in parts of 768, takes 1.92 ms for 1.21.  Where the step is a few rounds a workgroup, the
-// parts of the largest bins (the beam's) decide how long it is.  Kernel times in us for parts of
-//                                                         768 1536 2304 3072 4608 6144 9216
+// Particles per work item of a run with n_beam beam particles: whole rounds of the workgroup, at most
+// CH.  A bin of more is shared out.  An item costs its staging and flush (about 9 us on 16 x 8 x 8, more
+// where parts of a bin flush to the same cells at a time) besides 8 us a round, so that 128 x 128 x 512,
+// every bin of 2048 in parts of 768, takes 1.92 ms for 1.21.  Where the step is a few rounds a
+// workgroup, the parts of the largest bins (the beam's) decide how long it is.  Kernel times in us for
+// parts of                                                768 1536 2304 3072 4608 6144 9216
 //   32 x 32 x 64, beam of 16384                            25   35                       35
 //   24 x 40 x 64, plasma of 2 a cell                       27   38   44                  44
 //   40 x 24 x 144, plasma of 2 a cell                           56   54   63   85  108  151
 //   64 x 64 x 256, beam of 1.0 M, plasma of 2 a cell      347  279  229       232       308
 //   48 x 32 x 460, beam of 2.4 M, plasma of 2 a cell           455  375  337  298  286  288
 //   96 x 32 x 296, beam of 2.4 M, plasma and ions              635  530  472  382  366  355
-// So: two fifths of what a workgroup of the 256 CUs has to do (768, 768, 768, 4608, 5376, 9216 here),
-// but a plasma bin in no more parts than there are workgroups for all of them (2304 in the third).
-int split_chunk(const Params &P, int64_t n) {
+// So: about one part of the beam for each workgroup of the 256 CUs (768, 768, 768, 4608, 9216, 9216
+// here), but a plasma bin in no more parts than there are workgroups for all of them (2304 in the
+// third).  Without plasma to fill up with, the beam's parts and the bins' remainders have to be fewer than
+// the workgroups, or some take two (16 x 24 x 292, beam of 2.0 M: 0.40 ms a step in 7680, 0.38 in 9216).
+int split_chunk(const Params &P, int64_t n_beam) {
     int lds, threads;
     step_shape(P.tx, P.ty, P.tz, lds, threads);
     const int64_t wgs = P.ty == 1 ? 512 : 256;
     const int64_t plasma = P.has_plasma ? sheet_particles(P) / P.plane * P.ppz * P.tx * P.ty * P.tz : 0;
-    const int64_t part = plasma / std::max<int64_t>(1, wgs / P.nbins);
-    const int64_t rounds = std::max(2 * n / (5 * wgs * threads), (part + threads - 1) / threads);
-    return threads * (int)std::min<int64_t>(std::max<int64_t>(rounds, 1), CH / threads);
+    const int64_t part = std::max(n_beam / (P.has_plasma ? wgs : wgs - wgs / 4),
+                                  plasma / std::max<int64_t>(1, wgs / P.nbins));
+    return threads * (int)std::min<int64_t>(std::max<int64_t>((part + threads - 1) / threads, 1), CH / threads);
 }
 
 // overflow tails of the previous step: untiled path, one particle per thread,
