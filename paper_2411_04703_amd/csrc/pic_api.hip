@@ -578,7 +578,9 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->fc_rho = (double *)(A + off[26]);
     }
     hipError_t e = hipMemsetAsync(c->dflags, 0, 256, c->st);
-    if (e == hipSuccess) e = hipMemsetAsync(A + off[9], 0, 8 * P.nz, c->st);
+    // the ion profile; in FP32 mode both, which alternate whether or not the run has ions that write them
+    if (e == hipSuccess)
+        e = hipMemsetAsync(A + off[9], 0, (pl.precision == PIC_FP64_PLAIN ? 8 : 16) * P.nz, c->st);
     if (pl.precision == PIC_FP64_PLAIN) {
         for (int k = 0; k < 3; ++k) {
             c->E64[k] = (double *)(A + off[k]);
