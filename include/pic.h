@@ -346,7 +346,10 @@ PIC_API pic_status pic_lab_groups(pic_ctx *c, const pic_lab_groups_spec *spec, v
  * of a DEVICE buffer of layout.state_bytes, between steps.  A snapshot
  * restores into any context of the same configuration and continues
  * identically (bit for bit in FP32 mode).  Used for resume and by the
- * adjoint's recomputation (FP64 mode). */
+ * adjoint's recomputation (FP64 mode).  pic_set_state() returns PIC_ESTATE for
+ * a snapshot of another configuration or layout; FP64 snapshots of the layout
+ * that lost the last cells of B_z where nx ny nz is no multiple of 32 are
+ * refused so on such grids. */
 PIC_API pic_status pic_get_state(pic_ctx *c, void *dst);
 PIC_API pic_status pic_set_state(pic_ctx *c, const void *src);
 

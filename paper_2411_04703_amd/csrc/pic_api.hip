@@ -292,11 +292,11 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         off[26] = take(8 * (uint64_t)P.nc);      // and its node charge
     }
     pl.arena = a;
-    // state: header + E, B + particles
-    uint64_t fb = o->precision == PIC_FP64_PLAIN ? 8 : 4;
-    uint64_t st = 256 + al256(6 * fb * P.nc);
+    // state: header + E, B (each array on 256 bytes) + particles
+    uint64_t st;
     if (o->precision == PIC_FP64_PLAIN)
-        st += al256(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1)) + al256(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));
+        st = 256 + 6 * al256(8 * (uint64_t)P.nc) + al256(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1)) +
+             al256(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));
     else
         st = 256 + split_state_payload(P.nc, (int64_t)off[20] + pl.ovf_b, (int64_t)off[21] + pl.ovf_p, off[23],
                                        pl.record);
@@ -979,10 +979,18 @@ struct StateHeader {
     double bw, win_x0, win_t0;
 };
 
+// First word of a snapshot.  FP64 ones held E and B as one block of 48 bytes a cell once: on grids whose
+// arrays are no multiple of 256 bytes (32 cells) the block ended before B_z did.  Those are refused, by
+// another word here (their size differs on most of these grids, not on all).
+static uint64_t state_magic(const Ctx &c) {
+    return 0x5049435354415445ull + (c.precision == PIC_FP64_PLAIN && c.P.nc % 32 ? 1 : 0);
+}
+
 static StatePieces state_pieces(Ctx &c) {
     StatePieces s;
     if (c.precision == PIC_FP64_PLAIN) {
-        s.add(c.E64[0], 8 * 6 * (uint64_t)c.P.nc);
+        for (int k = 0; k < 3; ++k) s.add(c.E64[k], 8 * (uint64_t)c.P.nc);
+        for (int k = 0; k < 3; ++k) s.add(c.B64[k], 8 * (uint64_t)c.P.nc);
         s.add(c.b64.x, 60 * (uint64_t)std::max<int64_t>(c.cap_b, 1));
         s.add(c.p64.x, 60 * (uint64_t)std::max<int64_t>(c.cap_p, 1));
     } else {
@@ -1040,7 +1048,7 @@ static pic_status copy_state(Ctx &c, char *dev, const StateHeader *save) {
 
 pic_status pic_get_state(pic_ctx *c, void *dst) {
     if (!c || !dst) return PIC_EINVAL;
-    const StateHeader h = {0x5049435354415445ull, c->state_bytes, c->step, c->k0, c->sh_lo, c->sh_hi,
+    const StateHeader h = {state_magic(*c), c->state_bytes, c->step, c->k0, c->sh_lo, c->sh_hi,
                            c->nb_slots, c->np_slots, c->cur32, c->precision, c->bw, c->win_x0, c->win_t0};
     pic_status st = copy_state(*c, (char *)dst, &h);
     if (st != PIC_OK) return st;
@@ -1053,7 +1061,7 @@ pic_status pic_set_state(pic_ctx *c, const void *src) {
     StateHeader h;
     PIC_HIP(*c, hipMemcpyAsync(&h, src, sizeof h, hipMemcpyDeviceToHost, c->st));
     PIC_HIP(*c, hipStreamSynchronize(c->st));
-    if (h.magic != 0x5049435354415445ull || h.bytes != c->state_bytes || h.precision != c->precision) {
+    if (h.magic != state_magic(*c) || h.bytes != c->state_bytes || h.precision != c->precision) {
         c->err = "pic_set_state: snapshot does not belong to this configuration";
         return PIC_ESTATE;
     }
