@@ -353,7 +353,7 @@ __device__ inline void push_vay_adj(double dt, const double u[3], const double E
     for (int d = 0; d < 3; ++d) lu[d] += lv0[d] / g0 - u[d] * uv / (g0 * g0 * g0);
 }
 
-// adjoint of the particles that no list holds (dead slots): zero
+// adjoint of the particles that no list holds (dead slots, and live ones that the step takes out): zero
 __global__ void __launch_bounds__(AT) k_adj_dead(int64_t n, const uint32_t *key, int64_t nb, double *lb, int64_t capb,
                                                  double *lp, int64_t capp) {
     const int64_t q = (int64_t)blockIdx.x * AT + threadIdx.x;
@@ -712,7 +712,7 @@ pic_status adjoint_step(Ctx &c, double *lam, double grad[2]) {
     if (n > 0) {
         const int grid = std::min(c.ncu, 512);
         const bool flat = tiles64_flat(P);
-        tiles64_build(c, b, p, grid);
+        tiles64_build(c, b, p, grid, false);
         hipLaunchKernelGGL(k_adj_dead, dim3(nblocks(n, AT)), dim3(AT), 0, c.st, n, c.tiles.key, b.n, Lb.x[0], b.cap,
                            Lp.x[0], p.cap);
         const Bounds64 W(P, S.k0, S.k0n);

@@ -46,7 +46,8 @@ uint64_t tiles64_bytes(const Params &P, int64_t slots) {
 // table of bins and adds each bin's count to the global one once: a beam's particles come in no
 // order and crowd a few hundred bins, whose counters took 0.60 ms for 4.2 M particles when every
 // wave added to them (0.07 ms with the table).  A particle that finds no slot in 16 probes counts
-// globally.  A live particle that is not finite or outside the window is taken out.
+// globally.  A live particle that is not finite or outside the window (positions a caller wrote) is not
+// listed; the step, which passes its flags, takes it out, the other users leave the state as it is.
 constexpr int CT = 1024, HB = 13;
 template <int PPT>
 __global__ void __launch_bounds__(CT) k_tile_count(Params P, Bounds64 W, Species64 b, Species64 p, int lgx, int lgy,
@@ -72,7 +73,7 @@ __global__ void __launch_bounds__(CT) k_tile_count(Params P, Bounds64 W, Species
             int i, j, l;
             if (locate64(P, W, x, y, z, i, j, l)) {
                 key[v] = (uint32_t)((i >> lgx) + T.ntx * ((j >> lgy) + T.nty * (l >> lgz)));
-            } else {
+            } else if (flags) {
                 S.alive()[s] = 0;
                 if (!(isfinite(x) && isfinite(y) && isfinite(z))) atomicOr(flags, DFLAG_NONFINITE);
             }
@@ -176,7 +177,8 @@ __global__ void __launch_bounds__(LT) k_tile_scatter(int64_t n, TileList T) {
     if (key != NO_BIN) T.list[T.off[key] + T.rank[q]] = (uint32_t)q;
 }
 
-void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid) {
+void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid, bool take_out) {
+    int32_t *const flags = take_out ? c.dflags : nullptr;
     const int64_t n = b.n + p.n;
     const bool flat = tiles64_flat(c.P);
     c.tiles.chunk = chunk_of(n);
@@ -184,10 +186,10 @@ void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid) {
     const int lgx = 3, lgy = flat ? 0 : 3, lgz = flat ? 4 : 2;
     if (n >= (int64_t)1 << 21)  // many particles a thread where there are blocks enough all the same
         hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(n, 8 * CT)), dim3(CT), 0, c.st, c.P, W, b, p, lgx, lgy,
-                           lgz, c.tiles, c.dflags);
+                           lgz, c.tiles, flags);
     else if (n > 0)
         hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(n, CT)), dim3(CT), 0, c.st, c.P, W, b, p, lgx, lgy, lgz,
-                           c.tiles, c.dflags);
+                           c.tiles, flags);
     hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, c.st, c.tiles, grid / 8);
     if (n > 0) hipLaunchKernelGGL(k_tile_scatter, dim3(nblocks(n, LT)), dim3(LT), 0, c.st, n, c.tiles);
 }
@@ -400,7 +402,7 @@ void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f) {
         p{c.p64.x, std::max<int64_t>(c.cap_p, 1), c.np_slots};
     if (b.n + p.n <= 0) return;
     const int grid = 2 * c.ncu;
-    tiles64_build(c, b, p, grid);
+    tiles64_build(c, b, p, grid, true);
     if (tiles64_flat(c.P))
         launch_step<Geom2D>(c, S, b, p, f, grid);
     else
@@ -466,7 +468,7 @@ void rho64(Ctx &c, double *rho, int mask) {
         p{c.p64.x, std::max<int64_t>(c.cap_p, 1), mask & 2 ? c.np_slots : 0};
     if (b.n + p.n <= 0) return;
     const int grid = 4 * c.ncu;  // four workgroups of 512 fill a compute unit
-    tiles64_build(c, b, p, grid);
+    tiles64_build(c, b, p, grid, false);
     const Bounds64 W(P, c.k0, c.k0);
     const int k0r = (int)(c.k0 % P.nz);
     if (tiles64_flat(P))

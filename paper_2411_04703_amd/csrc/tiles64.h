@@ -263,7 +263,8 @@ __device__ inline Raw64 load_raw64(const Species64 &sb, const Species64 &sp, uin
 // host side (k_tiles64.hip)
 bool tiles64_flat(const Params &P);  // two-dimensional tiles?
 // lists of the live particles of beam and plasma (either may be empty) for the window of c.k0
-// and for a kernel of `grid` workgroups (a multiple of 8) that takes their items from ItemQueue64
-void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid);
+// and for a kernel of `grid` workgroups (a multiple of 8) that takes their items from ItemQueue64;
+// take_out: live particles that no tile can hold are marked dead (the step), else only left out
+void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid, bool take_out);
 
 }  // namespace pic
