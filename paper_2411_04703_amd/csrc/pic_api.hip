@@ -1027,10 +1027,20 @@ __global__ void __launch_bounds__(256) k_state_copy(StatePieces s, char *dev, in
     }
 }
 
+// Can a kernel of the context reach all of a caller's buffer?  Device memory of another GPU may not be
+// mapped here, nor host memory: the runtime's copies reach both.
+static bool on_device(const Ctx &c, const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeDevice && at.device == c.device;
+    (void)hipGetLastError();  // an address the runtime does not know
+    return false;
+}
+
 // the pieces between the context and a snapshot; one by one where the caller's buffer is not on 16 bytes
+// or not in the device's own memory
 static pic_status copy_state(Ctx &c, char *dev, const StateHeader *save) {
     const StatePieces s = state_pieces(c);
-    if (((uintptr_t)dev & 15) == 0) {
+    if (((uintptr_t)dev & 15) == 0 && on_device(c, dev)) {
         uint64_t bytes = 0;
         for (int k = 0; k < s.n; ++k) bytes += s.bytes[k];
         const dim3 grid((unsigned)std::min<uint64_t>(std::max<uint64_t>(bytes / (64 * 256), 1), 8192));
@@ -1039,10 +1049,10 @@ static pic_status copy_state(Ctx &c, char *dev, const StateHeader *save) {
         PIC_HIP(c, hipGetLastError());
         return PIC_OK;
     }
-    if (save) PIC_HIP(c, hipMemcpyAsync(dev, save, sizeof *save, hipMemcpyHostToDevice, c.st));
+    if (save) PIC_HIP(c, hipMemcpyAsync(dev, save, sizeof *save, hipMemcpyDefault, c.st));
     for (int k = 0; k < s.n; ++k)
         PIC_HIP(c, hipMemcpyAsync(save ? dev + s.at[k] : s.mine[k], save ? s.mine[k] : dev + s.at[k], s.bytes[k],
-                                  hipMemcpyDeviceToDevice, c.st));
+                                  hipMemcpyDefault, c.st));
     return PIC_OK;
 }
 
@@ -1059,7 +1069,7 @@ pic_status pic_get_state(pic_ctx *c, void *dst) {
 pic_status pic_set_state(pic_ctx *c, const void *src) {
     if (!c || !src) return PIC_EINVAL;
     StateHeader h;
-    PIC_HIP(*c, hipMemcpyAsync(&h, src, sizeof h, hipMemcpyDeviceToHost, c->st));
+    PIC_HIP(*c, hipMemcpyAsync(&h, src, sizeof h, hipMemcpyDefault, c->st));
     PIC_HIP(*c, hipStreamSynchronize(c->st));
     if (h.magic != state_magic(*c) || h.bytes != c->state_bytes || h.precision != c->precision) {
         c->err = "pic_set_state: snapshot does not belong to this configuration";
