@@ -1141,6 +1141,8 @@ pic_status pic_state_to_fp64(const pic_ctx *src, pic_ctx *dst) {
         return PIC_ENOMEM;
     }
     Ctx &d = *dst;
+    // src's steps are asynchronous on its own stream, the hand-over runs on dst's
+    if (src->st != d.st) PIC_HIP(d, hipStreamSynchronize(src->st));
     // fields: same ring layout once the window origin is copied; particles to their slots, those without
     // a particle dead
     Widen W{{}, {}, {}, d.jion64, d.b64.alive, d.p64.alive, B.nc, B.nz, std::max<int64_t>(d.cap_b, 1),
