@@ -1184,10 +1184,13 @@ uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, in
 // here), but a plasma bin in no more parts than there are workgroups for all of them (2304 in the
 // third).  Without plasma to fill up with, the beam's parts and the bins' remainders have to be fewer than
 // the workgroups, or some take two (16 x 24 x 292, beam of 2.0 M: 0.40 ms a step in 7680, 0.38 in 9216).
-int split_chunk(const Params &P, int64_t n_beam) {
+// The workgroups counted are those of the step kernel's grid on the 256 CUs: one a CU, two on x-z tiles, or
+// as many as wg_per_cu leaves (x-z, wg_per_cu 1).
+int split_chunk(const Params &P, int64_t n_beam, int wg_per_cu) {
     int lds, threads;
     step_shape(P.tx, P.ty, P.tz, lds, threads);
-    const int64_t wgs = P.ty == 1 ? 512 : 256;
+    const int most = P.ty == 1 ? 2 : 1;
+    const int64_t wgs = 256 * (wg_per_cu > 0 ? std::min(wg_per_cu, most) : most);
     const int64_t plasma = P.has_plasma ? sheet_particles(P) / P.plane * P.ppz * P.tx * P.ty * P.tz : 0;
     const int64_t part = std::max(n_beam / (P.has_plasma ? wgs : wgs - wgs / 4),
                                   plasma / std::max<int64_t>(1, wgs / P.nbins));

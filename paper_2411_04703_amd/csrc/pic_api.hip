@@ -271,7 +271,7 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         off[12] = take(2 * split_buffer_bytes(sb, cp + pl.ovf_p));
         uint64_t bins_bytes = 8 * (uint64_t)(nbins + 1) * 4 + 4 * (uint64_t)nbins * 4 + 256;
         off[13] = take(bins_bytes);
-        pl.chunk = split_chunk(P, pl.cap_b);
+        pl.chunk = split_chunk(P, pl.cap_b, o->wg_per_cu);
         uint64_t wl_bytes = 16 * (uint64_t)(P.nz + 8) + 256 + split_items_bytes(P, cb, cp, pl.chunk) +
                             4 * (uint64_t)(2 * nbins + 8) + 8 * (uint64_t)(nbins + 8) + 8192 + 4096;
         off[14] = take(wl_bytes);

@@ -150,7 +150,7 @@ void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma
 // FP32 split particles (k_split32.hip)
 void split_setup(Ctx &c);
 bool split_tile_supported(int tx, int ty, int tz);  // tiles the FP32 step kernel is built for
-int split_chunk(const Params &P, int64_t n_beam);         // particles per work item of the FP32 step
+int split_chunk(const Params &P, int64_t n_beam, int wg_per_cu);  // particles per work item of the FP32 step
 uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, int chunk);
 uint64_t split_state_payload(int64_t nc, int64_t slots_b, int64_t slots_p, uint64_t bins_bytes, int record);
 void split_export64(const Ctx &c, Part64 beam, Part64 plasma, hipStream_t st);  // record mode: particles to slots
