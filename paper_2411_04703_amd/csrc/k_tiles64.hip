@@ -39,7 +39,17 @@ static int64_t bins_of(const Params &P) {
 
 uint64_t tiles64_bytes(const Params &P, int64_t slots) {
     const uint64_t nb = (uint64_t)bins_of(P), n = (uint64_t)std::max<int64_t>(slots, 1);
-    return 2 * al(4 * nb) + 3 * al(4 * n) + al(16 * (nb + n / CHUNK_MIN + 16)) + 256 * 9;
+    return 2 * al(4 * nb) + al(16 * (nb + n / CHUNK_MIN + 16)) + 256 * 9;
+}
+
+uint64_t tiles64_list_bytes(int64_t slots) { return 3 * al(4 * (uint64_t)std::max<int64_t>(slots, 1)); }
+
+// the arrays with an entry per slot, in `room`
+static void place_lists(TileList &T, char *room, int64_t slots) {
+    const uint64_t n = al(4 * (uint64_t)std::max<int64_t>(slots, 1));
+    T.key = (uint32_t *)room;
+    T.rank = (uint32_t *)(room + n);
+    T.list = (uint32_t *)(room + 2 * n);
 }
 
 // Bin of every live particle and its place there.  A block counts its particles in an LDS hash
@@ -182,6 +192,8 @@ void tiles64_build(Ctx &c, Species64 b, Species64 p, int grid, bool take_out) {
     const int64_t n = b.n + p.n;
     const bool flat = tiles64_flat(c.P);
     c.tiles.chunk = chunk_of(n);
+    // the compaction's buffer, whichever of the two it is now
+    if (!c.tiles.room) place_lists(c.tiles, (char *)c.p64alt.x, c.cap_b + c.cap_p);
     const Bounds64 W(c.P, c.k0, c.k0);
     const int lgx = 3, lgy = flat ? 0 : 3, lgz = flat ? 4 : 2;
     if (n >= (int64_t)1 << 21)  // many particles a thread where there are blocks enough all the same
@@ -360,7 +372,7 @@ k_step64(Params P, StepCtx S, Bounds64 W, Species64 sb, Species64 sp, TileList T
 
 template <class G> static constexpr int step_lds() { return 8 * (G::NF + G::NJ); }
 
-pic_status tiles64_carve(Ctx &c, char *base, int64_t slots) {
+pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots) {
     const uint64_t nb = (uint64_t)bins_of(c.P), n = (uint64_t)std::max<int64_t>(slots, 1);
     TileList &T = c.tiles;
     tiles64_dims(c.P, T.ntx, T.nty, T.ntz);
@@ -372,9 +384,8 @@ pic_status tiles64_carve(Ctx &c, char *base, int64_t slots) {
     };
     T.cnt = (uint32_t *)take(4 * nb);
     T.off = (uint32_t *)take(4 * nb);
-    T.key = (uint32_t *)take(4 * n);
-    T.rank = (uint32_t *)take(4 * n);
-    T.list = (uint32_t *)take(4 * n);
+    T.room = room;
+    if (room) place_lists(T, room, slots);
     T.items = (int4 *)take(16 * (nb + n / CHUNK_MIN + 16));
     T.qnext = (int32_t *)take(256 * 8);
     T.nitems = (int32_t *)take(256);

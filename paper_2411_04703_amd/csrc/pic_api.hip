@@ -42,6 +42,7 @@ struct Plan {
     int precision, record, check_every;
     int64_t cap_b, cap_p, ovf_b, ovf_p;
     int chunk;
+    enum { LISTS_OWN, LISTS_IN_COMPACTION, LISTS_IN_STAGING } lists = LISTS_OWN;  // FP64 mode
     uint64_t off[40];
     uint64_t arena, state;
 };
@@ -249,7 +250,17 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         off[11] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1));   // beam
         off[12] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));   // plasma
         off[13] = pl.record ? 0 : take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));  // plasma (compaction)
-        off[27] = take(tiles64_bytes(P, pl.cap_b + pl.cap_p));                          // tile lists
+        off[27] = take(tiles64_bytes(P, pl.cap_b + pl.cap_p));  // tiles and work items
+        // The particle lists live from their building to the kernel behind it.  They share what is idle
+        // then: the buffer that the next compaction fills, or the normals' staging, which the beam's
+        // initialisation has read; room of their own (12 bytes a slot) only where neither holds them.
+        const uint64_t lists = tiles64_list_bytes(pl.cap_b + pl.cap_p);
+        if (!pl.record && lists <= 60 * (uint64_t)pl.cap_p)
+            pl.lists = Plan::LISTS_IN_COMPACTION;
+        else if (lists <= 48 * (uint64_t)pl.cap_b)
+            pl.lists = Plan::LISTS_IN_STAGING;
+        else
+            off[30] = take(lists);
     } else {
         pl.cap_p = P.has_plasma ? fill : 0;
         for (int k = 0; k < 6; ++k) off[k] = take(4 * P.nc);  // E B float
@@ -593,7 +604,11 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->p64 = carve64(A + off[12], c->cap_p);
         if (!pl.record) c->p64alt = carve64(A + off[13], c->cap_p);
         if (e == hipSuccess) e = hipMemsetAsync(c->b64.alive, 0, 4 * std::max<int64_t>(c->cap_b, 1), c->st);
-        if (e == hipSuccess && tiles64_carve(*c, A + off[27], c->cap_b + c->cap_p) != PIC_OK) e = hipErrorUnknown;
+        char *room = pl.lists == Plan::LISTS_IN_COMPACTION ? nullptr
+                     : pl.lists == Plan::LISTS_IN_STAGING  ? (char *)c->stage
+                                                           : A + off[30];
+        if (e == hipSuccess && tiles64_carve(*c, A + off[27], room, c->cap_b + c->cap_p) != PIC_OK)
+            e = hipErrorUnknown;
         if (e == hipSuccess && pl.record && adjoint_setup(*c) != PIC_OK) e = hipErrorUnknown;
     } else {
         for (int k = 0; k < 3; ++k) {

@@ -36,6 +36,7 @@ struct TileList {
     int ntx, nty, ntz, nbins, chunk;
     uint32_t *cnt;          // per bin, zero between uses
     uint32_t *off;          // per bin, first list entry
+    char *room;             // of the three below; null: in the plasma buffer that compaction fills next
     uint32_t *key, *rank;   // per particle (numbered through): its bin (NO_BIN: not listed), place in it
     uint32_t *list;         // particles bin by bin
     int4 *items;            // (bin, first entry, end entry, 0): at most `chunk` particles of one bin
@@ -141,8 +142,9 @@ void launch_inject64(const Params &P, int64_t l0, int64_t nsheets, double t, Par
 int64_t compact64(Ctx &c, Part64 src, Part64 dst, int64_t n);  // returns survivors (synchronising)
 
 // FP64 particles on cell tiles (k_tiles64.hip)
-uint64_t tiles64_bytes(const Params &P, int64_t slots);  // arena bytes of the particle lists
-pic_status tiles64_carve(Ctx &c, char *base, int64_t slots);
+uint64_t tiles64_bytes(const Params &P, int64_t slots);  // arena bytes of the tiles and work items
+uint64_t tiles64_list_bytes(int64_t slots);              // and of the particle lists (room)
+pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots);
 void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f);  // gather, push, move, deposit of both species
 
 void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma (bit 1) added into rho (ring order)
