@@ -373,9 +373,11 @@ PIC_API pic_status pic_adjoint_seed_bunching(pic_ctx *c, double bunch_period_cel
 PIC_API pic_status pic_adjoint_step(pic_ctx *c, void *lam, double grad[2]);
 
 /* Kernel timing with HIP events recorded on the context stream around each
- * launch class: [0] fused particle kernels (gather, push, deposit), [1] FDTD
- * (both B half steps, E update, Mur faces), [2] window, ion current,
- * injection and binning, [3] whole steps.  pic_timing(c, 1) clears and starts
+ * launch class: [0] particle kernels (gather, push, deposit; in FP32 mode the
+ * overflow tails and the plasma sheets that enter share a second launch, and
+ * a second timed region, of this class), [1] FDTD (B, E update, Mur faces),
+ * [2] window, ion current, work lists and, in FP64 mode, injection, [3] whole
+ * steps.  pic_timing(c, 1) clears and starts
  * collecting, pic_timing(c, 0) stops.  pic_timing_read() synchronises and
  * returns the summed milliseconds and the number of timed launches per class. */
 PIC_API pic_status pic_timing(pic_ctx *c, int32_t enable);

@@ -144,13 +144,6 @@ template <typename T> __device__ inline T spline2(T d) {
     return T(0);
 }
 
-template <typename T> __device__ inline T dspline2(T d) {
-    T a = d < T(0) ? -d : d;
-    if (a <= T(0.5)) return T(-2) * d;
-    if (a < T(1.5)) return d >= T(0) ? -(T(1.5) - d) : (T(1.5) + d);
-    return T(0);
-}
-
 // Three weights of the nearest node n and its neighbours for offset d = x - n, |d| <= 1/2.
 template <typename T> __device__ inline void weights3(T d, T w[3]) {
     T a = T(0.5) - d, b = T(0.5) + d;

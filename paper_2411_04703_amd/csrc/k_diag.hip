@@ -6,7 +6,7 @@
 // modulation at the boosted undulator period and half of it (section 3); the
 // bunching factor |sum w exp(i k z')| / sum w is taken at fixed t' in the
 // boosted frame.  All sums are FP64 with per-block partials, reduced on the
-// device in a fixed order (k_reduce_partials), so a diagnostic of a given
+// device in a fixed order (k_reduce_rows), so a diagnostic of a given
 // particle order is reproducible bit for bit.
 #include <math.h>
 #include <string.h>

@@ -14,8 +14,9 @@
 // the bins are re-laid out from the counts when the periodic host check finds
 // overflow or a bin close to its capacity.
 //
-// Work: one (bin, chunk) item at a time per workgroup, items taken from an
-// atomic counter by a persistent grid.  Per item: stage the tile's E, B (+
+// Work: one item (a bin, or a part of a crowded one) at a time per workgroup of
+// a persistent grid, taken from sixteen queues (slab of bins x species), each
+// with a counter.  Per item: stage the tile's E, B (+
 // halo) in LDS, gather with quadratic shapes, push (FP32; FP64 above a
 // Lorentz-factor threshold), move, and deposit Esirkepov currents as 64-bit
 // fixed-point integers into an LDS tile that is flushed with global 64-bit
@@ -46,7 +47,6 @@ struct Store {
     int32_t *ovf[2];       // per-buffer overflow counts
     int64_t bin_slots;     // slots of the bin region
     int64_t ovf_cap;
-    int64_t n_flat;        // init only
 };
 
 // A work item: particles [start, end) of a bin, which are the input slots from b0 on.
@@ -277,17 +277,11 @@ __device__ inline void unpack_cell(const Params &P, int cell, int &i, int &j, in
 // periodic wrap of an index at most one period outside [0, n)
 __device__ inline int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
-// linear index of cell (i, j, ring plane p), i and j at most one period outside the grid;
-// NY1: a two-dimensional x-z grid (ny = 1, tile edge 1 in y), where every j is row 0
-template <bool NY1 = false> __device__ inline int64_t near_cell(const Params &P, int i, int j, int p) {
-    return (int64_t)wrap1(i, P.nx) + (int64_t)P.nx * ((NY1 ? (int64_t)0 : (int64_t)wrap1(j, P.ny)) + (int64_t)P.ny * p);
+// in-plane index of cell (i, j), both at most one period outside the grid (in 32 bits, as all of an
+// FP32-mode grid: its cell index packs into 31)
+__device__ inline uint32_t near_column(const Params &P, int i, int j) {
+    return (uint32_t)wrap1(i, P.nx) + (uint32_t)P.nx * (uint32_t)wrap1(j, P.ny);
 }
-// the same in 32 bits: an FP32-mode grid has at most 2^31 cells (its cell index packs into 31 bits)
-template <bool NY1 = false> __device__ inline uint32_t near_cell32(const Params &P, int i, int j, int p) {
-    return (uint32_t)wrap1(i, P.nx) +
-           (uint32_t)P.nx * ((NY1 ? 0u : (uint32_t)wrap1(j, P.ny)) + (uint32_t)P.ny * (uint32_t)p);
-}
-
 
 // number of valid particles of bin b in a store
 __device__ inline int bin_count(const int64_t *off, const int32_t *cnt, int b) {
@@ -353,7 +347,7 @@ __device__ inline void ext_plane(const Params &P, int64_t k0, int l, double t, d
     s = (float)sn;
 }
 
-// per step: ext_plane of every logical plane -1 .. nz (entry l + 1)
+// and at the offset oz from it, added to E and B; a_l, cphi, sphi are of the particle's plane (ext_plane)
 __device__ inline void ext32(const Params &P, double a_l, float cphi, float sphi, float oz, float E[3], float B[3]) {
     double a = a_l + P.gR * (double)oz;
     double env, denv;
@@ -900,7 +894,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
             static_assert(G::NF <= SST && G::NE <= SST, "one node per thread");
             auto node = [&](int X) -> uint32_t {
                 const int c = tid / X, a = tid - c * X;
-                return near_cell32<true>(P, I.t0x - 1 + a, 0, 0) + plane_of(c);
+                return (uint32_t)wrap1(I.t0x - 1 + a, P.nx) + plane_of(c);
             };
             if (tid < G::NF) {
                 const uint32_t o = node(G::FX);
@@ -913,7 +907,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
         } else {
             if (tid < NCE) {
                 const int b = tid / G::FX, a = tid - b * G::FX;
-                const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
+                const uint32_t col = near_column(P, I.t0x - 1 + a, I.t0y - 1 + b);
 #pragma unroll
                 for (int c = 0; c < G::FZ; ++c) {
                     const uint32_t o = col + plane_of(c);
@@ -923,7 +917,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
             }
             auto stage_b = [&](int u, int c0) {  // B column u; the wave's first lane has column c0
                 const int b = u / G::EX, a = u - b * G::EX;
-                const uint32_t col = near_cell32<TY == 1>(P, I.t0x - 1 + a, I.t0y - 1 + b, 0);
+                const uint32_t col = near_column(P, I.t0x - 1 + a, I.t0y - 1 + b);
 #pragma unroll
                 for (int c = 0; c < G::EZ; ++c) {
                     const uint32_t o = col + plane_of(c);
@@ -1076,7 +1070,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
                 const int X = e < G::NJX ? G::XX : G::YX, z = h / X, x = h - z * X, l = C.t0z - 2 + z;
                 if (v == 0 || l < 0 || l >= P.nz) continue;
                 long long *J = e < G::NJX ? Jx : e < G::NJX + G::NJY ? Jy : Jz;
-                atomicAdd((unsigned long long *)&J[near_cell32<true>(P, C.t0x - 2 + x, 0, 0) +
+                atomicAdd((unsigned long long *)&J[(uint32_t)wrap1(C.t0x - 2 + x, P.nx) +
                                                    pl * (uint32_t)ring_plane(l, S.k0r, P.nz)],
                           (unsigned long long)v);
             }
@@ -1106,7 +1100,7 @@ k_split_step(Params P, StepCtx S, WorkList W, IOPair iop, FieldsT<float> f, long
                         x = h - y * G::ZX;
                         np = G::ZZ, stride = CZ, lb = G::NJX + G::NJY + h, J = Jz;
                     }
-                    const uint32_t col = near_cell32<TY == 1>(P, C.t0x - 2 + x, C.t0y - 2 + y, 0);
+                    const uint32_t col = near_column(P, C.t0x - 2 + x, C.t0y - 2 + y);
 #pragma unroll 1
                     for (int z = 0; z < NPMAX; ++z) {
                         if (z >= np) continue;
@@ -1182,8 +1176,13 @@ uint64_t split_items_bytes(const Params &P, int64_t slots_b, int64_t slots_p, in
 //   96 x 32 x 296, beam of 2.4 M, plasma and ions              635  530  472  382  366  355
 // So: about one part of the beam for each workgroup of the 256 CUs (768, 768, 768, 4608, 9216, 9216
 // here), but a plasma bin in no more parts than there are workgroups for all of them (2304 in the
-// third).  Without plasma to fill up with, the beam's parts and the bins' remainders have to be fewer than
-// the workgroups, or some take two (16 x 24 x 292, beam of 2.0 M: 0.40 ms a step in 7680, 0.38 in 9216).
+// third).  Without plasma to fill up with, where the beam's parts and the bins' remainders are more than
+// the workgroups some take two, and on narrow grids that is slower than items of 9216: three quarters of
+// the workgroups are counted there.  us a step, so / with a part for each workgroup / items of 9216:
+// 16 x 24 x 292, beam of 2.0 M 186 / 199 / 194; 64 x 64 x 256, 0.3 M 83 / 76 / 186, 0.6 M 109 / 102 / 199,
+// 1.05 M 145 / 143 / 202, 2.0 M 228 / 229 / 240; 96 x 64 x 128, 1.4 M 164 / 153 / 196; 512 x 1 x 1024, 1.0 M
+// 86 / 82 / 183: up to a tenth is given up so that none is slower than the large items (measured with
+// the step before its launches were joined).
 // The workgroups counted are those of the step kernel's grid on the 256 CUs: one a CU, two on x-z tiles, or
 // as many as wg_per_cu leaves (x-z, wg_per_cu 1).
 int split_chunk(const Params &P, int64_t n_beam, int wg_per_cu) {
@@ -1652,7 +1651,6 @@ static pic_status bins_from_flat(Ctx &c) {
         if (s != PIC_OK) return s;
         // the flat list is the "overflow" of buffer 1: no bin entries
         PIC_HIP(c, hipMemsetAsync(X.s[sp].cnt[1], 0, 4 * nb, c.st));
-        X.s[sp].n_flat = nflat[sp];
     }
     // the flat lists are read as overflow tails that start at slot 0 and may fill the whole buffer
     build_worklist(c, 1, nullptr);

@@ -269,8 +269,8 @@ template <class G, int C> __device__ inline void deposit_lds(double *Js, const i
 // (162 reads and 27 to 144 FP64 adds of 8 clocks a wave), the beam's 0.9 ms by its slots, which are
 // in no order (a 64-byte line for every 8 bytes read or written; 0.4 ms were they in tile order).
 // Two 512-thread workgroups share a CU, so that one's rounds run under the other's staging and
-// flush; 512 is the particles of a tile at 2 per cell (384 threads: 2.9 ms, 256: 2.2 ms).  128
-// VGPRs spill 30, nearly all outside the particle loop.  The next item is claimed when the current
+// flush; 512 is the particles of a tile at 2 per cell (384 threads: 2.9 ms, 256: 2.2 ms).  Of
+// its 128 VGPRs 16 are spilled (14 on x-z tiles).  The next item is claimed when the current
 // one starts; loading its fields and particles across the flush as well took 10 to 40 % longer
 // (spills).
 template <class G>

@@ -33,7 +33,7 @@ static pic_status fail(std::string *err, pic_status s, const std::string &msg) {
 // ---------------------------------------------------------------- derivation
 // FP32 grids up to this many cells hold E and B twice, so that a step updates them in one pass
 // (k_fields); 24 bytes a cell, 3.2 GB at the limit.  Larger grids keep the memory for cells and
-// update in place, in two passes and one over the faces.
+// update in place, in two passes (B; E with the faces) and one over a plane when the window shifts.
 constexpr int64_t FIELDS_TWICE = (int64_t)1 << 27;
 
 struct Plan {

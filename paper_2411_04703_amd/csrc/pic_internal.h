@@ -19,7 +19,7 @@ struct Part64 {
 };
 
 // FP32 split particle SoA: logical cell index (i + nx (j + ny l), l = window plane)
-// plus FP32 offsets in [0, 1), FP32 momenta and weight.
+// plus FP32 offsets from the cell's centre in [-1/2, 1/2), FP32 momenta and weight.
 struct Part32 {
     int32_t *cell;
     float *ox, *oy, *oz, *ux, *uy, *uz, *w;
