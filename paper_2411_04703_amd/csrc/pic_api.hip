@@ -1020,13 +1020,14 @@ static StatePieces state_pieces(Ctx &c) {
 __global__ void __launch_bounds__(256) k_state_copy(StatePieces s, char *dev, int save, StateHeader h) {
     const uint64_t t = threadIdx.x;
     if (save && blockIdx.x == 0 && t == 0) *(StateHeader *)dev = h;
+    uint32_t b0 = blockIdx.x;  // a piece's first round; the next piece goes on from the workgroup this one ends at
     for (int k = 0; k < s.n; ++k) {
         const char *src = save ? s.mine[k] : dev + s.at[k];
         char *dst = save ? dev + s.at[k] : s.mine[k];
         const uint64_t n16 = s.bytes[k] / 16;
         const uint4 *a = (const uint4 *)src;
         uint4 *b = (uint4 *)dst;
-        for (uint64_t i = (uint64_t)blockIdx.x * 1024 + t; i - t < n16; i += (uint64_t)gridDim.x * 1024) {
+        for (uint64_t i = (uint64_t)b0 * 1024 + t; i - t < n16; i += (uint64_t)gridDim.x * 1024) {
             if (i - t + 1024 <= n16) {
                 const uint4 v0 = a[i], v1 = a[i + 256], v2 = a[i + 512], v3 = a[i + 768];
                 b[i] = v0;
@@ -1039,6 +1040,8 @@ __global__ void __launch_bounds__(256) k_state_copy(StatePieces s, char *dev, in
         }
         if (blockIdx.x == 0 && t < (s.bytes[k] - 16 * n16) / 4)
             ((uint32_t *)(dst + 16 * n16))[t] = ((const uint32_t *)(src + 16 * n16))[t];
+        const uint32_t used = (uint32_t)((n16 + 1023) / 1024 % gridDim.x);
+        b0 = b0 >= used ? b0 - used : b0 + gridDim.x - used;
     }
 }
 
