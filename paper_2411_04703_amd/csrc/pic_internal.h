@@ -40,6 +40,7 @@ struct TileList {
     uint32_t *key, *rank;   // per particle (numbered through): its bin (NO_BIN: not listed), place in it
     uint32_t *list;         // particles bin by bin
     int4 *items;            // (bin, first entry, end entry, 0): at most `chunk` particles of one bin
+    uint2 *totals;          // of each block of bins: particles, items (large grids)
     int32_t *nitems, *qnext;
 };
 // partial sums of a reverse step: one of each of 256 workgroups, two of each of up to 512
