@@ -105,16 +105,10 @@ __device__ inline double wave_sums16(double v[16]) {
     return v[0] + __shfl_xor(v[0], 1);
 }
 
-// A particle into a block's LDS table of lab groups (lab_table_*): called by every lane of a wave, `in`
-// where it has a particle.  Neighbouring particles share groups, and 64 lanes adding to one entry add
-// one after the other; a group of eight lanes or more is summed across the wave and added once.  The
-// beam of 4.2 M particles in 64 slices: 8.0 ms lane by lane, 0.34 ms with a sum of each value by
-// itself, 0.16 ms with wave_sums16.
-__device__ inline void lab_group_add_wave(double *tab, const LabGroupSpec &G, const Params &P, double t, bool in,
-                                          double x, double y, double z, double ux, double uy, double uz, double w) {
-    const int g = in ? lab_group_of(G, z, uz) : -1;
-    bool mine = g >= 0;
-    double v[LAB_GROUP_VALUES], L[8];
+// the 16 values of a particle in its lab group
+__device__ inline void lab_group_values(const Params &P, double t, double x, double y, double z, double ux, double uy,
+                                        double uz, double w, double v[LAB_GROUP_VALUES]) {
+    double L[8];
     lab_of(P, t, x, y, z, ux, uy, uz, L);
     v[0] = 1.0;
     v[1] = w;
@@ -131,6 +125,43 @@ __device__ inline void lab_group_add_wave(double *tab, const LabGroupSpec &G, co
     v[13] = w * L[5];
     v[14] = w * L[5] * L[5];
     v[15] = w * L[7];
+}
+
+// added to group g of a block's LDS table (lab_table_*) by one lane
+__device__ inline void lab_group_lane(double *tab, int g, const double v[LAB_GROUP_VALUES]) {
+    double *e = tab + LAB_GROUP_VALUES * g;
+#pragma unroll
+    for (int k = 0; k < LAB_GROUP_VALUES; ++k) {
+        if (k == 3)
+            atomicMin(&e[k], v[k]);
+        else if (k == 4)
+            atomicMax(&e[k], v[k]);
+        else
+            atomicAdd(&e[k], v[k]);
+    }
+}
+
+// a particle into the table, by its lane
+__device__ inline void lab_group_add(double *tab, const LabGroupSpec &G, const Params &P, double t, double x, double y,
+                                     double z, double ux, double uy, double uz, double w) {
+    const int g = lab_group_of(G, z, uz);
+    if (g < 0) return;
+    double v[LAB_GROUP_VALUES];
+    lab_group_values(P, t, x, y, z, ux, uy, uz, w, v);
+    lab_group_lane(tab, g, v);
+}
+
+// The same called by every lane of a wave, `in` where it has a particle.  Neighbouring particles share
+// groups, and 64 lanes adding to one entry add one
+// after the other; a group of eight lanes or more is summed across the wave and added once.  The
+// beam of 4.2 M particles in 64 slices: 8.0 ms lane by lane, 0.34 ms with a sum of each value by
+// itself, 0.16 ms with wave_sums16.
+__device__ inline void lab_group_add_wave(double *tab, const LabGroupSpec &G, const Params &P, double t, bool in,
+                                          double x, double y, double z, double ux, double uy, double uz, double w) {
+    const int g = in ? lab_group_of(G, z, uz) : -1;
+    bool mine = g >= 0;
+    double v[LAB_GROUP_VALUES];
+    lab_group_values(P, t, x, y, z, ux, uy, uz, w, v);
     unsigned long long todo = __ballot(mine);
     while (todo) {
         const int lead = __ffsll(todo) - 1, lg = __builtin_amdgcn_readlane(g, lead);
@@ -152,18 +183,10 @@ __device__ inline void lab_group_add_wave(double *tab, const LabGroupSpec &G, co
         if (lane == 32) atomicMax(&e[4], -m);
         if (here) mine = false;
     }
-    if (!mine) return;
-    double *e = tab + LAB_GROUP_VALUES * g;
-#pragma unroll
-    for (int k = 0; k < LAB_GROUP_VALUES; ++k) {
-        if (k == 3)
-            atomicMin(&e[k], v[k]);
-        else if (k == 4)
-            atomicMax(&e[k], v[k]);
-        else
-            atomicAdd(&e[k], v[k]);
-    }
+    if (mine) lab_group_lane(tab, g, v);
 }
+
+void lab_groups_clear(double *out, int ng, hipStream_t st);  // k_diag.hip
 
 // k_split32.hip: partials of the FP32 store's sums into part, one row per workgroup; return the rows
 int split_moments1(Ctx &c, double kb, double *part);

@@ -215,11 +215,15 @@ __global__ void __launch_bounds__(DT) k_lab_groups64(Params P, LabGroupSpec G, P
     lab_table_flush(tab, ng, out);
 }
 
+void lab_groups_clear(double *out, int ng, hipStream_t st) {
+    hipLaunchKernelGGL(k_lab_groups_init, dim3(nblocks(LAB_GROUP_VALUES * ng, DT)), dim3(DT), 0, st, out, ng);
+}
+
 pic_status lab_groups(Ctx &c, const LabGroupSpec &G, double *out) {
     const int ng = G.nz * G.nu;
     const double t = (double)c.step * c.P.dt;
-    hipLaunchKernelGGL(k_lab_groups_init, dim3(nblocks(LAB_GROUP_VALUES * ng, DT)), dim3(DT), 0, c.st, out, ng);
     if (c.precision == PIC_FP64_PLAIN) {
+        lab_groups_clear(out, ng, c.st);
         if (c.nb_slots)
             hipLaunchKernelGGL(k_lab_groups64, dim3(std::min(nblocks(c.nb_slots, DT), 1024)), dim3(DT), 0, c.st, c.P,
                                G, c.b64, c.nb_slots, t, out);

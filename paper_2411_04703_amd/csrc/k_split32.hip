@@ -1967,15 +1967,46 @@ struct BinRanks {
     }
 };
 
-// pref of a store, by one workgroup
+// pref of a store.  A block takes PREFIX_BINS bins at a time; up to FEW_BINS one block goes through them all
+// (2.3 us a time), more get a block each, which starts from the totals of those before it
+// (k_split_totals).  groups: ng lab groups' sums to clear for the kernel that follows, or null.
+constexpr int PREFIX_V = 4, PREFIX_BINS = 1024 * PREFIX_V, FEW_BINS = 4 * PREFIX_BINS;
+
+__global__ void __launch_bounds__(1024) k_split_totals(const int64_t *off, const int32_t *cnt, int nbins,
+                                                       int64_t *totals) {
+    __shared__ int64_t ws[16];
+    int64_t n = 0;
+    for (int v = 0; v < PREFIX_V; ++v) {
+        const int b = (int)blockIdx.x * PREFIX_BINS + v * 1024 + (int)threadIdx.x;
+        n += b < nbins ? bin_count(off, cnt, b) : 0;
+    }
+    for (int h = 32; h > 0; h >>= 1) n += __shfl_down(n, h);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) n += ws[w];
+        totals[blockIdx.x] = n;
+    }
+}
+
 __global__ void __launch_bounds__(1024) k_split_prefix(const int64_t *off, const int32_t *cnt, const int32_t *ovf,
-                                                       int64_t ovf_cap, int nbins, int64_t *pref) {
-    constexpr int V = 4;
+                                                       int64_t ovf_cap, int nbins, const int64_t *totals,
+                                                       int64_t *pref, double *groups, int ng) {
+    constexpr int V = PREFIX_V;
     __shared__ int64_t ws[16], run;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (groups && blockIdx.x == 0) lab_table_clear(groups, ng);
     if (t == 0) run = 0;
     __syncthreads();
-    for (int base = 0; base < nbins; base += 1024 * V) {
+    if (gridDim.x > 1) {  // what the blocks before this one have
+        int64_t n = 0;
+        for (int b = t; b < (int)blockIdx.x; b += 1024) n += totals[b];
+        for (int h = 32; h > 0; h >>= 1) n += __shfl_down(n, h);
+        if (lane == 0) atomicAdd((unsigned long long *)&run, (unsigned long long)n);
+        __syncthreads();
+    }
+    const int end = gridDim.x == 1 ? nbins : min(nbins, ((int)blockIdx.x + 1) * PREFIX_BINS);
+    for (int base = (int)blockIdx.x * PREFIX_BINS; base < end; base += PREFIX_BINS) {
         int64_t n[V], sum = 0;
         for (int v = 0; v < V; ++v) {
             const int b = base + t * V + v;
@@ -2000,7 +2031,7 @@ __global__ void __launch_bounds__(1024) k_split_prefix(const int64_t *off, const
         if (t == 1023) run = p;
         __syncthreads();
     }
-    if (t == 0) {
+    if (t == 0 && end == nbins) {
         pref[nbins] = run;
         pref[nbins + 1] = run + min((int64_t)*ovf, ovf_cap);
     }
@@ -2028,13 +2059,17 @@ __global__ void __launch_bounds__(256) k_split_out(Params P, int64_t k0, Part32 
     dst[6 * n + d] = (double)in.w[s];
 }
 
-static BinRanks bin_ranks(Ctx &c, int sp) {
+// groups: lab groups to clear with it, or null
+static BinRanks bin_ranks(Ctx &c, int sp, double *groups = nullptr, int ng = 0) {
     SplitState &X = SS(c);
     Store &s = X.s[sp];
-    const int cur = c.cur32;
-    hipLaunchKernelGGL(k_split_prefix, dim3(1), dim3(1024), 0, c.st, s.off[cur], s.cnt[cur], s.ovf[cur], s.ovf_cap,
-                       c.P.nbins, X.tmpoff);
-    return BinRanks{X.tmpoff, s.off[cur], s.bin_slots, c.P.nbins};
+    const int cur = c.cur32, nbins = c.P.nbins, blocks = nbins <= FEW_BINS ? 1 : nblocks(nbins, PREFIX_BINS);
+    int64_t *totals = (int64_t *)X.tmpcnt;  // 8 bytes a bin, used while the bins are laid out only
+    if (blocks > 1)
+        hipLaunchKernelGGL(k_split_totals, dim3(blocks), dim3(1024), 0, c.st, s.off[cur], s.cnt[cur], nbins, totals);
+    hipLaunchKernelGGL(k_split_prefix, dim3(blocks), dim3(1024), 0, c.st, s.off[cur], s.cnt[cur], s.ovf[cur],
+                       s.ovf_cap, nbins, totals, X.tmpoff, groups, ng);
+    return BinRanks{X.tmpoff, s.off[cur], s.bin_slots, nbins};
 }
 
 void split_read(Ctx &c, int sp, double *dst7, int32_t *alive, int64_t *n) {
@@ -2244,11 +2279,48 @@ __global__ void __launch_bounds__(DT) k_split_lab_groups(Params P, LabGroupSpec 
     lab_table_flush(tab, ng, out);
 }
 
+// The same for a small beam: workgroups stride over the bins (and the overflow tail, "bin" nbins), every
+// particle added by its lane.
+__global__ void __launch_bounds__(DT) k_split_lab_groups_few(Params P, LabGroupSpec G, int64_t k0, Part32 in,
+                                                             const int64_t *off, const int32_t *cnt,
+                                                             int64_t ovf_start, const int32_t *ovf, int64_t ovf_cap,
+                                                             double t, double *out) {
+    __shared__ double tab[LAB_GROUP_VALUES * LAB_GROUPS_MAX];
+    const int ng = G.nz * G.nu;
+    lab_table_clear(tab, ng);
+    __syncthreads();
+    for (int b = blockIdx.x; b <= P.nbins; b += gridDim.x) {
+        const int64_t s0 = b < P.nbins ? off[b] : ovf_start;
+        const int64_t n = b < P.nbins ? (int64_t)bin_count(off, cnt, b) : min((int64_t)*ovf, ovf_cap);
+        for (int64_t e = threadIdx.x; e < n; e += DT) {
+            const int64_t s = s0 + e;
+            int i, j, l;
+            unpack_cell(P, in.cell[s], i, j, l);
+            lab_group_add(tab, G, P, t, (i + 0.5) + (double)in.ox[s], (j + 0.5) + (double)in.oy[s],
+                          ((double)(k0 + l) + 0.5) + (double)in.oz[s], in.ux[s], in.uy[s], in.uz[s], in.w[s]);
+        }
+    }
+    __syncthreads();
+    lab_table_flush(tab, ng, out);
+}
+
 void split_lab_groups(Ctx &c, const LabGroupSpec &G, double t, double *out) {
     const Store &S = SS(c).s[0];
-    const BinRanks R = bin_ranks(c, 0);
+    const int cur = c.cur32, ng = G.nz * G.nu;
+    // Numbering the store takes some 12 us of a call; a beam too small to keep one workgroup busy for that
+    // long, were it all in one bin (2.6 ns a particle), goes without, unless there are more bins than one
+    // block numbers, of which each workgroup would visit sixteen or more.  us a call, 64 groups, with / without:
+    // 32 x 32 x 64 with 1000 particles 46 / 35, with 16384 46 / 53 (all in one bin: 45 / 75),
+    // 128 x 128 x 512 with 1000 51 / 39, 256 x 256 x 1024 (65536 bins) with 1000 52 / 59.
+    if (c.beam.n_macro <= 8192 && c.P.nbins <= FEW_BINS) {
+        lab_groups_clear(out, ng, c.st);
+        hipLaunchKernelGGL(k_split_lab_groups_few, dim3(std::min(c.P.nbins + 1, SUM_ROWS)), dim3(DT), 0, c.st, c.P, G,
+                           c.k0, S.buf[cur], S.off[cur], S.cnt[cur], S.bin_slots, S.ovf[cur], S.ovf_cap, t, out);
+        return;
+    }
+    const BinRanks R = bin_ranks(c, 0, out, ng);
     hipLaunchKernelGGL(k_split_lab_groups, dim3(sum_rows(c.beam.n_macro)), dim3(DT), 0, c.st, c.P, G, c.k0,
-                       S.buf[c.cur32], R, t, out);
+                       S.buf[cur], R, t, out);
 }
 
 void split_probe(Ctx &c, double *acc) {
