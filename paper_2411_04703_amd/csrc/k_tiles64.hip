@@ -42,8 +42,10 @@ static int64_t bins_of(const Params &P) {
 
 uint64_t tiles64_bytes(const Params &P, int64_t slots) {
     const uint64_t nb = (uint64_t)bins_of(P), n = (uint64_t)std::max<int64_t>(slots, 1);
-    return 2 * al(4 * nb) + al(16 * (nb + n / CHUNK_MIN + 16)) + al(8 * (nb / SCAN_BINS + 1)) + 256 * 9;
+    return al(4 * nb) + al(16 * (nb + n / CHUNK_MIN + 16)) + al(8 * (nb / SCAN_BINS + 1)) + 256 * 9;
 }
+
+uint64_t tiles64_count_bytes(const Params &P) { return 4 * (uint64_t)bins_of(P); }
 
 uint64_t tiles64_list_bytes(int64_t slots) { return 3 * al(4 * (uint64_t)std::max<int64_t>(slots, 1)); }
 
@@ -426,7 +428,7 @@ k_step64(Params P, StepCtx S, Bounds64 W, Species64 sb, Species64 sp, TileList T
 
 template <class G> static constexpr int step_lds() { return 8 * (G::NF + G::NJ); }
 
-pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots) {
+pic_status tiles64_carve(Ctx &c, char *cnt, char *base, char *room, int64_t slots) {
     const uint64_t nb = (uint64_t)bins_of(c.P), n = (uint64_t)std::max<int64_t>(slots, 1);
     TileList &T = c.tiles;
     tiles64_dims(c.P, T.ntx, T.nty, T.ntz);
@@ -436,7 +438,7 @@ pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots) {
         base += al(bytes);
         return r;
     };
-    T.cnt = (uint32_t *)take(4 * nb);
+    T.cnt = (uint32_t *)cnt;
     T.off = (uint32_t *)take(4 * nb);
     T.room = room;
     if (room) place_lists(T, room, slots);
@@ -444,7 +446,6 @@ pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots) {
     T.totals = (uint2 *)take(8 * (nb / SCAN_BINS + 1));
     T.qnext = (int32_t *)take(256 * 8);
     T.nitems = (int32_t *)take(256);
-    PIC_HIP(c, hipMemsetAsync(T.cnt, 0, 4 * nb, c.st));
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, c.device) == hipSuccess && prop.multiProcessorCount > 0)
         c.ncu = (prop.multiProcessorCount + 7) / 8 * 8;

@@ -247,6 +247,7 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         pl.cap_p = P.has_plasma ? fill + (between + 2) * sheets_per_step(P) * sheet : 0;
         for (int k = 0; k < 9; ++k) off[k] = take(8 * P.nc);             // E B J
         off[9] = take(8 * P.nz);                                          // jion
+        off[10] = take(tiles64_count_bytes(P));  // particles of each tile; cleared with what lies before them
         off[11] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_b, 1));   // beam
         off[12] = take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));   // plasma
         off[13] = pl.record ? 0 : take(60 * (uint64_t)std::max<int64_t>(pl.cap_p, 1));  // plasma (compaction)
@@ -589,9 +590,6 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         c->fc_rho = (double *)(A + off[26]);
     }
     hipError_t e = hipMemsetAsync(c->dflags, 0, 256, c->st);
-    // the ion profile; in FP32 mode both, which alternate whether or not the run has ions that write them
-    if (e == hipSuccess)
-        e = hipMemsetAsync(A + off[9], 0, (pl.precision == PIC_FP64_PLAIN ? 8 : 16) * P.nz, c->st);
     if (pl.precision == PIC_FP64_PLAIN) {
         for (int k = 0; k < 3; ++k) {
             c->E64[k] = (double *)(A + off[k]);
@@ -599,7 +597,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
             c->J64[k] = (double *)(A + off[6 + k]);
         }
         c->jion64 = (double *)(A + off[9]);
-        if (e == hipSuccess) e = hipMemsetAsync(A + off[0], 0, off[9] - off[0], c->st);
+        if (e == hipSuccess) e = hipMemsetAsync(A + off[0], 0, off[10] + tiles64_count_bytes(P) - off[0], c->st);
         c->b64 = carve64(A + off[11], c->cap_b);
         c->p64 = carve64(A + off[12], c->cap_p);
         if (!pl.record) c->p64alt = carve64(A + off[13], c->cap_p);
@@ -607,7 +605,7 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         char *room = pl.lists == Plan::LISTS_IN_COMPACTION ? nullptr
                      : pl.lists == Plan::LISTS_IN_STAGING  ? (char *)c->stage
                                                            : A + off[30];
-        if (e == hipSuccess && tiles64_carve(*c, A + off[27], room, c->cap_b + c->cap_p) != PIC_OK)
+        if (e == hipSuccess && tiles64_carve(*c, A + off[10], A + off[27], room, c->cap_b + c->cap_p) != PIC_OK)
             e = hipErrorUnknown;
         if (e == hipSuccess && pl.record && adjoint_setup(*c) != PIC_OK) e = hipErrorUnknown;
     } else {
@@ -622,7 +620,8 @@ pic_status pic_init(const pic_grid *g, const pic_frame *f, const pic_beam *b, co
         }
         c->jioni = (long long *)(A + off[9]);
         c->jionn = c->jioni + P.nz;
-        if (e == hipSuccess) e = hipMemsetAsync(A + off[0], 0, off[9] - off[0], c->st);
+        // with both ion profiles, which alternate whether or not the run has ions that write them
+        if (e == hipSuccess) e = hipMemsetAsync(A + off[0], 0, off[9] + 2 * 8 * (uint64_t)P.nz - off[0], c->st);
     }
     if (e != hipSuccess) {
         hip_check(*c, e, "pic_init memset");

@@ -145,7 +145,8 @@ int64_t compact64(Ctx &c, Part64 src, Part64 dst, int64_t n);  // returns surviv
 // FP64 particles on cell tiles (k_tiles64.hip)
 uint64_t tiles64_bytes(const Params &P, int64_t slots);  // arena bytes of the tiles and work items
 uint64_t tiles64_list_bytes(int64_t slots);              // and of the particle lists (room)
-pic_status tiles64_carve(Ctx &c, char *base, char *room, int64_t slots);
+uint64_t tiles64_count_bytes(const Params &P);           // and of the tiles' counts (cnt, zero at the start)
+pic_status tiles64_carve(Ctx &c, char *cnt, char *base, char *room, int64_t slots);
 void step64_particles(Ctx &c, const StepCtx &S, FieldsT<double> f);  // gather, push, move, deposit of both species
 
 void rho64(Ctx &c, double *rho, int mask);  // charge of beam (bit 0) and plasma (bit 1) added into rho (ring order)
