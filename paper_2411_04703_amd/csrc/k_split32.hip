@@ -1233,15 +1233,28 @@ __global__ void __launch_bounds__(ST) k_rebin(Params P, WorkList W, const Specie
                    q.u, q.w, flags, iids[sp].out, q.id);
         }
     };
-    for (int q = 0; q < 2 * W.nslab; ++q)
-        for (int k = blockIdx.x; k < W.count[q]; k += gridDim.x) {
+    // pieces numbered through, the queues' and then the tails', taken from one counter (the first queue's):
+    // 6.38 ms for two starts and re-layouts where fixed shares took 6.94 (256 x 256 x 1024, 128 x 128 x 512)
+    __shared__ int s_piece;
+    for (;;) {
+        if (threadIdx.x == 0) s_piece = atomicAdd(&W.next[0], 1);
+        __syncthreads();
+        int k = s_piece;
+        __syncthreads();
+        int q = 0, sp = 0, n = 0;
+        for (; q < 2 * W.nslab && k >= W.count[q]; ++q) k -= W.count[q];
+        if (q < 2 * W.nslab) {
             const Item it = W.items[W.base(q) + k];
             move(it.sp, it.b0, it.start, it.end);
+            continue;
         }
-    for (int sp = 0; sp < 2; ++sp) {
-        const int n = (int)min((int64_t)*ios[sp].in_ovf, ios[sp].in_ovf_cap);
-        for (int start = blockIdx.x * ST; start < n; start += gridDim.x * ST)
-            move(sp, ios[sp].in_ovf_start, start, min(n, start + ST));
+        for (; sp < 2; ++sp) {
+            n = (int)min((int64_t)*ios[sp].in_ovf, ios[sp].in_ovf_cap);
+            if (k < (n + CH - 1) / CH) break;
+            k -= (n + CH - 1) / CH;
+        }
+        if (sp == 2) return;
+        move(sp, ios[sp].in_ovf_start, k * CH, min(n, (k + 1) * CH));
     }
 }
 
