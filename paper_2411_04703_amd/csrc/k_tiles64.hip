@@ -321,7 +321,7 @@ template <class G, int C> __device__ inline void deposit_lds(double *Js, const i
 // and deposit into the LDS current boxes, which are added to the grid at the end.  One thread per
 // particle over the grid (fields from global memory, every contribution a global FP64 atomic) took
 // 25.5 ms for the 128x128x512 run's 4.2 M beam and 16.5 M plasma particles; this takes 2.1 ms and
-// its lists 0.37.  Bound: the plasma's 1.2 ms by VALU (1430 instructions a wave, 55 % busy) and LDS
+// its lists 0.34.  Bound: the plasma's 1.2 ms by VALU (1430 instructions a wave, 55 % busy) and LDS
 // (162 reads and 27 to 144 FP64 adds of 8 clocks a wave), the beam's 0.9 ms by its slots, which are
 // in no order (a 64-byte line for every 8 bytes read or written; 0.4 ms were they in tile order).
 // Two 512-thread workgroups share a CU, so that one's rounds run under the other's staging and
