@@ -32,8 +32,9 @@ static pic_status fail(std::string *err, pic_status s, const std::string &msg) {
 
 // ---------------------------------------------------------------- derivation
 // FP32 grids up to this many cells hold E and B twice, so that a step updates them in one pass
-// (k_fields); 24 bytes a cell, 3.2 GB at the limit.  Larger grids keep the memory for cells and
-// update in place, in two passes (B; E with the faces) and one over a plane when the window shifts.
+// (k_fields): 24 bytes a cell, 3.2 GB at the limit, unless a buffer that is idle then has room
+// (make_plan).  Larger grids keep the memory for cells and update in place, in two passes (B; E with the
+// faces) and one over a plane when the window shifts.
 constexpr int64_t FIELDS_TWICE = (int64_t)1 << 27;
 
 struct Plan {
@@ -267,7 +268,6 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
         for (int k = 0; k < 6; ++k) off[k] = take(4 * P.nc);  // E B float
         for (int k = 6; k < 9; ++k) off[k] = take(8 * P.nc);  // J int64
         off[9] = take(2 * 8 * P.nz);  // jion, twice
-        if (P.nc <= FIELDS_TWICE) off[28] = take(6 * al256(4 * P.nc));  // E B of the next step
         // particle double buffers with bin slack and an overflow tail (k_split32.hip)
         int64_t nbins = P.nbins;
         // bin slack: the beam pinches and moves between re-layouts, so its bins get 1/2 of their count as
@@ -297,6 +297,14 @@ static pic_status make_plan(const pic_grid *g, const pic_frame *f, const pic_bea
     off[17] = pl.record ? take(8 * 6 * P.nc) : 0;                   // adjoint scratch
     off[29] = pl.record ? take(16 * (uint64_t)ADJ_PARTS) : 0;       // its partial sums
     off[18] = take(8 * 6 * (uint64_t)std::max<int64_t>(b->n_macro, 1));  // normals staging
+    if (o->precision == PIC_FP32_SPLIT && P.nc <= FIELDS_TWICE) {
+        // E, B of the next step: in the adjoint's scratch, which is the FP64 mode's, or the normals' staging,
+        // read before the first step, where they hold them
+        const uint64_t twice = 6 * al256(4 * (uint64_t)P.nc);
+        off[28] = pl.record && twice <= 8 * 6 * (uint64_t)P.nc ? off[17]
+                  : twice <= 8 * 6 * (uint64_t)b->n_macro      ? off[18]
+                                                               : take(twice);
+    }
     off[19] = take(256);                                            // device flags + lab-probe sums
     off[22] = take(8 * 2 * (uint64_t)(nblocks(nmax, 256) + 4));     // scan scratch
     if (o->init_fields == 2) {
